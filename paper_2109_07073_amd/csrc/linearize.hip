@@ -55,6 +55,27 @@ __device__ __forceinline__ void relative_pose64(const double *__restrict__ pi,
   for (int r = 0; r < 3; ++r) t[r] = (pj[r] * d0 + pj[3 + r] * d1) + pj[6 + r] * d2;
 }
 
+// Entry l of the same pose (l < 9: the rotation, row-major; else the
+// translation), the same bits.  Called by whole waves with l = min(lane, 11):
+// the twelve entries cost one entry's instructions.
+__device__ __forceinline__ double relative_pose_entry(const double *__restrict__ pi,
+                                                      const double *__restrict__ pj, uint32_t l) {
+#pragma clang fp contract(off)
+  const bool rot = l < 9u;
+  const uint32_t r = rot ? l / 3u : l - 9u;
+  const uint32_t c = rot ? l - 3u * r : 0u;
+  const bool same =
+      __builtin_amdgcn_ballot_w64(__double_as_longlong(pi[l]) != __double_as_longlong(pj[l])) == 0;
+  double v[3];
+#pragma unroll
+  for (int k = 0; k < 3; ++k) {
+    const double x = pi[rot ? c + 3 * k : 9 + k];
+    v[k] = rot ? x : x - pj[9 + k];
+  }
+  const double e = (pj[r] * v[0] + pj[3 + r] * v[1]) + pj[6 + r] * v[2];
+  return same ? (rot && l % 4u == 0u ? 1.0 : 0.0) : e;
+}
+
 // The FP32 coordinates, in voxel units, that decide the correspondence of a
 // point (the voxel holding T_j^-1 T_i mu, Sec. III-A): three fused
 // multiply-adds per axis with the rotation and translation scaled by the
@@ -1522,28 +1543,118 @@ hipError_t launch_voxel_order_keys(const vgicp_factorset_s *fs, const double *po
 }
 
 // ---------------------------------------------------------------- reduce
-// One 64-lane block per factor: add the factor's tile partials in tile order
-// (FP64), then expand the source-frame system to the 12x12 Hessian factor.
+// The sum of p[0], p[step], ... (n values) in that order, with 16 loads in
+// flight at once.
+__device__ __forceinline__ double column_sum(const double *__restrict__ p, int64_t step,
+                                             int32_t n) {
+  double acc = 0.0;
+  for (int32_t t = 0; t < n; t += 16) {
+    double x[16];
+#pragma unroll
+    for (int u = 0; u < 16; ++u) x[u] = p[min(t + u, n - 1) * step];
+#pragma unroll
+    for (int u = 0; u < 16; ++u)
+      if (t + u < n) acc += x[u];
+  }
+  return acc;
+}
+
+// One block per factor: add the factor's tile partials in tile order (FP64),
+// then expand the source-frame system to the 12x12 Hessian factor.
 //   mode 0: linearize (H, b, e, inliers)   1: cost only (e, inliers)
 //   mode 2: overlap (hits, overlap)
-__global__ void __launch_bounds__(64)
+// Bound by latency: a factor's rows (256 bytes each) come from other XCDs'
+// blocks, so each load is a trip to memory.  Both variants add in the same
+// order and give the same bits:
+//   narrow: one wave, a lane per column with 16 loads in flight;
+//   wide:   four waves with up to kReduceRows rows in flight at once, staged
+//           in LDS, where a lane per column adds them, while the last wave
+//           computes the relative pose.
+// (One load in flight per lane took 10.7 us for 45 factors of 27 tiles and 16
+// us for 48 factors of up to 53.)
+constexpr int kReduceRows = 64;
+constexpr int kReduceQuads = kReduceRows / 16;  // 16 rows per 16-byte load of the block
+
+// Whether factors of `tiles` tiles on average use the wide variant: beyond 16
+// the narrow one takes a second trip to memory.
+static inline bool reduce_wide(int64_t factors, int64_t tiles) { return tiles > 16 * factors; }
+
+// Entry l < 36 of Ad(T^-1) = [[R^T, 0], [-R^T [t]x, R^T]], (omega, rho) order,
+// from T = (R row-major, t).
+__device__ __forceinline__ double adjoint_entry(const double *T, int l) {
+  const int r = l / 6, c = l % 6;
+  if ((r < 3) == (c < 3)) return T[3 * (c % 3) + r % 3];
+  if (r < 3) return 0.0;
+  // minus row r - 3 of R^T times column c of [t]x, which is t x e_c
+  const int c1 = (c + 1) % 3, c2 = (c + 2) % 3;
+  return T[3 * c2 + r - 3] * T[9 + c1] - T[3 * c1 + r - 3] * T[9 + c2];
+}
+
+template <bool WIDE>
+__global__ void __launch_bounds__(WIDE ? kBlock : 64)
 k_reduce(const FactorDesc *__restrict__ factors, int64_t factor_base,
          const double *__restrict__ poses, const double *__restrict__ partials, int mode,
          double *__restrict__ H, double *__restrict__ b, double *__restrict__ e,
          int64_t *__restrict__ inl, double *__restrict__ overlap) {
+  constexpr int kThreads = WIDE ? kBlock : 64;
   __shared__ double s[kPartialStride];
-  __shared__ double Hr[36], Ad[36], K[36], Hjj[36];
+  __shared__ double T[12], Hr[36], Ad[36], K[36], Hjj[36];
   const int64_t f = factor_base + blockIdx.x;
-  const FactorDesc fd = factors[f];
+  const FactorDesc &fd = factors[f];
+  const int32_t n_tiles = fd.n_tiles;
   const int lane = threadIdx.x;
-  if (lane <= kNumSums) {
-    double acc = 0.0;
-    const bool used = (mode == 0) || lane >= 27;
+  const bool used = lane <= kNumSums && (mode == 0 || lane >= 27);
+  double acc = 0.0;
+  // the adjoint, by one wave (l: its lane)
+  auto adjoint = [&](int l) {
+    const double p = relative_pose_entry(poses + 12 * int64_t(fd.pose_i),
+                                         poses + 12 * int64_t(fd.pose_j), uint32_t(min(l, 11)));
+    if (l < 12) T[l] = p;
+    __builtin_amdgcn_wave_barrier();
+    if (l < 36) Ad[l] = adjoint_entry(T, l);
+  };
+  if constexpr (WIDE) {
+    __shared__ double2 rows[kReduceRows * kPartialStride / 2];
+    const int64_t stride = int64_t(fd.tile_stride) * (kPartialStride / 2);
+    const double2 *__restrict__ part = reinterpret_cast<const double2 *>(partials) +
+                                       int64_t(fd.tile_begin) * (kPartialStride / 2);
+    const int row = lane >> 4, col = lane & 15;
+    int32_t t0 = 0;
+    do {  // once for a factor without tiles
+      double2 v[kReduceQuads];
+#pragma unroll
+      for (int q = 0; q < kReduceQuads; ++q) {
+        const int32_t t = t0 + q * 16 + row;
+        if (t < n_tiles) v[q] = part[t * stride + col];
+      }
+      if (t0 == 0 && mode == 0 && lane >= kThreads - 64) adjoint(lane - (kThreads - 64));
+      if (t0 > 0) __syncthreads();  // the previous rows have been added
+#pragma unroll
+      for (int q = 0; q < kReduceQuads; ++q)
+        if (t0 + q * 16 + row < n_tiles) rows[(q * 16 + row) * (kPartialStride / 2) + col] = v[q];
+      __syncthreads();
+      if (used) {
+        const double *c = reinterpret_cast<const double *>(rows) + lane;
+        const int32_t m = min(n_tiles - t0, kReduceRows);
+        int32_t r = 0;
+        for (; r + 8 <= m; r += 8) {
+          double x[8];
+#pragma unroll
+          for (int u = 0; u < 8; ++u) x[u] = c[(r + u) * kPartialStride];
+#pragma unroll
+          for (int u = 0; u < 8; ++u) acc += x[u];
+        }
+        for (; r < m; ++r) acc += c[r * kPartialStride];
+      }
+      t0 += kReduceRows;
+    } while (t0 < n_tiles);
+  } else {
+    if (mode == 0) adjoint(lane);
     if (used)
-      for (int32_t tt = 0; tt < fd.n_tiles; ++tt)
-        acc += partials[(fd.tile_begin + int64_t(tt) * fd.tile_stride) * kPartialStride + lane];
-    s[lane] = acc;
+      acc = column_sum(partials + int64_t(fd.tile_begin) * kPartialStride + lane,
+                       int64_t(fd.tile_stride) * kPartialStride, n_tiles);
   }
+  if (lane <= kNumSums) s[lane] = acc;
   __syncthreads();
   if (mode == 2) {
     if (lane == 0) {
@@ -1567,22 +1678,6 @@ k_reduce(const FactorDesc *__restrict__ factors, int64_t factor_base,
     const int idx = lo * 6 - lo * (lo - 1) / 2 + (hi - lo);
     Hr[lane] = s[idx];
   }
-  if (lane == 0) {
-    double R[9], t[3];
-    relative_pose64(poses + 12 * int64_t(fd.pose_i), poses + 12 * int64_t(fd.pose_j), R, t);
-    // Ad(T^-1) = [[R^T, 0], [-R^T [t]x, R^T]] in (omega, rho) order
-    const double tx[9] = {0.0, -t[2], t[1], t[2], 0.0, -t[0], -t[1], t[0], 0.0};
-    for (int r = 0; r < 3; ++r)
-      for (int c = 0; c < 3; ++c) {
-        const double RT = R[3 * c + r];
-        double RTt = 0.0;
-        for (int a = 0; a < 3; ++a) RTt += R[3 * a + r] * tx[3 * a + c];
-        Ad[6 * r + c] = RT;
-        Ad[6 * r + 3 + c] = 0.0;
-        Ad[6 * (3 + r) + c] = -RTt;
-        Ad[6 * (3 + r) + 3 + c] = RT;
-      }
-  }
   __syncthreads();
   if (lane < 36) {  // K = Hr Ad
     const int r = lane / 6, c = lane % 6;
@@ -1600,7 +1695,7 @@ k_reduce(const FactorDesc *__restrict__ factors, int64_t factor_base,
   }
   __syncthreads();
   double *__restrict__ Hf = H + f * 144;
-  for (int idx = lane; idx < 144; idx += 64) {
+  for (int idx = lane; idx < 144; idx += kThreads) {
     const int r = idx / 12, c = idx % 12;
     double v;
     if (r < 6 && c < 6) v = Hr[6 * r + c];
@@ -1619,33 +1714,28 @@ k_reduce(const FactorDesc *__restrict__ factors, int64_t factor_base,
   }
 }
 
-// Pair form: one 64-lane block per factor adds the factor's tile partials in
-// tile order (FP64) and writes the 12 x 12 H from its upper triangle, b, e
-// and the inliers.
-__global__ void __launch_bounds__(64)
+// Pair form: one 128-lane block per factor adds the factor's tile partials in
+// tile order (FP64; a lane per column) and writes the 12 x 12 H from its upper
+// triangle, b, e and the inliers.
+__global__ void __launch_bounds__(128)
 k_reduce_pair(const FactorDesc *__restrict__ factors, int64_t factor_base,
               const double *__restrict__ partials, const double *__restrict__ partials_pair,
               double *__restrict__ H, double *__restrict__ b, double *__restrict__ e,
               int64_t *__restrict__ inl) {
   __shared__ double s[kPairStride];
   const int64_t f = factor_base + blockIdx.x;
-  const FactorDesc fd = factors[f];
+  const FactorDesc &fd = factors[f];
   const int lane = threadIdx.x;
-  for (int i = lane; i < kNumPairSums; i += 64) {
-    double acc = 0.0;
-    for (int32_t tt = 0; tt < fd.n_tiles; ++tt)
-      acc += partials_pair[(fd.tile_begin + int64_t(tt) * fd.tile_stride) * kPairStride + i];
-    s[i] = acc;
-  }
-  if (lane == 0) {
-    double hits = 0.0;
-    for (int32_t tt = 0; tt < fd.n_tiles; ++tt)
-      hits += partials[(fd.tile_begin + int64_t(tt) * fd.tile_stride) * kPartialStride + kNumSums];
-    inl[f] = int64_t(hits);
-  }
+  const int64_t first = fd.tile_begin, stride = fd.tile_stride;
+  if (lane < kNumPairSums)
+    s[lane] = column_sum(partials_pair + first * kPairStride + lane, stride * kPairStride,
+                         fd.n_tiles);
+  else if (lane == kNumPairSums)
+    inl[f] = int64_t(column_sum(partials + first * kPartialStride + kNumSums,
+                                stride * kPartialStride, fd.n_tiles));
   __syncthreads();
   double *__restrict__ Hf = H + f * 144;
-  for (int idx = lane; idx < 144; idx += 64) {
+  for (int idx = lane; idx < 144; idx += 128) {
     const int r = idx / 12, c = idx % 12;
     Hf[idx] = r <= c ? s[pair_index(r, c)] : s[pair_index(c, r)];
   }
@@ -1654,50 +1744,73 @@ k_reduce_pair(const FactorDesc *__restrict__ factors, int64_t factor_base,
 }
 
 // ---------------------------------------------------------------- assembly
-// One 64-lane block per pose: lanes 0..35 own an entry of the 6x6 diagonal
-// block, lanes 36..41 an entry of b.  Contributions are added in CSR order
-// (factor order), so the sums are deterministic.  An entry is factor * 4 +
-// side (0: the pose is the factor's pose i, 1: pose j) + 2 when the factor's
-// two poses coincide; such a factor's pose-i entry also adds H_ij + H_ij^T.
-__global__ void __launch_bounds__(64)
-k_assemble_diag(const int64_t *__restrict__ off, const int64_t *__restrict__ ent,
-                const double *__restrict__ H, const double *__restrict__ b,
-                double *__restrict__ Hdiag, double *__restrict__ bvec) {
-  const int p = blockIdx.x, lane = threadIdx.x;
-  if (lane >= 42) return;
+// Bound by latency: contributions are added in CSR order, and each is an
+// entry read and then a block of H read at the place it names.  kAssembleBatch
+// entries are read together, then their blocks together, so that a pose of a
+// submap (some twenty contributions) takes three round trips to memory
+// instead of forty.
+constexpr int kAssembleBatch = 16;
+
+// The sum over the list entries [k0, k1) of term(entry), in list order.
+template <typename Term>
+__device__ __forceinline__ double csr_sum(const int64_t *__restrict__ ent, int64_t k0, int64_t k1,
+                                          Term term) {
   double acc = 0.0;
-  for (int64_t k = off[p]; k < off[p + 1]; ++k) {
-    const int64_t f = ent[k] >> 2;
-    const int o = 6 * (ent[k] & 1);
-    if (lane < 36) {
-      const int r = lane / 6, c = lane % 6;
-      acc += H[f * 144 + (o + r) * 12 + (o + c)];
-      if (ent[k] & 2) acc += H[f * 144 + r * 12 + (6 + c)] + H[f * 144 + (6 + r) * 12 + c];
-    } else {
-      acc += b[f * 12 + o + (lane - 36)];
-    }
+  for (; k0 < k1; k0 += kAssembleBatch) {
+    int64_t en[kAssembleBatch];
+    double x[kAssembleBatch];
+#pragma unroll
+    for (int u = 0; u < kAssembleBatch; ++u) en[u] = ent[min(k0 + u, k1 - 1)];
+#pragma unroll
+    for (int u = 0; u < kAssembleBatch; ++u)
+      if (k0 + u < k1) x[u] = term(en[u]);
+#pragma unroll
+    for (int u = 0; u < kAssembleBatch; ++u)
+      if (k0 + u < k1) acc += x[u];
   }
-  if (lane < 36)
-    Hdiag[int64_t(p) * 36 + lane] = acc;
-  else
-    bvec[int64_t(p) * 6 + (lane - 36)] = acc;
+  return acc;
 }
 
-// One 64-lane block per unordered pose pair (p, q), p < q: block (p, q) is the
-// sum of H_ij over factors (i, j) = (p, q) and of H_ij^T over (i, j) = (q, p).
+// One 64-lane block per pose, then one per unordered pose pair (p, q), p < q.
+// Pose blocks: lanes 0..35 own an entry of the 6x6 diagonal block, lanes
+// 36..41 an entry of b.  Contributions are added in CSR order (factor order),
+// so the sums are deterministic.  An entry is factor * 4 + side (0: the pose
+// is the factor's pose i, 1: pose j) + 2 when the factor's two poses coincide;
+// such a factor's pose-i entry also adds H_ij + H_ij^T.
+// Pair blocks: block (p, q) is the sum of H_ij over factors (i, j) = (p, q)
+// and of H_ij^T over (i, j) = (q, p) (entries factor * 2 + flip).
 __global__ void __launch_bounds__(64)
-k_assemble_pairs(const int64_t *__restrict__ off, const int64_t *__restrict__ ent,
-                 const double *__restrict__ H, double *__restrict__ Hoff) {
-  const int q = blockIdx.x, lane = threadIdx.x;
-  if (lane >= 36) return;
+k_assemble(int32_t n_poses, const int64_t *__restrict__ pose_off,
+           const int64_t *__restrict__ pose_ent, const int64_t *__restrict__ pair_off,
+           const int64_t *__restrict__ pair_ent, const double *__restrict__ H,
+           const double *__restrict__ b, double *__restrict__ Hdiag, double *__restrict__ bvec,
+           double *__restrict__ Hoff) {
+  const int lane = threadIdx.x;
   const int r = lane / 6, c = lane % 6;
-  double acc = 0.0;
-  for (int64_t k = off[q]; k < off[q + 1]; ++k) {
-    const int64_t f = ent[k] >> 1;
-    const bool flip = ent[k] & 1;
-    acc += flip ? H[f * 144 + (6 + r) * 12 + c] : H[f * 144 + r * 12 + (6 + c)];
+  if (blockIdx.x < uint32_t(n_poses)) {
+    const int64_t p = blockIdx.x;
+    const int64_t k0 = pose_off[p], k1 = pose_off[p + 1];
+    if (lane < 36) {
+      Hdiag[p * 36 + lane] = csr_sum(pose_ent, k0, k1, [&](int64_t en) {
+        const double *Hf = H + (en >> 2) * 144;
+        const int o = 6 * int(en & 1);
+        double x = Hf[(o + r) * 12 + (o + c)];
+        if (en & 2) x += Hf[r * 12 + (6 + c)] + Hf[(6 + r) * 12 + c];
+        return x;
+      });
+    } else if (lane < 42) {
+      bvec[p * 6 + (lane - 36)] = csr_sum(pose_ent, k0, k1, [&](int64_t en) {
+        return b[(en >> 2) * 12 + 6 * int(en & 1) + (lane - 36)];
+      });
+    }
+    return;
   }
-  Hoff[int64_t(q) * 36 + lane] = acc;
+  if (lane >= 36) return;
+  const int64_t q = blockIdx.x - uint32_t(n_poses);
+  Hoff[q * 36 + lane] = csr_sum(pair_ent, pair_off[q], pair_off[q + 1], [&](int64_t en) {
+    const double *Hf = H + (en >> 1) * 144;
+    return (en & 1) ? Hf[(6 + r) * 12 + c] : Hf[r * 12 + (6 + c)];
+  });
 }
 
 // ---------------------------------------------------------------- launchers
@@ -1907,7 +2020,7 @@ hipError_t launch_linearize_pair(const vgicp_factorset_s *fs, int accum, int res
 hipError_t launch_reduce_pair(const vgicp_factorset_s *fs, int64_t f0, int64_t nf, double *H,
                               double *b, double *e, int64_t *inl, hipStream_t st) {
   if (nf <= 0) return hipSuccess;
-  k_reduce_pair<<<unsigned(nf), 64, 0, st>>>(fs->d_factors, f0, fs->d_partials,
+  k_reduce_pair<<<unsigned(nf), 128, 0, st>>>(fs->d_factors, f0, fs->d_partials,
                                               fs->d_partials_pair, H, b, e, inl);
   return hipGetLastError();
 }
@@ -1922,18 +2035,12 @@ hipError_t launch_overlap(const vgicp_factorset_s *fs, int64_t tb, int64_t te,
 
 hipError_t launch_assemble(const vgicp_factorset_s *fs, const double *H, const double *b,
                            double *Hdiag, double *bvec, double *Hoff, hipStream_t st) {
-  if (fs->n_poses > 0) {
-    k_assemble_diag<<<unsigned(fs->n_poses), 64, 0, st>>>(fs->d_pose_off, fs->d_pose_ent, H, b,
-                                                         Hdiag, bvec);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-  }
-  if (Hoff && fs->n_pairs > 0) {
-    k_assemble_pairs<<<unsigned(fs->n_pairs), 64, 0, st>>>(fs->d_pair_off, fs->d_pair_ent, H,
-                                                           Hoff);
-    return hipGetLastError();
-  }
-  return hipSuccess;
+  const int64_t blocks = int64_t(fs->n_poses) + (Hoff ? fs->n_pairs : 0);
+  if (blocks <= 0) return hipSuccess;
+  k_assemble<<<unsigned(blocks), 64, 0, st>>>(fs->n_poses, fs->d_pose_off, fs->d_pose_ent,
+                                              fs->d_pair_off, fs->d_pair_ent, H, b, Hdiag, bvec,
+                                              Hoff);
+  return hipGetLastError();
 }
 
 hipError_t launch_reduce_from(const vgicp_factorset_s *fs, int64_t f0, int64_t nf,
@@ -1941,8 +2048,12 @@ hipError_t launch_reduce_from(const vgicp_factorset_s *fs, int64_t f0, int64_t n
                               double *b, double *e, int64_t *inl, double *overlap,
                               hipStream_t st) {
   if (nf <= 0) return hipSuccess;
-  k_reduce<<<unsigned(nf), 64, 0, st>>>(fs->d_factors, f0, poses, partials, mode, H, b, e, inl,
-                                         overlap);
+  if (reduce_wide(fs->n_factors, fs->n_tiles))
+    k_reduce<true><<<unsigned(nf), kBlock, 0, st>>>(fs->d_factors, f0, poses, partials, mode, H, b,
+                                                    e, inl, overlap);
+  else
+    k_reduce<false><<<unsigned(nf), 64, 0, st>>>(fs->d_factors, f0, poses, partials, mode, H, b, e,
+                                                 inl, overlap);
   return hipGetLastError();
 }
 

@@ -1,0 +1,84 @@
+"""The reduce and assembly kernels at the edges of their batches.
+
+The reduce adds a factor's tile partials 16 or 64 at a time in one of two
+variants chosen by the set's average tiles per factor; both add in tile order,
+so they give the same bits.  The assembly adds a pose's contributions 16 at a
+time in list order."""
+
+import numpy as np
+import pytest
+
+from synth import make_tiny_workload
+from tests.gpu_helpers import GpuWorkload, assert_linearize_parity, oracle_results
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def vg():
+    import torch
+    assert torch.cuda.is_available(), "GPU tests need a GPU"
+    from paper_2109_07073_amd import vgicp
+    return vgicp
+
+
+@pytest.fixture(scope="module")
+def ctx(vg):
+    return vg.Context(0)
+
+
+@pytest.mark.parametrize("form", ["source", "pair"])
+@pytest.mark.parametrize("tiles", [1, 16, 17, 64, 65, 130])
+def test_tile_counts(vg, ctx, tiles, form):
+    w = make_tiny_workload(seed=700 + tiles, n_src=256 * tiles - 3, n_tgt=900, resolution=0.5)
+    g = GpuWorkload(vg, ctx, w, tile_points=256)
+    assert g.fs.n_tiles == tiles
+    got = g.linearize(form=form)
+    _, ref = oracle_results(w, with_corr=False)
+    assert_linearize_parity(got, ref)
+    # nine more factors without points: on average at most 16 tiles each
+    w.sources.append((np.zeros((0, 3), np.float32), np.zeros((0, 6), np.float32)))
+    w.factors = np.concatenate([w.factors, np.tile(np.array([[1, 0, 0, 1]], np.int32), (9, 1))])
+    many = GpuWorkload(vg, ctx, w, tile_points=256).linearize(form=form)
+    for k in ("H", "b", "e", "inliers"):
+        assert np.array_equal(many[k][0], got[k][0]), k
+        assert not np.any(many[k][1:]), k
+
+
+@pytest.mark.parametrize("n", [1, 15, 16, 17, 33])
+def test_contribution_counts(vg, ctx, n):
+    """Pose 0 joins n others (in both directions) and poses 1 and 0 are joined
+    n times more; random H and b, sums in FP64 against numpy's (an FP64 sum of
+    m terms is within m 2^-52 of the sum of their magnitudes)."""
+    import torch
+    w = make_tiny_workload(seed=720, n_src=50, n_tgt=50, resolution=1.0)
+    rows = [(0, 0, 0, k) if k % 2 else (0, 0, k, 0) for k in range(1, n + 1)]
+    rows += [(0, 0, 1, 0) if k % 3 else (0, 0, 0, 1) for k in range(n)] + [(0, 0, 0, 0)]
+    w.factors = np.array(rows, np.int32)
+    w.poses = np.tile(w.poses[:1], (n + 1, 1))
+    g = GpuWorkload(vg, ctx, w)
+    rng = np.random.default_rng(n)
+    H, b = rng.normal(size=(len(rows), 12, 12)), rng.normal(size=(len(rows), 12))
+    got = vg.assemble_system(ctx, g.fs, torch.from_numpy(H).cuda(), torch.from_numpy(b).cuda())
+    ctx.synchronize()
+    P, pairs = n + 1, [tuple(p) for p in g.fs.pairs]
+    ref = [np.zeros((P, 6, 6)), np.zeros((P, 6)), np.zeros((len(pairs), 6, 6))]
+    mag = [np.zeros_like(a) for a in ref]
+
+    def add(which, at, block):
+        ref[which][at] += block
+        mag[which][at] += np.abs(block)
+
+    for (_, _, i, j), Hf, bf in zip(rows, H, b):
+        add(0, i, Hf[:6, :6])
+        add(0, j, Hf[6:, 6:])
+        add(1, i, bf[:6])
+        add(1, j, bf[6:])
+        if i == j:
+            add(0, i, Hf[:6, 6:])
+            add(0, i, Hf[6:, :6])
+        else:
+            k = pairs.index((min(i, j), max(i, j)))
+            add(2, k, Hf[:6, 6:] if i < j else Hf[6:, :6])
+    for key, r, m in zip(("Hdiag", "bvec", "Hoff"), ref, mag):
+        assert np.all(np.abs(got[key].cpu().numpy() - r) <= (4 * n + 8) * 2.0 ** -52 * m), key

@@ -687,6 +687,15 @@ namespace {
 constexpr int kKindLinearize = 0;
 constexpr int kKindEvaluate = 1;
 
+// Rounds of more tiles than this read their factors' constants from a table
+// that one launch writes first; smaller rounds compute them in every tile,
+// while its first loads are in flight.  The launch takes 2.5 us and a gap, the
+// constants about 190 VALU instructions per wave and tile: without the table a
+// round of 500 factors in 3,500 tiles takes 84.6 us instead of 86.3 and a
+// submap's iteration (two rounds of 1,216 tiles) 43.0 us instead of 45.7,
+// while 4,500 factors in 12,144 tiles take 0.2 to 1.1 % longer.
+constexpr int64_t kConstsTableTiles = 4096;
+
 }  // namespace
 
 int vgicp::check_common(vgicp_ctx ctx, vgicp_factorset fs, const double *poses, const char *who) {
@@ -767,11 +776,12 @@ hipError_t enqueue_range(vgicp_ctx ctx, vgicp_factorset fs, int kind, int accum,
                          hipStream_t st, int form = VGICP_FORM_SOURCE, int32_t stride = 1) {
   const int tk = kind == kKindLinearize ? VGICP_KERNEL_LINEARIZE : VGICP_KERNEL_EVALUATE;
   hipError_t err = hipSuccess;
-  // a launch over the whole tile table reads the factors' constants from a
-  // table written once for the round; a launch over one factor's tiles
-  // computes them in every tile
+  // a launch over the whole of a large tile table reads the factors' constants
+  // from a table written once for the round; the others compute them in every
+  // tile
   const void *consts = nullptr;
-  if (tb == 0 && te == fs->n_tiles && f0 == 0 && nf == fs->n_factors && fs->d_consts) {
+  if (tb == 0 && te == fs->n_tiles && f0 == 0 && nf == fs->n_factors && fs->d_consts &&
+      fs->n_tiles > kConstsTableTiles) {
     err = launch_factor_consts(fs, poses, st);
     if (err != hipSuccess) return err;
     consts = fs->d_consts;

@@ -294,7 +294,8 @@ struct vgicp_context_s {
   void *scratch = nullptr;
   size_t scratch_bytes = 0;
   uint32_t *err_word = nullptr;       // device
-  uint32_t *host_pinned = nullptr;    // pinned host word pair for small readbacks
+  uint32_t *host_pinned = nullptr;    // pinned host words (64 bytes) for small readbacks
+  uint32_t group_seq = 0;             // voxelizations whose counts the host has asked for
   int cu_count = 0;
   // Growable workspace of the keyframe calls (vgicp_connect,
   // vgicp_submap_step): device tables and pinned host staging.

@@ -6,13 +6,20 @@
 // brick after brick (bricks of 4 x 4 x 4 voxels), and found through an
 // open-addressed table of brick records holding each brick's occupancy mask.
 //
-// Steps: keys -> radix sort of (key, point index) -> segment heads -> scan ->
-// segment starts -> [host sync: voxel count] -> per voxel its brick-major
-// sort key -> radix sort of (brick key and bit, voxel ordinal) -> brick heads
-// -> scan -> brick starts -> [host sync: brick count] -> brick table insertion
-// and FP64 voxel sums.  This runs once per cloud, off the per-iteration path.
+// Clouds of at most kGroupMaxPoints points are grouped by brick in a hash
+// table (see "grouped construction"): six launches and one wait of the host.
+// Larger clouds, and the few whose bricks do not fit the table or that put
+// more than kHeavyMax points in one voxel, are sorted instead: keys -> radix
+// sort of (key, point index) -> segment heads -> scan -> segment starts ->
+// [host sync: voxel count] -> per voxel its brick-major sort key -> radix sort
+// of (brick key and bit, voxel ordinal) -> brick heads -> scan -> brick starts
+// -> [host sync: brick count] -> brick table insertion and FP64 voxel sums.
+// Both give the same map.  This runs once per cloud, off the per-iteration
+// path.
 
+#include <algorithm>
 #include <cstring>
+#include <type_traits>
 
 #include <rocprim/device/device_radix_sort.hpp>
 #include <rocprim/device/device_scan.hpp>
@@ -21,13 +28,11 @@
 
 namespace vgicp {
 
-__global__ void __launch_bounds__(256)
-k_voxel_keys(const float *__restrict__ xyz, int64_t n, float s, uint64_t *__restrict__ keys,
-             uint32_t *__restrict__ idx, uint32_t *__restrict__ err) {
-  const int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (i >= n) return;
+// The voxel key of point i (zeros on an axis it is refused on) and the error
+// bits of its coordinates.
+__device__ __forceinline__ uint32_t point_key(const float *__restrict__ xyz, int64_t n, int64_t i,
+                                              float s, int32_t k[3]) {
   uint32_t bad = 0;
-  int32_t k[3];
 #pragma unroll
   for (int a = 0; a < 3; ++a) {
     const float x = xyz[a * n + i];
@@ -42,6 +47,16 @@ k_voxel_keys(const float *__restrict__ xyz, int64_t n, float s, uint64_t *__rest
       k[a] = int32_t(floorf(v));
     }
   }
+  return bad;
+}
+
+__global__ void __launch_bounds__(256)
+k_voxel_keys(const float *__restrict__ xyz, int64_t n, float s, uint64_t *__restrict__ keys,
+             uint32_t *__restrict__ idx, uint32_t *__restrict__ err) {
+  const int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
+  if (i >= n) return;
+  int32_t k[3];
+  const uint32_t bad = point_key(xyz, n, i, s, k);
   if (bad) atomicOr(err, bad);
   keys[i] = pack_key(k[0], k[1], k[2]);
   idx[i] = uint32_t(i);
@@ -64,10 +79,10 @@ k_segment_starts(const uint32_t *__restrict__ head, const uint32_t *__restrict__
   if (i == n - 1) seg[ord1[i]] = uint32_t(n);
 }
 
-__global__ void __launch_bounds__(256)
-k_fill_empty(BrickRecord *__restrict__ bricks, int64_t cap, uint32_t *__restrict__ occ,
-             uint32_t occ_words) {
-  const int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
+// Record i of an empty table, and word i of its bitset.
+__device__ __forceinline__ void fill_empty(int64_t i, BrickRecord *__restrict__ bricks,
+                                           int64_t cap, uint32_t *__restrict__ occ,
+                                           uint32_t occ_words) {
   if (i < cap) {
     BrickRecord r;
     r.key = kEmptyKey;
@@ -77,6 +92,12 @@ k_fill_empty(BrickRecord *__restrict__ bricks, int64_t cap, uint32_t *__restrict
     bricks[i] = r;
   }
   if (i < int64_t(occ_words)) occ[i] = 0u;
+}
+
+__global__ void __launch_bounds__(256)
+k_fill_empty(BrickRecord *__restrict__ bricks, int64_t cap, uint32_t *__restrict__ occ,
+             uint32_t occ_words) {
+  fill_empty(int64_t(blockIdx.x) * blockDim.x + threadIdx.x, bricks, cap, occ, occ_words);
 }
 
 // Per voxel (in lexicographic order): its packed key and its brick-major sort
@@ -101,19 +122,10 @@ k_brick_heads(const uint64_t *__restrict__ bsort, int64_t n_voxels, uint32_t *__
   head[d] = (d == 0 || (bsort[d] >> 6) != (bsort[d - 1] >> 6)) ? 1u : 0u;
 }
 
-// One thread per brick: its occupancy mask from its voxels' bits, then
-// linear-probing insertion of the record.
-__global__ void __launch_bounds__(256)
-k_build_bricks(const uint64_t *__restrict__ bsort, const uint32_t *__restrict__ bstart,
-               int64_t n_bricks, int64_t n_voxels, BrickRecord *__restrict__ bricks,
-               uint32_t log2cap, uint32_t *__restrict__ occ, uint32_t occ_mask) {
-  const int64_t b = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (b >= n_bricks) return;
-  const uint32_t d0 = bstart[b];
-  const uint32_t d1 = (b + 1 < n_bricks) ? bstart[b + 1] : uint32_t(n_voxels);
-  uint64_t mask = 0;
-  for (uint32_t d = d0; d < d1; ++d) mask |= 1ull << (bsort[d] & 63u);
-  const uint64_t key = brick_key_of_sort_key(bsort[d0]);
+// Linear-probing insertion of a brick's record and its occupancy bit.
+__device__ __forceinline__ void insert_record(uint64_t key, uint64_t mask, uint32_t base,
+                                              BrickRecord *__restrict__ bricks, uint32_t log2cap,
+                                              uint32_t *__restrict__ occ, uint32_t occ_mask) {
   const uint32_t cmask = (1u << log2cap) - 1u;
   uint32_t h = brick_slot_of_key(key, log2cap);
   // the records of one position in the lines: cap / kProbeStep of them
@@ -125,9 +137,24 @@ k_build_bricks(const uint64_t *__restrict__ bsort, const uint32_t *__restrict__ 
     h = (h + kProbeStep) & cmask;
   }
   bricks[h].mask = mask;
-  bricks[h].base = d0;
+  bricks[h].base = base;
   const uint32_t bit = h & occ_mask;
   atomicOr(&occ[bit >> 5], 1u << (bit & 31u));
+}
+
+// One thread per brick: its occupancy mask from its voxels' bits, then its
+// record.
+__global__ void __launch_bounds__(256)
+k_build_bricks(const uint64_t *__restrict__ bsort, const uint32_t *__restrict__ bstart,
+               int64_t n_bricks, int64_t n_voxels, BrickRecord *__restrict__ bricks,
+               uint32_t log2cap, uint32_t *__restrict__ occ, uint32_t occ_mask) {
+  const int64_t b = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
+  if (b >= n_bricks) return;
+  const uint32_t d0 = bstart[b];
+  const uint32_t d1 = (b + 1 < n_bricks) ? bstart[b + 1] : uint32_t(n_voxels);
+  uint64_t mask = 0;
+  for (uint32_t d = d0; d < d1; ++d) mask |= 1ull << (bsort[d] & 63u);
+  insert_record(brick_key_of_sort_key(bsort[d0]), mask, d0, bricks, log2cap, occ, occ_mask);
 }
 
 // One thread per voxel, by dense (brick-major) position d: sequential FP64
@@ -164,6 +191,536 @@ k_build_payload(const float *__restrict__ xyz, const float *__restrict__ cov, in
   in.ordinal = int32_t(v);
   in.count = int32_t(e - b);
   info[d] = in;
+}
+
+// ---------------------------------------------------------------- grouped construction
+// Points are grouped by brick in an open-addressed table of 64 counters per
+// brick, so nothing of the cloud's size is sorted; only the bricks are
+// ordered, a few hundred to a few thousand, by counting, for each, the ones
+// before it.  Bound by the latency of dependent launches, atomics and gathers
+// (a scan moves about a megabyte), so the steps are few and each keeps many
+// loads in flight:
+//   clear    the counters and slots of the table;
+//   insert   per point: its brick's slot, its arrival number in its voxel;
+//   compact  per 512 slots: a list of the occupied ones, their masks, and
+//            where each voxel's points start;
+//   number   per brick: its rank and the voxels before it (against every
+//            other brick), so the dense position of its voxels; and per
+//            point: its index into its voxel's list.  Its first thread hands
+//            the counts to the host, which meanwhile allocates the map;
+//   finish   per voxel: its points put back in point order (they arrive in
+//            any), gathered, and summed in that order in FP64; per brick: the
+//            lexicographic ordinals of its voxels; the table's empty records;
+//   records  per brick: its record.
+// A call on 20,011 returns takes 46 us (180 us by sorting), on a merged submap
+// of 320,000 points 94 us (464 us).  Beyond kGroupMaxPoints the counters'
+// share shrinks and the sort is bound by its passes, so it stays.
+constexpr int64_t kGroupMaxPoints = int64_t(1) << 20;
+constexpr uint32_t kGroupMaxSlots = 1u << 15;  // 8 MB of counters
+constexpr uint32_t kGroupProbes = 64;          // slots a point tries
+constexpr uint32_t kLightMax = 64;             // points of a voxel one wave sums
+constexpr uint32_t kHeavyMax = 4096;           // points of a voxel one block sums
+constexpr uint32_t kNumberBlocks = 512;
+constexpr uint32_t kNumberBricks = 4;  // bricks a wave numbers at once
+constexpr uint32_t kErrFull = 4u;  // a brick found no slot
+constexpr uint32_t kNoVoxel = 0xffffffffu;
+
+// Totals of the listed bricks in one word: points in the low 21 bits, voxels in
+// the next 21, bricks above.
+constexpr uint32_t kVoxelsShift = 21, kBricksShift = 42;
+constexpr uint32_t kTotalsMask = (1u << 21) - 1u;
+static_assert(kGroupMaxPoints <= int64_t(kTotalsMask), "totals in 21 bits");
+
+struct GroupHeader {
+  uint64_t totals;
+  uint32_t n_heavy;    // voxels of more than kLightMax points,
+  uint32_t max_count;  // points of the fullest of them (0 without one),
+  uint32_t heavy_at;   // and how many of them are listed
+  uint32_t err;
+};
+
+// What the host waits for (pinned); `seq` is written last.
+struct GroupCounts {
+  uint32_t err, n_voxels, n_bricks, n_heavy, max_count, seq;
+};
+
+struct Group {
+  GroupHeader *hdr;
+  uint64_t *keys;       // [slots] brick key or kEmptyKey
+  uint32_t *count;      // [slots][64] points per voxel
+  uint32_t *rel;        // [slots][64] first point of a voxel in its brick's list
+  uint32_t *first;      // [slots] first point of a brick in the list
+  uint64_t *bkey, *bmask;  // [bricks] in any order
+  uint32_t *bslot;
+  uint64_t *skey, *smask;  // [bricks] in key order
+  uint32_t *sbase;         // voxels in earlier bricks
+  uint2 *sseg;             // the bricks with the same x field
+  uint32_t *code, *arrival;  // [n] slot * 64 + bit of the point's voxel
+  uint32_t *list;            // [n] points, voxel after voxel
+  uint2 *vox;                // [voxels] start in the list, points
+  uint32_t *heavy;           // voxels of more than kLightMax points
+};
+
+// Sum over the wave, in every lane.
+__device__ __forceinline__ uint32_t wave_total(uint32_t v) {
+  int x = int(v);
+#define VGICP_ADD(CTRL, MASK) x += __builtin_amdgcn_update_dpp(0, x, CTRL, MASK, 0xf, false);
+  VGICP_ADD(0xb1, 0xf) VGICP_ADD(0x4e, 0xf) VGICP_ADD(0x141, 0xf) VGICP_ADD(0x140, 0xf)
+  VGICP_ADD(0x142, 0xa) VGICP_ADD(0x143, 0xc)
+#undef VGICP_ADD
+  return uint32_t(__builtin_amdgcn_readlane(x, 63));
+}
+
+// Inclusive sum over the lanes up to this one.
+__device__ __forceinline__ uint32_t wave_scan(uint32_t v) {
+  const uint32_t lane = threadIdx.x & 63;
+#pragma unroll
+  for (uint32_t d = 1; d < 64; d <<= 1) {
+    const uint32_t o = __shfl_up(v, d);
+    if (lane >= d) v += o;
+  }
+  return v;
+}
+
+__global__ void __launch_bounds__(256)
+k_group_clear(Group g, uint32_t slots) {
+  const uint32_t i = blockIdx.x * 256 + threadIdx.x;  // 16 bytes of counters each
+  if (i < slots * 16) reinterpret_cast<uint4 *>(g.count)[i] = make_uint4(0, 0, 0, 0);
+  if (i < slots) g.keys[i] = kEmptyKey;
+  if (i == 0) *g.hdr = GroupHeader{0, 0, 0, 0, 0};
+}
+
+// Consecutive points of a scan often fall in one voxel (the near rings put
+// hundreds there), so a wave's runs of equal keys look their brick up once and
+// take their arrival numbers with one atomic.
+__global__ void __launch_bounds__(256)
+k_group_insert(Group g, uint32_t log2slots, const float *__restrict__ xyz, uint32_t n, float s) {
+  const uint32_t i = blockIdx.x * 256 + threadIdx.x, lane = threadIdx.x & 63;
+  int32_t k[3] = {0, 0, 0};
+  uint32_t bad = i < n ? point_key(xyz, n, i, s, k) : 0u;
+  const bool valid = i < n && !bad;
+  // whole waves shuffle
+  const int32_t px = __shfl_up(k[0], 1), py = __shfl_up(k[1], 1), pz = __shfl_up(k[2], 1);
+  const int pvalid = __shfl_up(int(valid), 1);
+  const bool joins =
+      lane > 0 && valid && pvalid != 0 && px == k[0] && py == k[1] && pz == k[2];
+  const uint64_t heads = __ballot(!joins);
+  const uint32_t head = 63u - uint32_t(__clzll(heads & (~0ull >> (63 - lane))));
+  uint32_t code = kNoVoxel, arrival = 0;
+  if (valid && !joins) {
+    const uint64_t later = lane == 63 ? 0ull : heads >> (lane + 1);
+    const uint32_t run = later ? uint32_t(__ffsll((unsigned long long)later)) : 64u - lane;
+    const uint64_t key = brick_key(brick_field(k[0]), brick_field(k[1]), brick_field(k[2]));
+    const uint32_t smask = (1u << log2slots) - 1u;
+    uint32_t h = uint32_t((key * 0x9E3779B97F4A7C15ull) >> (64 - log2slots));
+    bad = kErrFull;
+    for (uint32_t p = 0; p < kGroupProbes; ++p) {
+      // a slot's key never changes once set, and a stale empty one only sends
+      // the point to the exchange
+      unsigned long long at = reinterpret_cast<volatile unsigned long long *>(g.keys)[h];
+      if (at == kEmptyKey) {
+        at = atomicCAS(reinterpret_cast<unsigned long long *>(&g.keys[h]),
+                       (unsigned long long)kEmptyKey, (unsigned long long)key);
+        if (at == kEmptyKey) at = key;
+      }
+      if (at == key) {
+        bad = 0;
+        break;
+      }
+      h = (h + 1) & smask;
+    }
+    if (!bad) {
+      code = (h << 6) | brick_bit(k[0], k[1], k[2]);
+      arrival = atomicAdd(&g.count[code], run);
+    }
+  }
+  if (bad) atomicOr(&g.hdr->err, bad);
+  code = __shfl(code, int(head));
+  arrival = __shfl(arrival, int(head)) + (lane - head);
+  if (i < n) {
+    g.code[i] = code;
+    g.arrival[i] = arrival;
+  }
+}
+
+// One block of 16 waves per kCompactSlots slots; each wave takes four bricks at
+// once.  The blocks place their bricks and points with one atomic each, few
+// enough (at most 64) that its serial updates do not show: with a block per 64
+// slots they took 10 us more.
+constexpr uint32_t kCompactSlots = 512;
+constexpr uint32_t kCompactThreads = 1024;
+constexpr uint32_t kCompactWaves = kCompactThreads / 64;
+constexpr uint32_t kSlotWaves = kCompactSlots / 64;
+static_assert(kSlotWaves <= kCompactWaves, "a thread per slot");
+
+__global__ void __launch_bounds__(kCompactThreads)
+k_group_compact(Group g) {
+  __shared__ uint32_t occupied[kCompactSlots], points[kCompactSlots], slot_n[kSlotWaves],
+      point_n[kSlotWaves], vox_n, heavy_n, most_n;
+  __shared__ uint64_t masks[kCompactSlots];
+  __shared__ uint64_t at;
+  const uint32_t tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const uint32_t slot = blockIdx.x * kCompactSlots + tid;
+  const bool used = tid < kCompactSlots && g.keys[slot] != kEmptyKey;
+  const uint64_t m = __ballot(used);
+  if (lane == 0 && wave < kSlotWaves) slot_n[wave] = uint32_t(__popcll(m));
+  if (tid == 0) vox_n = heavy_n = most_n = 0;
+  __syncthreads();
+  uint32_t nb = 0, pos = uint32_t(__popcll(m & ((1ull << lane) - 1ull)));
+#pragma unroll
+  for (uint32_t w = 0; w < kSlotWaves; ++w) {
+    if (w < wave) pos += slot_n[w];
+    nb += slot_n[w];
+  }
+  if (nb == 0) return;
+  if (used) occupied[pos] = slot;
+  __syncthreads();
+  uint32_t vox = 0, heavy = 0, most = 0;
+  for (uint32_t b0 = wave * 4; b0 < nb; b0 += kCompactWaves * 4) {
+    uint32_t c[4];
+#pragma unroll
+    for (uint32_t q = 0; q < 4; ++q) c[q] = g.count[(occupied[min(b0 + q, nb - 1)] << 6) | lane];
+#pragma unroll
+    for (uint32_t q = 0; q < 4; ++q) {
+      if (b0 + q >= nb) break;
+      const uint32_t incl = wave_scan(c[q]);
+      const uint64_t mask = __ballot(c[q] > 0);
+      if (c[q] > 0) g.rel[(occupied[b0 + q] << 6) | lane] = incl - c[q];
+      if (lane == 63) {
+        points[b0 + q] = incl;
+        masks[b0 + q] = mask;
+      }
+      vox += uint32_t(__popcll(mask));
+      heavy += uint32_t(__popcll(__ballot(c[q] > kLightMax)));
+      most = max(most, c[q]);
+    }
+  }
+  if (heavy > 0) atomicMax(&most_n, most);
+  if (lane == 0) {
+    atomicAdd(&vox_n, vox);
+    atomicAdd(&heavy_n, heavy);
+  }
+  __syncthreads();
+  const uint32_t p = tid < nb ? points[tid] : 0u;
+  const uint32_t incl = wave_scan(p);
+  if (lane == 63 && wave < kSlotWaves) point_n[wave] = incl;
+  __syncthreads();
+  if (tid == 0) {
+    uint64_t pts = 0;
+    for (uint32_t w = 0; w < kSlotWaves; ++w) pts += point_n[w];
+    at = atomicAdd(reinterpret_cast<unsigned long long *>(&g.hdr->totals),
+                   (unsigned long long)((uint64_t(nb) << kBricksShift) |
+                                        (uint64_t(vox_n) << kVoxelsShift) | pts));
+    if (heavy_n > 0) {
+      atomicAdd(&g.hdr->n_heavy, heavy_n);
+      atomicMax(&g.hdr->max_count, most_n);
+    }
+  }
+  __syncthreads();
+  if (tid < nb) {
+    uint32_t before = incl - p;
+    for (uint32_t w = 0; w < wave; ++w) before += point_n[w];
+    const uint32_t id = uint32_t(at >> kBricksShift) + tid, sl = occupied[tid];
+    g.bkey[id] = g.keys[sl];
+    g.bmask[id] = masks[tid];
+    g.bslot[id] = sl;
+    g.first[sl] = (uint32_t(at) & kTotalsMask) + before;
+  }
+}
+
+// Blocks [0, number_blocks): bricks; the others: points.
+__global__ void __launch_bounds__(256)
+k_group_number(Group g, uint32_t number_blocks, uint32_t n, GroupCounts *host, uint32_t seq) {
+  if (blockIdx.x >= number_blocks) {
+    const uint32_t i = (blockIdx.x - number_blocks) * 256 + threadIdx.x;
+    if (i >= n) return;
+    const uint32_t code = g.code[i];
+    if (code != kNoVoxel) g.list[g.first[code >> 6] + g.rel[code] + g.arrival[i]] = i;
+    return;
+  }
+  const uint64_t totals = g.hdr->totals;
+  const uint32_t nb = uint32_t(totals >> kBricksShift);
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    host->err = g.hdr->err;
+    host->n_voxels = uint32_t(totals >> kVoxelsShift) & kTotalsMask;
+    host->n_bricks = nb;
+    host->n_heavy = g.hdr->n_heavy;
+    host->max_count = g.hdr->max_count;
+    __hip_atomic_store(&host->seq, seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+  }
+  const uint32_t lane = threadIdx.x & 63;
+  const uint32_t w = __builtin_amdgcn_readfirstlane(blockIdx.x * 4 + (threadIdx.x >> 6));
+  for (uint32_t i0 = w * kNumberBricks; i0 < nb; i0 += number_blocks * 4 * kNumberBricks) {
+    uint64_t key[kNumberBricks];
+    uint32_t rank[kNumberBricks], base[kNumberBricks], lt[kNumberBricks], le[kNumberBricks];
+#pragma unroll
+    for (uint32_t q = 0; q < kNumberBricks; ++q) {
+      key[q] = g.bkey[min(i0 + q, nb - 1)];
+      rank[q] = base[q] = lt[q] = le[q] = 0;
+    }
+#pragma unroll 4
+    for (uint32_t j = lane; j < nb; j += 64) {
+      const uint64_t k = g.bkey[j];
+      const uint32_t pop = uint32_t(__popcll(g.bmask[j]));
+      const uint32_t x = uint32_t(k >> (2 * kBrickBits));
+#pragma unroll
+      for (uint32_t q = 0; q < kNumberBricks; ++q) {
+        const uint32_t xq = uint32_t(key[q] >> (2 * kBrickBits));
+        rank[q] += k < key[q] ? 1u : 0u;
+        base[q] += k < key[q] ? pop : 0u;
+        lt[q] += x < xq ? 1u : 0u;
+        le[q] += x <= xq ? 1u : 0u;
+      }
+    }
+#pragma unroll
+    for (uint32_t q = 0; q < kNumberBricks; ++q) {
+      if (i0 + q >= nb) break;
+      const uint32_t r = wave_total(rank[q]), b = wave_total(base[q]);
+      const uint32_t s0 = wave_total(lt[q]), s1 = wave_total(le[q]);
+      const uint64_t mask = g.bmask[i0 + q];
+      const uint32_t slot = g.bslot[i0 + q];
+      if (lane == 0) {
+        g.skey[r] = key[q];
+        g.smask[r] = mask;
+        g.sbase[r] = b;
+        g.sseg[r] = make_uint2(s0, s1);
+      }
+      if ((mask >> lane) & 1ull) {
+        const uint32_t at64 = (slot << 6) | lane;
+        const uint32_t d = b + uint32_t(__popcll(mask & ((1ull << lane) - 1ull)));
+        const uint32_t c = g.count[at64];
+        g.vox[d] = make_uint2(g.first[slot] + g.rel[at64], c);
+        if (c > kLightMax) g.heavy[atomicAdd(&g.hdr->heavy_at, 1u)] = d;
+      }
+    }
+  }
+}
+
+// Coordinates and covariance of point p.
+__device__ __forceinline__ void gather_point(const float *__restrict__ xyz,
+                                             const float *__restrict__ cov, uint32_t n, uint32_t p,
+                                             float v[9]) {
+  v[0] = xyz[p], v[1] = xyz[uint64_t(n) + p], v[2] = xyz[2ull * n + p];
+  const float2 *c = reinterpret_cast<const float2 *>(cov + 6ull * p);
+#pragma unroll
+  for (int a = 0; a < 3; ++a) v[3 + 2 * a] = c[a].x, v[4 + 2 * a] = c[a].y;
+}
+
+// Adds m values to acc one after the other.
+__device__ __forceinline__ double add_in_order(double acc, const float *v, uint32_t m) {
+  uint32_t r = 0;
+  for (; r + 8 <= m; r += 8) {
+    float x[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) x[u] = v[r + u];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) acc += double(x[u]);
+  }
+  for (; r < m; ++r) acc += double(v[r]);
+  return acc;
+}
+
+constexpr uint32_t kGatherStride = 260;  // lists after nine rows are 16-byte aligned
+constexpr uint32_t kLightStride = kLightMax + 1;
+
+// Entries of the sorted list of a voxel of m points.
+__host__ __device__ inline uint32_t list_size(uint32_t m) {
+  uint32_t m2 = 128;
+  while (m2 < m) m2 <<= 1;
+  return m2;
+}
+
+// LDS of a finish block: the gathered points of a heavy voxel and its list
+// (the fullest voxel's, so that blocks take no more than they need), or the
+// points of four light ones.
+static size_t finish_lds(uint32_t max_count) {
+  if (max_count <= kLightMax) return 4 * 9 * kLightStride * sizeof(float);
+  return (9 * kGatherStride + list_size(max_count)) * sizeof(float);
+}
+static_assert(9 * kGatherStride % 4 == 0, "aligned lists");
+static_assert(9 * kGatherStride + 128 >= 4 * 9 * kLightStride, "light points fit a heavy block");
+
+// A voxel of more than kLightMax points, by one block.  Up to 256 points take
+// the place that counting the smaller indices gives them, while they are
+// gathered; more are sorted in LDS first, then gathered 256 at a time while
+// nine lanes of the first wave add the previous ones.
+__device__ void finish_heavy(float *lds, const Group &g, uint32_t d,
+                             const float *__restrict__ xyz, const float *__restrict__ cov,
+                             uint32_t n, float *__restrict__ stats) {
+  const uint32_t tid = threadIdx.x;
+  const uint2 vx = g.vox[d];
+  const uint32_t m = vx.y;
+  const uint32_t m2 = list_size(m);
+  uint32_t *idx = reinterpret_cast<uint32_t *>(lds + 9 * kGatherStride);
+  for (uint32_t i = tid; i < m2; i += 256) idx[i] = i < m ? g.list[vx.x + i] : 0xffffffffu;
+  __syncthreads();
+  double acc = 0.0;
+  if (m <= 256) {
+    float v[9];
+    const uint32_t p = tid < m ? idx[tid] : 0u;
+    if (tid < m) gather_point(xyz, cov, n, p, v);
+    uint32_t rank = 0;
+    for (uint32_t l = 0; l < m2; l += 4) {
+      const uint4 o = *reinterpret_cast<const uint4 *>(idx + l);
+      rank += (o.x < p ? 1u : 0u) + (o.y < p ? 1u : 0u) + (o.z < p ? 1u : 0u) + (o.w < p ? 1u : 0u);
+    }
+    if (tid < m) {
+#pragma unroll
+      for (uint32_t a = 0; a < 9; ++a) lds[a * kGatherStride + rank] = v[a];
+    }
+    __syncthreads();
+    if (tid < 9) acc = add_in_order(0.0, lds + tid * kGatherStride, m);
+  } else {
+    for (uint32_t k = 2; k <= m2; k <<= 1)
+      for (uint32_t j = k >> 1; j > 0; j >>= 1) {
+        for (uint32_t t = tid; t < m2 / 2; t += 256) {
+          const uint32_t lo = 2 * t - (t & (j - 1)), hi = lo + j;
+          const uint32_t a = idx[lo], b = idx[hi];
+          if ((a > b) == ((lo & k) == 0)) {
+            idx[lo] = b;
+            idx[hi] = a;
+          }
+        }
+        __syncthreads();
+      }
+    for (uint32_t c0 = 0; c0 < m; c0 += 256) {
+      float v[9];
+      if (c0 + tid < m) gather_point(xyz, cov, n, idx[c0 + tid], v);
+      __syncthreads();  // the previous points have been added
+      if (c0 + tid < m) {
+#pragma unroll
+        for (uint32_t a = 0; a < 9; ++a) lds[a * kGatherStride + tid] = v[a];
+      }
+      __syncthreads();
+      if (tid < 9) acc = add_in_order(acc, lds + tid * kGatherStride, min(m - c0, 256u));
+    }
+  }
+  if (tid < 9) stats[9ull * d + tid] = float(acc / double(m));
+}
+
+// A voxel of at most kLightMax points, by one wave.
+__device__ __forceinline__ void finish_light(float *lds, const Group &g, uint32_t d,
+                                             const float *__restrict__ xyz,
+                                             const float *__restrict__ cov, uint32_t n,
+                                             float *__restrict__ stats) {
+  const uint32_t lane = threadIdx.x & 63;
+  const uint2 vx = g.vox[d];
+  const uint32_t m = __builtin_amdgcn_readfirstlane(vx.y);
+  if (m > kLightMax) return;
+  uint32_t p = 0, rank = 0;
+  float v[9];
+  if (lane < m) {
+    p = g.list[vx.x + lane];
+    gather_point(xyz, cov, n, p, v);
+  }
+  for (uint32_t l = 0; l < m; ++l)
+    rank += uint32_t(__builtin_amdgcn_readlane(int(p), int(l))) < p ? 1u : 0u;
+  if (lane < m) {
+#pragma unroll
+    for (uint32_t a = 0; a < 9; ++a) lds[a * kLightStride + rank] = v[a];
+  }
+  __builtin_amdgcn_wave_barrier();
+  if (lane < 9) stats[9ull * d + lane] = float(add_in_order(0.0, lds + lane * kLightStride, m) / double(m));
+}
+
+// The voxels of brick s (in key order), a lane per voxel of the brick.  A
+// voxel's ordinal counts the voxels whose key comes first, axis after axis:
+// every voxel of the bricks with a smaller x field, and in the bricks with the
+// same x field (neighbours in key order) those its own bits select.
+__device__ __forceinline__ void finish_brick(const Group &g, uint32_t s,
+                                             VoxelInfo *__restrict__ info) {
+  const uint32_t lane = threadIdx.x & 63;
+  const uint64_t key = g.skey[s], mask = g.smask[s];
+  const uint2 seg = g.sseg[s];
+  // bits of a brick whose position on an axis (its bits h1 h0) equals this
+  // lane's, and is less
+  auto axis = [&](uint32_t b1, uint32_t b0, uint64_t h1, uint64_t h0, uint64_t &eq, uint64_t &lt) {
+    const bool v1 = (lane >> b1) & 1u, v0 = (lane >> b0) & 1u;
+    const uint64_t e1 = v1 ? h1 : ~h1;
+    eq = e1 & (v0 ? h0 : ~h0);
+    lt = (v1 ? ~h1 : 0ull) | (v0 ? e1 & ~h0 : 0ull);
+  };
+  uint64_t xeq, xlt, yeq, ylt, zeq, zlt;
+  axis(5, 2, 0xffffffff00000000ull, 0xf0f0f0f0f0f0f0f0ull, xeq, xlt);
+  axis(4, 1, 0xffff0000ffff0000ull, 0xccccccccccccccccull, yeq, ylt);
+  axis(3, 0, 0xff00ff00ff00ff00ull, 0xaaaaaaaaaaaaaaaaull, zeq, zlt);
+  (void)zeq;
+  const uint32_t fmask = (1u << kBrickBits) - 1u;
+  const uint32_t y = uint32_t(key >> kBrickBits) & fmask, z = uint32_t(key) & fmask;
+  uint32_t ordinal = g.sbase[seg.x];
+  for (uint32_t j0 = seg.x; j0 < seg.y; j0 += 64) {
+    const uint32_t j = min(j0 + lane, seg.y - 1);
+    const uint64_t kj = g.skey[j], mj = g.smask[j];
+    const uint32_t cnt = min(seg.y - j0, 64u);
+    for (uint32_t l = 0; l < cnt; ++l) {
+      const uint32_t klo = uint32_t(__builtin_amdgcn_readlane(int(uint32_t(kj)), int(l)));
+      const uint32_t khi = uint32_t(__builtin_amdgcn_readlane(int(uint32_t(kj >> 32)), int(l)));
+      const uint32_t mlo = uint32_t(__builtin_amdgcn_readlane(int(uint32_t(mj)), int(l)));
+      const uint32_t mhi = uint32_t(__builtin_amdgcn_readlane(int(uint32_t(mj >> 32)), int(l)));
+      const uint64_t k = (uint64_t(khi) << 32) | klo;
+      const uint32_t yj = uint32_t(k >> kBrickBits) & fmask, zj = uint32_t(k) & fmask;
+      uint64_t sel = xlt;
+      if (yj < y) {
+        sel |= xeq;
+      } else if (yj == y) {
+        sel |= xeq & (ylt | (zj < z ? yeq : zj == z ? (yeq & zlt) : 0ull));
+      }
+      ordinal += uint32_t(__popcll(sel & ((uint64_t(mhi) << 32) | mlo)));
+    }
+  }
+  if ((mask >> lane) & 1ull) {
+    const uint32_t d = g.sbase[s] + uint32_t(__popcll(mask & ((1ull << lane) - 1ull)));
+    const int32_t x4 = (int32_t(uint32_t(key >> (2 * kBrickBits))) - kBrickBias) * 4;
+    const int32_t y4 = (int32_t(y) - kBrickBias) * 4, z4 = (int32_t(z) - kBrickBias) * 4;
+    const int32_t a = int32_t((lane >> 4) & 2u) | int32_t((lane >> 2) & 1u);
+    const int32_t b = int32_t((lane >> 3) & 2u) | int32_t((lane >> 1) & 1u);
+    const int32_t c = int32_t((lane >> 2) & 2u) | int32_t(lane & 1u);
+    VoxelInfo in;
+    in.key = pack_key(x4 + a, y4 + b, z4 + c);
+    in.ordinal = int32_t(ordinal);
+    in.count = int32_t(g.vox[d].y);
+    info[d] = in;
+  }
+}
+
+// Blocks: one per heavy voxel (they take longest), then fill_blocks empty the
+// table, then four bricks a block, then four light voxels a block.
+__global__ void __launch_bounds__(256)
+k_group_finish(Group g, uint32_t n_bricks, uint32_t n_voxels, uint32_t n_heavy,
+               uint32_t fill_blocks, const float *__restrict__ xyz,
+               const float *__restrict__ cov, uint32_t n,
+               BrickRecord *__restrict__ bricks, int64_t cap, uint32_t *__restrict__ occ,
+               uint32_t occ_words, VoxelStats *__restrict__ stats, VoxelInfo *__restrict__ info) {
+  extern __shared__ float lds[];
+  uint32_t blk = blockIdx.x;
+  const uint32_t wave = threadIdx.x >> 6;
+  float *st = reinterpret_cast<float *>(stats);
+  if (blk < n_heavy) {
+    finish_heavy(lds, g, g.heavy[blk], xyz, cov, n, st);
+    return;
+  }
+  blk -= n_heavy;
+  if (blk < fill_blocks) {
+    fill_empty(int64_t(blk) * 256 + threadIdx.x, bricks, cap, occ, occ_words);
+    return;
+  }
+  blk -= fill_blocks;
+  const uint32_t brick_blocks = (n_bricks + 3) / 4;
+  if (blk < brick_blocks) {
+    const uint32_t s = __builtin_amdgcn_readfirstlane(blk * 4 + wave);
+    if (s < n_bricks) finish_brick(g, s, info);
+    return;
+  }
+  const uint32_t d = __builtin_amdgcn_readfirstlane((blk - brick_blocks) * 4 + wave);
+  if (d < n_voxels) finish_light(lds + wave * 9 * kLightStride, g, d, xyz, cov, n, st);
+}
+
+__global__ void __launch_bounds__(256)
+k_group_records(Group g, uint32_t n_bricks, BrickRecord *__restrict__ bricks, uint32_t log2cap,
+                uint32_t *__restrict__ occ, uint32_t occ_mask) {
+  const uint32_t s = blockIdx.x * 256 + threadIdx.x;
+  if (s < n_bricks)
+    insert_record(g.skey[s], g.smask[s], g.sbase[s], bricks, log2cap, occ, occ_mask);
 }
 
 __global__ void __launch_bounds__(256)
@@ -289,15 +846,113 @@ static int ensure_scratch(vgicp_ctx ctx, size_t bytes, std::string &msg) {
   return VGICP_OK;
 }
 
+// Workspace of the grouped construction for n points and 2^log2slots slots.
+static size_t carve_group(char *base, size_t n, size_t slots, Group *g) {
+  size_t at = 0;
+  auto take = [&](auto **p, size_t count) {
+    *p = reinterpret_cast<std::remove_reference_t<decltype(*p)>>(base + at);
+    at += align256(count * sizeof(**p));
+  };
+  take(&g->hdr, 1);
+  take(&g->keys, slots);
+  take(&g->count, slots * 64);
+  take(&g->rel, slots * 64);
+  take(&g->first, slots);
+  take(&g->bkey, slots);
+  take(&g->bmask, slots);
+  take(&g->bslot, slots);
+  take(&g->skey, slots);
+  take(&g->smask, slots);
+  take(&g->sbase, slots);
+  take(&g->sseg, slots);
+  take(&g->code, n);
+  take(&g->arrival, n);
+  take(&g->list, n);
+  take(&g->vox, n);
+  take(&g->heavy, n / kLightMax + 1);
+  return at;
+}
+
+// Groups the cloud's points (the launches up to `number`) and waits for the
+// counts.  *taken is false when the cloud has to be sorted instead.
+static int group_points(vgicp_ctx ctx, const vgicp_cloud *cloud, float s, Group *g,
+                        GroupCounts *counts, bool *taken, std::string &msg) {
+  const hipStream_t st = ctx->stream;
+  const uint32_t n = uint32_t(cloud->n);
+  // twice as many slots as there can be bricks for a small cloud; a larger one
+  // has eight or more points to a brick (a street of 20,000 returns has about
+  // 1,000 bricks at 0.5 m and 2,500 at 0.25 m), and the counters cost 256
+  // bytes a slot to clear
+  const uint32_t want = std::min(2 * n, std::max(8192u, n / 2));
+  uint32_t log2slots = 10;
+  while ((1u << log2slots) < kGroupMaxSlots && (1u << log2slots) < want) ++log2slots;
+  const uint32_t slots = 1u << log2slots;
+  const int rc = ensure_scratch(ctx, carve_group(nullptr, n, slots, g), msg);
+  if (rc != VGICP_OK) return rc;
+  carve_group(static_cast<char *>(ctx->scratch), n, slots, g);
+  // the counts follow the two words of the sorted construction
+  constexpr int kCountsWord = 4;
+  auto *host = reinterpret_cast<GroupCounts *>(ctx->host_pinned + kCountsWord);
+  void *pinned_dev = nullptr;
+  HIP_TRY(hipHostGetDevicePointer(&pinned_dev, ctx->host_pinned, 0));
+  auto *host_dev =
+      reinterpret_cast<GroupCounts *>(static_cast<uint32_t *>(pinned_dev) + kCountsWord);
+  const uint32_t seq = ++ctx->group_seq;
+  const uint32_t points = grid_for(n), number = std::min(kNumberBlocks, grid_for(n, 16));
+  k_group_clear<<<slots / 16, 256, 0, st>>>(*g, slots);
+  k_group_insert<<<points, 256, 0, st>>>(*g, log2slots, cloud->xyz, n, s);
+  k_group_compact<<<slots / kCompactSlots, kCompactThreads, 0, st>>>(*g);
+  k_group_number<<<number + points, 256, 0, st>>>(*g, number, n, host_dev, seq);
+  HIP_TRY(hipGetLastError());
+  // The kernel's first thread writes the counts, so the host need not wait for
+  // its end; a stream with much work before it is waited for as usual.
+  for (int spin = 0; spin < 20000; ++spin) {
+    if (__atomic_load_n(&host->seq, __ATOMIC_ACQUIRE) == seq) break;
+    __builtin_ia32_pause();
+  }
+  if (__atomic_load_n(&host->seq, __ATOMIC_ACQUIRE) != seq) HIP_TRY(hipStreamSynchronize(st));
+  if (__atomic_load_n(&host->seq, __ATOMIC_ACQUIRE) != seq) {
+    msg = "vgicp_voxelize: the counts of the voxel map did not arrive";
+    return VGICP_EHIP;
+  }
+  *counts = *host;
+  *taken = !(counts->err & kErrFull) && counts->max_count <= kHeavyMax;
+  return VGICP_OK;
+}
+
+static int point_error(uint32_t err, std::string &msg) {
+  if (err & kErrNonFinite) {
+    msg = "vgicp_voxelize: a point coordinate is not finite";
+    return VGICP_ENONFINITE;
+  }
+  if (err & kErrRange) {
+    msg = "vgicp_voxelize: a voxel key lies outside [-2^20, 2^20)";
+    return VGICP_ERANGE;
+  }
+  return VGICP_OK;
+}
+
 int voxelize_impl(vgicp_ctx ctx, const vgicp_cloud *cloud, double resolution, vgicp_map *out,
                   std::string &msg) {
   const int64_t n = cloud->n;
   const float s = float(1.0 / resolution);
   const hipStream_t st = ctx->stream;
 
-  int64_t n_voxels = 0;
+  int64_t n_voxels = 0, n_bricks = 0;
   VoxScratch sc{};
-  if (n > 0) {
+  Group group{};
+  GroupCounts counts{};
+  bool grouped = false;
+  if (n > 0 && n <= kGroupMaxPoints) {
+    int rc = group_points(ctx, cloud, s, &group, &counts, &grouped, msg);
+    if (rc == VGICP_OK) rc = point_error(counts.err, msg);
+    if (rc != VGICP_OK) return rc;
+    if (grouped) {
+      n_voxels = counts.n_voxels;
+      n_bricks = counts.n_bricks;
+    }
+  }
+  if (n > 0 && !grouped) {
     size_t total = 0, sort_bytes = 0, scan_bytes = 0;
     HIP_TRY(plan_scratch(n, st, &total, &sort_bytes, &scan_bytes));
     int rc = ensure_scratch(ctx, total, msg);
@@ -323,23 +978,15 @@ int voxelize_impl(vgicp_ctx ctx, const vgicp_cloud *cloud, double resolution, vg
     HIP_TRY(hipMemcpyAsync(ctx->host_pinned + 1, sc.ord1 + (n - 1), sizeof(uint32_t),
                            hipMemcpyDeviceToHost, st));
     HIP_TRY(hipStreamSynchronize(st));
-    const uint32_t err = ctx->host_pinned[0];
-    if (err & kErrNonFinite) {
-      msg = "vgicp_voxelize: a point coordinate is not finite";
-      return VGICP_ENONFINITE;
-    }
-    if (err & kErrRange) {
-      msg = "vgicp_voxelize: a voxel key lies outside [-2^20, 2^20)";
-      return VGICP_ERANGE;
-    }
+    const int prc = point_error(ctx->host_pinned[0], msg);
+    if (prc != VGICP_OK) return prc;
     n_voxels = int64_t(ctx->host_pinned[1]);
   }
 
   // Brick order: sort the voxels by (brick key, position in the brick).
-  int64_t n_bricks = 0;
   uint64_t *vkey = sc.keys_in;
   uint32_t *vord_in = sc.idx_in, *bhead = sc.head, *bord1 = sc.ord1, *vord_out = sc.spare;
-  if (n_voxels > 0) {
+  if (n_voxels > 0 && !grouped) {
     size_t need_sort = 0, need_scan = 0;
     HIP_TRY(rocprim::radix_sort_pairs(nullptr, need_sort, (uint64_t *)nullptr,
                                       (uint64_t *)nullptr, (uint32_t *)nullptr,
@@ -431,9 +1078,19 @@ int voxelize_impl(vgicp_ctx ctx, const vgicp_cloud *cloud, double resolution, vg
     msg = std::string("vgicp_voxelize: hipMalloc of the voxel map: ") + hipGetErrorString(e);
     return e == hipErrorOutOfMemory ? VGICP_ENOMEM : VGICP_EHIP;
   }
-  k_fill_empty<<<grid_for(std::max<int64_t>(cap, obits / 32)), 256, 0, st>>>(
-      m->bricks, cap, m->occ, obits / 32);
-  if (n_voxels > 0) {
+  const unsigned fill = grid_for(std::max<int64_t>(cap, obits / 32));
+  if (grouped) {
+    const uint32_t nb = uint32_t(n_bricks), nv = uint32_t(n_voxels);
+    k_group_finish<<<counts.n_heavy + fill + grid_for(nb, 4) + grid_for(nv, 4), 256,
+                     finish_lds(counts.max_count), st>>>(
+        group, nb, nv, counts.n_heavy, fill, cloud->xyz, cloud->cov, uint32_t(n), m->bricks, cap,
+        m->occ, obits / 32, m->stats, m->info);
+    k_group_records<<<grid_for(nb), 256, 0, st>>>(group, nb, m->bricks, log2cap, m->occ,
+                                                  obits - 1);
+  } else {
+    k_fill_empty<<<fill, 256, 0, st>>>(m->bricks, cap, m->occ, obits / 32);
+  }
+  if (n_voxels > 0 && !grouped) {
     k_build_bricks<<<grid_for(n_bricks), 256, 0, st>>>(sc.bsort_out, sc.bstart, n_bricks,
                                                        n_voxels, m->bricks, log2cap, m->occ,
                                                        obits - 1);

@@ -13,7 +13,7 @@
 // The results are the same up to FP32 summation order (integer outputs are
 // identical).
 
-#include "vgicp_internal.hpp"
+#include "group.hpp"
 
 #include <rocprim/device/device_radix_sort.hpp>
 
@@ -42,37 +42,40 @@ __device__ __forceinline__ uint64_t spread3(uint32_t v) {
   return x;
 }
 
-// Morton key (63 bits, x most significant within each bit triple) and the
-// point's own index of every point of one cloud.
+// Morton key (63 bits, x most significant within each bit triple) of the cell
+// of point i.
+__device__ __forceinline__ uint64_t morton_key(const float *__restrict__ xyz, uint32_t n,
+                                               uint32_t i, float inv_cell) {
+  const uint32_t cx = cell21(xyz[i], inv_cell);
+  const uint32_t cy = cell21(xyz[uint64_t(n) + i], inv_cell);
+  const uint32_t cz = cell21(xyz[2ull * n + i], inv_cell);
+  return (spread3(cx) << 2) | (spread3(cy) << 1) | spread3(cz);
+}
+
+// The Morton key and the point's own index of every point of one cloud.
 __global__ void __launch_bounds__(kThreads)
 k_morton_keys(const float *__restrict__ xyz, uint32_t n, float inv_cell,
               uint64_t *__restrict__ keys, uint32_t *__restrict__ idx) {
   const uint32_t i = blockIdx.x * kThreads + threadIdx.x;
   if (i >= n) return;
-  const uint32_t cx = cell21(xyz[i], inv_cell);
-  const uint32_t cy = cell21(xyz[uint64_t(n) + i], inv_cell);
-  const uint32_t cz = cell21(xyz[2ull * n + i], inv_cell);
-  keys[i] = (spread3(cx) << 2) | (spread3(cy) << 1) | spread3(cz);
+  keys[i] = morton_key(xyz, n, i, inv_cell);
   idx[i] = i;
 }
 
-// Copy point perm[i] of the cloud to position i of the ordered copy
-// (three coordinates and six covariance entries per point), and
-// count the points with a non-finite coordinate (nonfinite[0]) or covariance
-// entry (nonfinite[1]): the only full pass over a factor set's inputs.
-__global__ void __launch_bounds__(kThreads)
-k_gather_points(const float *__restrict__ xyz, const float *__restrict__ cov, uint32_t n,
-                const int32_t *__restrict__ perm, float *__restrict__ xyz_out,
-                float *__restrict__ cov_out, unsigned long long *__restrict__ nonfinite) {
-  const uint32_t i = blockIdx.x * kThreads + threadIdx.x;
-  if (i >= n) return;
-  const uint64_t j = uint32_t(perm[i]);
+// Point j of the cloud to position i of the ordered copy, counting a
+// non-finite coordinate (nonfinite[0]) or covariance entry (nonfinite[1]): the
+// only full pass over a factor set's inputs.
+__device__ __forceinline__ void copy_point(const float *__restrict__ xyz,
+                                           const float *__restrict__ cov, uint32_t n, uint64_t j,
+                                           uint64_t i, float *__restrict__ xyz_out,
+                                           float *__restrict__ cov_out,
+                                           unsigned long long *__restrict__ nonfinite) {
   const float x = xyz[j], y = xyz[uint64_t(n) + j], z = xyz[2ull * n + j];
-  xyz_out[3ull * i] = x;
-  xyz_out[3ull * i + 1] = y;
-  xyz_out[3ull * i + 2] = z;
+  xyz_out[3 * i] = x;
+  xyz_out[3 * i + 1] = y;
+  xyz_out[3 * i + 2] = z;
   const float2 *src = reinterpret_cast<const float2 *>(cov + 6 * j);
-  float2 *dst = reinterpret_cast<float2 *>(cov_out + 6ull * i);
+  float2 *dst = reinterpret_cast<float2 *>(cov_out + 6 * i);
   const float2 c0 = src[0], c1 = src[1], c2 = src[2];
   dst[0] = c0;
   dst[1] = c1;
@@ -82,6 +85,124 @@ k_gather_points(const float *__restrict__ xyz, const float *__restrict__ cov, ui
                        isfinite(c2.x) && isfinite(c2.y));
   if (bad_p) atomicAdd(&nonfinite[0], 1ull);
   if (bad_c) atomicAdd(&nonfinite[1], 1ull);
+}
+
+// Copies point perm[i] of the cloud to position i of the ordered copy.
+__global__ void __launch_bounds__(kThreads)
+k_gather_points(const float *__restrict__ xyz, const float *__restrict__ cov, uint32_t n,
+                const int32_t *__restrict__ perm, float *__restrict__ xyz_out,
+                float *__restrict__ cov_out, unsigned long long *__restrict__ nonfinite) {
+  const uint32_t i = blockIdx.x * kThreads + threadIdx.x;
+  if (i < n) copy_point(xyz, cov, n, uint32_t(perm[i]), i, xyz_out, cov_out, nonfinite);
+}
+
+// ---------------------------------------------------------------- grouped order
+// The Morton order of many clouds at once: each is grouped by cells and bricks
+// (group.hpp; a brick's key is the Morton key of its cells above their six low
+// bits, which are the cell's place in the brick), number counts the points in
+// the bricks before each brick, and place puts every point behind the points
+// of earlier cells and the earlier points of its own.  Five launches order as
+// many clouds as the workspace holds; sorting them one by one took twelve
+// launches a cloud (450 us of a 10-scan submap's factor set).
+struct OrderJob {
+  Group g;
+  uint32_t *base;  // [slots] points in earlier bricks
+  const float *xyz, *cov;
+  float *xyz_out, *cov_out;
+  int32_t *perm;
+  uint32_t n;
+  float inv_cell;
+  uint32_t *redo;  // set when the cloud has to be sorted instead
+};
+
+constexpr size_t kOrderWorkspace = size_t(192) << 20;  // bytes of grouped clouds at once
+constexpr uint32_t kOrderJobs = 256;                   // and clouds
+constexpr uint32_t kOrderBlocks = 64;                  // blocks that number a cloud's bricks
+constexpr uint32_t kOrderBricks = 4;                   // bricks a wave numbers at once
+
+__global__ void __launch_bounds__(256)
+k_order_clear(const OrderJob *__restrict__ jobs) {
+  group_clear(jobs[blockIdx.y].g, blockIdx.x);
+}
+
+__global__ void __launch_bounds__(256)
+k_order_insert(const OrderJob *__restrict__ jobs) {
+  const OrderJob &job = jobs[blockIdx.y];
+  const uint32_t n = job.n;
+  if (blockIdx.x * 256 >= n) return;
+  const float *xyz = job.xyz;
+  const float inv = job.inv_cell;
+  group_insert(job.g, blockIdx.x * 256 + threadIdx.x, n,
+               [&](uint32_t i, uint64_t &brick, uint32_t &cell) {
+                 const uint64_t k = morton_key(xyz, n, i, inv);
+                 brick = k >> 6;
+                 cell = uint32_t(k) & 63u;
+                 return 0u;
+               });
+}
+
+__global__ void __launch_bounds__(kCompactThreads)
+k_order_compact(const OrderJob *__restrict__ jobs) {
+  const Group &g = jobs[blockIdx.y].g;
+  if (blockIdx.x * kCompactSlots < (1u << g.log2slots)) group_compact(g, blockIdx.x);
+}
+
+// Blocks [0, kOrderBlocks): bricks; the others: points.
+__global__ void __launch_bounds__(256)
+k_order_number(const OrderJob *__restrict__ jobs) {
+  const OrderJob &job = jobs[blockIdx.y];
+  const Group &g = job.g;
+  if (blockIdx.x >= kOrderBlocks) {
+    group_scatter(g, (blockIdx.x - kOrderBlocks) * 256 + threadIdx.x, job.n);
+    return;
+  }
+  if (blockIdx.x == 0 && threadIdx.x == 0)
+    *job.redo = (g.hdr->err != 0 || g.hdr->max_count > kHeavyMax) ? 1u : 0u;
+  const uint32_t nb = uint32_t(g.hdr->totals >> kBricksShift), lane = threadIdx.x & 63;
+  const uint32_t w = __builtin_amdgcn_readfirstlane(blockIdx.x * 4 + (threadIdx.x >> 6));
+  for (uint32_t i0 = w * kOrderBricks; i0 < nb; i0 += kOrderBlocks * 4 * kOrderBricks) {
+    uint64_t key[kOrderBricks];
+    uint32_t base[kOrderBricks];
+#pragma unroll
+    for (uint32_t q = 0; q < kOrderBricks; ++q) {
+      key[q] = g.bkey[min(i0 + q, nb - 1)];
+      base[q] = 0;
+    }
+#pragma unroll 4
+    for (uint32_t j = lane; j < nb; j += 64) {
+      const uint64_t k = g.bkey[j];
+      const uint32_t pts = g.bpts[j];
+#pragma unroll
+      for (uint32_t q = 0; q < kOrderBricks; ++q) base[q] += k < key[q] ? pts : 0u;
+    }
+#pragma unroll
+    for (uint32_t q = 0; q < kOrderBricks; ++q) {
+      if (i0 + q >= nb) break;
+      const uint32_t b = wave_total(base[q]);
+      if (lane == 0) job.base[g.bslot[i0 + q]] = b;
+    }
+  }
+}
+
+__global__ void __launch_bounds__(256)
+k_order_place(const OrderJob *__restrict__ jobs, unsigned long long *__restrict__ nonfinite) {
+  const OrderJob &job = jobs[blockIdx.y];
+  const uint32_t n = job.n, i = blockIdx.x * 256 + threadIdx.x;
+  if (i >= n || *job.redo) return;
+  const Group &g = job.g;
+  const uint32_t code = g.code[i], slot = code >> 6;
+  const uint32_t rel = g.rel[code], m = g.count[code];
+  const uint32_t *list = g.list + g.first[slot] + rel;
+  uint32_t at = job.base[slot] + rel;
+  for (uint32_t l = 0; l < m; l += 4) {
+    uint32_t o[4];
+#pragma unroll
+    for (uint32_t u = 0; u < 4; ++u) o[u] = list[min(l + u, m - 1)];
+#pragma unroll
+    for (uint32_t u = 0; u < 4; ++u) at += (l + u < m && o[u] < i) ? 1u : 0u;
+  }
+  copy_point(job.xyz, job.cov, n, i, at, job.xyz_out, job.cov_out, nonfinite);
+  job.perm[at] = int32_t(i);
 }
 
 size_t align256(size_t b) { return (b + 255) & ~size_t(255); }
@@ -209,80 +330,189 @@ hipError_t reorder_by_target(vgicp_factorset_s *fs, const double *poses, hipStre
   return hipSuccess;
 }
 
-hipError_t make_sorted_sources(const vgicp_cloud *sources, int32_t n_sources,
-                               const std::vector<double> &cell, void **buffer,
-                               std::vector<SortedSource> &out, hipStream_t st,
-                               int64_t *nonfinite) {
-  *buffer = nullptr;
-  if (nonfinite) nonfinite[0] = nonfinite[1] = 0;
-  out.assign(size_t(n_sources), SortedSource{});
-  // layout: per used cloud, covariances [n][6], coordinates [n][3], permutation [n]
-  size_t total = 0;
-  uint32_t nmax = 0;
-  std::vector<size_t> off(size_t(n_sources), 0);
-  for (int32_t s = 0; s < n_sources; ++s) {
-    const int64_t n = sources[s].n;
-    if (!(cell[size_t(s)] > 0.0) || n <= 0) continue;
-    off[size_t(s)] = total;
-    total += align256(24 * size_t(n)) + align256(12 * size_t(n)) + align256(4 * size_t(n));
-    nmax = std::max(nmax, uint32_t(n));
-  }
-  if (total == 0) return hipSuccess;
+namespace {
 
+// Orders the clouds `which` one by one with a radix sort of their Morton keys,
+// into the copies out names.  Enqueued on st and synchronized.
+hipError_t sort_sources(const vgicp_cloud *sources, const std::vector<int32_t> &which,
+                        const std::vector<double> &cell, const std::vector<SortedSource> &out,
+                        unsigned long long *d_bad, hipStream_t st) {
   size_t sort_bytes = 0;
-  for (int32_t s = 0; s < n_sources; ++s) {
-    if (!(cell[size_t(s)] > 0.0) || sources[s].n <= 0) continue;
+  uint32_t nmax = 0;
+  for (int32_t s : which) {
     size_t b = 0;
-    hipError_t e = rocprim::radix_sort_pairs(nullptr, b, static_cast<const uint64_t *>(nullptr),
-                                             static_cast<uint64_t *>(nullptr),
-                                             static_cast<const uint32_t *>(nullptr),
-                                             static_cast<uint32_t *>(nullptr),
-                                             uint32_t(sources[s].n), 0, 63, st);
+    const hipError_t e = rocprim::radix_sort_pairs(
+        nullptr, b, static_cast<const uint64_t *>(nullptr), static_cast<uint64_t *>(nullptr),
+        static_cast<const uint32_t *>(nullptr), static_cast<uint32_t *>(nullptr),
+        uint32_t(sources[s].n), 0, 63, st);
     if (e != hipSuccess) return e;
     sort_bytes = std::max(sort_bytes, b);
+    nmax = std::max(nmax, uint32_t(sources[s].n));
   }
-  const size_t kbytes = align256(8 * size_t(nmax));
-  const size_t ibytes = align256(4 * size_t(nmax));
+  const size_t kbytes = align256(8 * size_t(nmax)), ibytes = align256(4 * size_t(nmax));
   char *tmp = nullptr;
-  hipError_t e = hipMalloc(buffer, total);
-  if (e == hipSuccess) e = hipMalloc(&tmp, 2 * kbytes + ibytes + align256(sort_bytes) + 256);
-  if (e != hipSuccess) {
-    if (*buffer) (void)hipFree(*buffer);
-    *buffer = nullptr;
-    return e;
-  }
+  hipError_t e = hipMalloc(&tmp, 2 * kbytes + ibytes + align256(sort_bytes));
+  if (e != hipSuccess) return e;
   uint64_t *keys_in = reinterpret_cast<uint64_t *>(tmp);
   uint64_t *keys_out = reinterpret_cast<uint64_t *>(tmp + kbytes);
   uint32_t *idx_in = reinterpret_cast<uint32_t *>(tmp + 2 * kbytes);
   void *sort_tmp = tmp + 2 * kbytes + ibytes;
-  unsigned long long *d_bad =
-      reinterpret_cast<unsigned long long *>(tmp + 2 * kbytes + ibytes + align256(sort_bytes));
-  e = hipMemsetAsync(d_bad, 0, 2 * sizeof(unsigned long long), st);
-
-  char *base = static_cast<char *>(*buffer);
-  for (int32_t s = 0; s < n_sources && e == hipSuccess; ++s) {
+  for (int32_t s : which) {
+    if (e != hipSuccess) break;
     const vgicp_cloud &c = sources[s];
-    if (!(cell[size_t(s)] > 0.0) || c.n <= 0) continue;
-    const uint32_t n = uint32_t(c.n);
-    char *p = base + off[size_t(s)];
-    float *cov_s = reinterpret_cast<float *>(p);
-    float *xyz_s = reinterpret_cast<float *>(p + align256(24 * size_t(n)));
-    int32_t *perm = reinterpret_cast<int32_t *>(p + align256(24 * size_t(n)) + align256(12 * size_t(n)));
-    const uint32_t grid = (n + kThreads - 1) / kThreads;
-    k_morton_keys<<<grid, kThreads, 0, st>>>(c.xyz, n, float(1.0 / cell[size_t(s)]), keys_in, idx_in);
+    const SortedSource &o = out[size_t(s)];
+    const uint32_t n = uint32_t(c.n), grid = (n + kThreads - 1) / kThreads;
+    int32_t *perm = const_cast<int32_t *>(o.perm);
+    k_morton_keys<<<grid, kThreads, 0, st>>>(c.xyz, n, float(1.0 / cell[size_t(s)]), keys_in,
+                                             idx_in);
     e = hipGetLastError();
     size_t b = align256(sort_bytes);
     if (e == hipSuccess)
       e = rocprim::radix_sort_pairs(sort_tmp, b, keys_in, keys_out, idx_in,
                                     reinterpret_cast<uint32_t *>(perm), n, 0, 63, st);
     if (e == hipSuccess) {
-      k_gather_points<<<grid, kThreads, 0, st>>>(c.xyz, c.cov, n, perm, xyz_s, cov_s, d_bad);
+      k_gather_points<<<grid, kThreads, 0, st>>>(c.xyz, c.cov, n, perm, const_cast<float *>(o.xyz),
+                                                 const_cast<float *>(o.cov), d_bad);
       e = hipGetLastError();
     }
-    out[size_t(s)] = SortedSource{xyz_s, cov_s, perm};
   }
-  // the temporaries are reused cloud after cloud on the stream; free them
-  // once the last gather has run
+  // the temporaries are reused cloud after cloud on the stream; free them once
+  // the last gather has run
+  const hipError_t se = hipStreamSynchronize(st);
+  if (e == hipSuccess) e = se;
+  (void)hipFree(tmp);
+  return e;
+}
+
+// Orders the clouds `which` by grouping, as many at once as kOrderWorkspace
+// holds, in ctx's scratch.  redo receives the ones that have to be sorted.
+// Enqueued on ctx's stream and synchronized.
+hipError_t group_sources(vgicp_ctx ctx, const vgicp_cloud *sources,
+                         const std::vector<int32_t> &which, const std::vector<double> &cell,
+                         const std::vector<SortedSource> &out, unsigned long long *d_bad,
+                         std::vector<int32_t> &redo) {
+  const hipStream_t st = ctx->stream;
+  const size_t count = which.size();
+  // jobs and flags first, then the batches' workspaces over each other
+  size_t head = 0;
+  OrderJob *d_jobs = nullptr;
+  uint32_t *d_redo = nullptr;
+  carve_piece<OrderJob>(nullptr, head, &d_jobs, count);
+  carve_piece<uint32_t>(nullptr, head, &d_redo, count);
+  std::vector<OrderJob> jobs(count);
+  std::vector<size_t> batch;  // first job of each
+  size_t most = 0, at = head;
+  auto place = [&](char *base) {
+    batch.clear();
+    at = head;
+    for (size_t k = 0; k < count; ++k) {
+      const size_t n = size_t(sources[which[k]].n);
+      auto carve = [&] {
+        carve_group(base, at, n, &jobs[k].g);
+        carve_piece(base, at, &jobs[k].base, size_t(1) << jobs[k].g.log2slots);
+      };
+      const size_t before = at;
+      if (k > 0) carve();
+      if (k == 0 || at - head > kOrderWorkspace || k - batch.back() >= kOrderJobs) {
+        if (k > 0) most = std::max(most, before);
+        at = head;
+        batch.push_back(k);
+        carve();
+      }
+    }
+    most = std::max(most, at);
+  };
+  place(nullptr);
+  std::string msg;
+  const int rc = ensure_scratch(ctx, most, msg);
+  if (rc != VGICP_OK) return rc == VGICP_ENOMEM ? hipErrorOutOfMemory : hipErrorUnknown;
+  char *base = static_cast<char *>(ctx->scratch);
+  place(base);
+  head = 0;
+  carve_piece(base, head, &d_jobs, count);
+  carve_piece(base, head, &d_redo, count);
+  for (size_t k = 0; k < count; ++k) {
+    const vgicp_cloud &c = sources[which[k]];
+    const SortedSource &o = out[size_t(which[k])];
+    jobs[k].xyz = c.xyz;
+    jobs[k].cov = c.cov;
+    jobs[k].xyz_out = const_cast<float *>(o.xyz);
+    jobs[k].cov_out = const_cast<float *>(o.cov);
+    jobs[k].perm = const_cast<int32_t *>(o.perm);
+    jobs[k].n = uint32_t(c.n);
+    jobs[k].inv_cell = float(1.0 / cell[size_t(which[k])]);
+    jobs[k].redo = d_redo + k;
+  }
+  hipError_t e =
+      hipMemcpyAsync(d_jobs, jobs.data(), count * sizeof(OrderJob), hipMemcpyHostToDevice, st);
+  for (size_t b = 0; b < batch.size() && e == hipSuccess; ++b) {
+    const size_t k0 = batch[b], k1 = b + 1 < batch.size() ? batch[b + 1] : count;
+    uint32_t nmax = 0, slots = 0;
+    for (size_t k = k0; k < k1; ++k) {
+      nmax = std::max(nmax, jobs[k].n);
+      slots = std::max(slots, 1u << jobs[k].g.log2slots);
+    }
+    const unsigned nj = unsigned(k1 - k0), points = (nmax + 255) / 256;
+    const OrderJob *d = d_jobs + k0;
+    k_order_clear<<<dim3(slots / 16, nj), 256, 0, st>>>(d);
+    k_order_insert<<<dim3(points, nj), 256, 0, st>>>(d);
+    k_order_compact<<<dim3(slots / kCompactSlots, nj), kCompactThreads, 0, st>>>(d);
+    k_order_number<<<dim3(kOrderBlocks + points, nj), 256, 0, st>>>(d);
+    k_order_place<<<dim3(points, nj), 256, 0, st>>>(d, d_bad);
+    e = hipGetLastError();
+  }
+  std::vector<uint32_t> flags(count);
+  if (e == hipSuccess)
+    e = hipMemcpyAsync(flags.data(), d_redo, count * sizeof(uint32_t), hipMemcpyDeviceToHost, st);
+  const hipError_t se = hipStreamSynchronize(st);
+  if (e == hipSuccess) e = se;
+  if (e != hipSuccess) return e;
+  for (size_t k = 0; k < count; ++k)
+    if (flags[k]) redo.push_back(which[k]);
+  return hipSuccess;
+}
+
+}  // namespace
+
+hipError_t make_sorted_sources(vgicp_ctx ctx, const vgicp_cloud *sources, int32_t n_sources,
+                               const std::vector<double> &cell, void **buffer,
+                               std::vector<SortedSource> &out, int64_t *nonfinite) {
+  const hipStream_t st = ctx->stream;
+  *buffer = nullptr;
+  if (nonfinite) nonfinite[0] = nonfinite[1] = 0;
+  out.assign(size_t(n_sources), SortedSource{});
+  // layout: per used cloud, covariances [n][6], coordinates [n][3], permutation
+  // [n]; then the two counts of non-finite points
+  size_t total = 0;
+  std::vector<size_t> off(size_t(n_sources), 0);
+  std::vector<int32_t> grouped, sorted;
+  for (int32_t s = 0; s < n_sources; ++s) {
+    const int64_t n = sources[s].n;
+    if (!(cell[size_t(s)] > 0.0) || n <= 0) continue;
+    off[size_t(s)] = total;
+    total += align256(24 * size_t(n)) + align256(12 * size_t(n)) + align256(4 * size_t(n));
+    (n <= kGroupMaxPoints ? grouped : sorted).push_back(s);
+  }
+  if (total == 0) return hipSuccess;
+  hipError_t e = hipMalloc(buffer, total + 2 * sizeof(unsigned long long));
+  if (e != hipSuccess) {
+    *buffer = nullptr;
+    return e;
+  }
+  char *base = static_cast<char *>(*buffer);
+  for (const auto *list : {&grouped, &sorted})
+    for (int32_t s : *list) {
+      const size_t n = size_t(sources[s].n);
+      char *p = base + off[size_t(s)];
+      out[size_t(s)] = SortedSource{
+          reinterpret_cast<float *>(p + align256(24 * n)), reinterpret_cast<float *>(p),
+          reinterpret_cast<int32_t *>(p + align256(24 * n) + align256(12 * n))};
+    }
+  auto *d_bad = reinterpret_cast<unsigned long long *>(base + total);
+  e = hipMemsetAsync(d_bad, 0, 2 * sizeof(unsigned long long), st);
+  if (e == hipSuccess && !grouped.empty())
+    e = group_sources(ctx, sources, grouped, cell, out, d_bad, sorted);
+  if (e == hipSuccess && !sorted.empty()) e = sort_sources(sources, sorted, cell, out, d_bad, st);
   unsigned long long bad[2] = {0, 0};
   if (e == hipSuccess)
     e = hipMemcpyAsync(bad, d_bad, sizeof(bad), hipMemcpyDeviceToHost, st);
@@ -292,7 +522,6 @@ hipError_t make_sorted_sources(const vgicp_cloud *sources, int32_t n_sources,
     nonfinite[0] = int64_t(bad[0]);
     nonfinite[1] = int64_t(bad[1]);
   }
-  (void)hipFree(tmp);
   if (e != hipSuccess) {
     (void)hipFree(*buffer);
     *buffer = nullptr;

@@ -464,8 +464,8 @@ int vgicp_factorset_create(vgicp_ctx ctx, const vgicp_cloud *sources, int32_t n_
       c = (c == 0.0) ? r : std::min(c, r);
     }
     int64_t nonfinite[2] = {0, 0};
-    const hipError_t se = make_sorted_sources(sources, n_sources, cell, &fs->d_sorted, sorted,
-                                              ctx->stream, nonfinite);
+    const hipError_t se = make_sorted_sources(ctx, sources, n_sources, cell, &fs->d_sorted,
+                                              sorted, nonfinite);
     fs->nonfinite_points = nonfinite[0];
     fs->nonfinite_covs = nonfinite[1];
     if (se != hipSuccess) {

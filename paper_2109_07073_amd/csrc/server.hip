@@ -587,7 +587,7 @@ int vgicp_server_add_frame(vgicp_server srv, const float *h_xyz, const float *h_
       std::vector<SortedSource> ss;
       void *buf = nullptr;
       hipStream_t st = srv->ingest.stream;
-      hipError_t se = make_sorted_sources(&c, 1, cell, &buf, ss, st);
+      hipError_t se = make_sorted_sources(&srv->ingest, &c, 1, cell, &buf, ss);
       if (se == hipSuccess && buf) {
         se = hipMemcpyAsync(fr.cloud, ss[0].xyz, size_t(3 * n) * sizeof(float),
                             hipMemcpyDeviceToDevice, st);

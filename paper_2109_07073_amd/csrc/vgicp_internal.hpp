@@ -3,6 +3,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cstdint>
 #include <string>
 #include <utility>
@@ -219,12 +220,11 @@ hipError_t launch_interleave_xyz(const float *planes, int64_t n, float *out, hip
 // Ordered copies of the clouds s with cell[s] > 0 and n > 0, in one device
 // allocation returned in *buffer (NULL when there is none); out[s] points into
 // it.  nonfinite (may be NULL) receives the number of copied points with a
-// non-finite coordinate and with a non-finite covariance entry.  Enqueued on
-// st and synchronized before returning.
-hipError_t make_sorted_sources(const vgicp_cloud *sources, int32_t n_sources,
+// non-finite coordinate and with a non-finite covariance entry.  Works in
+// ctx's scratch, enqueued on its stream and synchronized before returning.
+hipError_t make_sorted_sources(vgicp_ctx ctx, const vgicp_cloud *sources, int32_t n_sources,
                                const std::vector<double> &cell, void **buffer,
-                               std::vector<SortedSource> &out, hipStream_t st,
-                               int64_t *nonfinite = nullptr);
+                               std::vector<SortedSource> &out, int64_t *nonfinite = nullptr);
 
 // Replace the source copies of fs by per-factor copies with each factor's
 // points in the order of the target voxels they fall in at `poses` (device)
@@ -264,6 +264,10 @@ constexpr int kPairStride = 96;
 // Error bits of the device error word.
 constexpr uint32_t kErrNonFinite = 1u;
 constexpr uint32_t kErrRange = 2u;
+
+// Grows ctx's scratch to at least `bytes` (synchronizing its stream when it
+// replaces the old one).  Returns a status and sets msg on failure.
+int ensure_scratch(vgicp_ctx ctx, size_t bytes, std::string &msg);
 
 // Records `msg` as the last error of ctx (or of the calling thread when ctx
 // is NULL) and returns `code`.

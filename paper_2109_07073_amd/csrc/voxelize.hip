@@ -7,7 +7,7 @@
 // open-addressed table of brick records holding each brick's occupancy mask.
 //
 // Clouds of at most kGroupMaxPoints points are grouped by brick in a hash
-// table (see "grouped construction"): six launches and one wait of the host.
+// table (group.hpp): six launches and one wait of the host.
 // Larger clouds, and the few whose bricks do not fit the table or that put
 // more than kHeavyMax points in one voxel, are sorted instead: keys -> radix
 // sort of (key, point index) -> segment heads -> scan -> segment starts ->
@@ -19,12 +19,11 @@
 
 #include <algorithm>
 #include <cstring>
-#include <type_traits>
 
 #include <rocprim/device/device_radix_sort.hpp>
 #include <rocprim/device/device_scan.hpp>
 
-#include "vgicp_internal.hpp"
+#include "group.hpp"
 
 namespace vgicp {
 
@@ -194,255 +193,69 @@ k_build_payload(const float *__restrict__ xyz, const float *__restrict__ cov, in
 }
 
 // ---------------------------------------------------------------- grouped construction
-// Points are grouped by brick in an open-addressed table of 64 counters per
-// brick, so nothing of the cloud's size is sorted; only the bricks are
-// ordered, a few hundred to a few thousand, by counting, for each, the ones
-// before it.  Bound by the latency of dependent launches, atomics and gathers
-// (a scan moves about a megabyte), so the steps are few and each keeps many
-// loads in flight:
-//   clear    the counters and slots of the table;
-//   insert   per point: its brick's slot, its arrival number in its voxel;
-//   compact  per 512 slots: a list of the occupied ones, their masks, and
-//            where each voxel's points start;
+// group.hpp's steps with cells = voxels, and then
 //   number   per brick: its rank and the voxels before it (against every
-//            other brick), so the dense position of its voxels; and per
-//            point: its index into its voxel's list.  Its first thread hands
-//            the counts to the host, which meanwhile allocates the map;
-//   finish   per voxel: its points put back in point order (they arrive in
-//            any), gathered, and summed in that order in FP64; per brick: the
-//            lexicographic ordinals of its voxels; the table's empty records;
+//            other brick), so the dense position of its voxels.  Its first
+//            thread hands the counts to the host, which meanwhile allocates
+//            the map (the same launch scatters the points);
+//   finish   per voxel: its points put back in point order, gathered, and
+//            summed in that order in FP64; per brick: the lexicographic
+//            ordinals of its voxels; the table's empty records;
 //   records  per brick: its record.
 // A call on 20,011 returns takes 46 us (180 us by sorting), on a merged submap
 // of 320,000 points 94 us (464 us).  Beyond kGroupMaxPoints the counters'
 // share shrinks and the sort is bound by its passes, so it stays.
-constexpr int64_t kGroupMaxPoints = int64_t(1) << 20;
-constexpr uint32_t kGroupMaxSlots = 1u << 15;  // 8 MB of counters
-constexpr uint32_t kGroupProbes = 64;          // slots a point tries
-constexpr uint32_t kLightMax = 64;             // points of a voxel one wave sums
-constexpr uint32_t kHeavyMax = 4096;           // points of a voxel one block sums
 constexpr uint32_t kNumberBlocks = 512;
 constexpr uint32_t kNumberBricks = 4;  // bricks a wave numbers at once
-constexpr uint32_t kErrFull = 4u;  // a brick found no slot
-constexpr uint32_t kNoVoxel = 0xffffffffu;
-
-// Totals of the listed bricks in one word: points in the low 21 bits, voxels in
-// the next 21, bricks above.
-constexpr uint32_t kVoxelsShift = 21, kBricksShift = 42;
-constexpr uint32_t kTotalsMask = (1u << 21) - 1u;
-static_assert(kGroupMaxPoints <= int64_t(kTotalsMask), "totals in 21 bits");
-
-struct GroupHeader {
-  uint64_t totals;
-  uint32_t n_heavy;    // voxels of more than kLightMax points,
-  uint32_t max_count;  // points of the fullest of them (0 without one),
-  uint32_t heavy_at;   // and how many of them are listed
-  uint32_t err;
-};
 
 // What the host waits for (pinned); `seq` is written last.
 struct GroupCounts {
   uint32_t err, n_voxels, n_bricks, n_heavy, max_count, seq;
 };
 
-struct Group {
-  GroupHeader *hdr;
-  uint64_t *keys;       // [slots] brick key or kEmptyKey
-  uint32_t *count;      // [slots][64] points per voxel
-  uint32_t *rel;        // [slots][64] first point of a voxel in its brick's list
-  uint32_t *first;      // [slots] first point of a brick in the list
-  uint64_t *bkey, *bmask;  // [bricks] in any order
-  uint32_t *bslot;
+struct VoxelGroup : Group {
   uint64_t *skey, *smask;  // [bricks] in key order
   uint32_t *sbase;         // voxels in earlier bricks
   uint2 *sseg;             // the bricks with the same x field
-  uint32_t *code, *arrival;  // [n] slot * 64 + bit of the point's voxel
-  uint32_t *list;            // [n] points, voxel after voxel
-  uint2 *vox;                // [voxels] start in the list, points
-  uint32_t *heavy;           // voxels of more than kLightMax points
+  uint2 *vox;              // [voxels] start in the list, points
+  uint32_t *heavy;         // voxels of more than kLightMax points
 };
 
-// Sum over the wave, in every lane.
-__device__ __forceinline__ uint32_t wave_total(uint32_t v) {
-  int x = int(v);
-#define VGICP_ADD(CTRL, MASK) x += __builtin_amdgcn_update_dpp(0, x, CTRL, MASK, 0xf, false);
-  VGICP_ADD(0xb1, 0xf) VGICP_ADD(0x4e, 0xf) VGICP_ADD(0x141, 0xf) VGICP_ADD(0x140, 0xf)
-  VGICP_ADD(0x142, 0xa) VGICP_ADD(0x143, 0xc)
-#undef VGICP_ADD
-  return uint32_t(__builtin_amdgcn_readlane(x, 63));
-}
-
-// Inclusive sum over the lanes up to this one.
-__device__ __forceinline__ uint32_t wave_scan(uint32_t v) {
-  const uint32_t lane = threadIdx.x & 63;
-#pragma unroll
-  for (uint32_t d = 1; d < 64; d <<= 1) {
-    const uint32_t o = __shfl_up(v, d);
-    if (lane >= d) v += o;
-  }
-  return v;
+__global__ void __launch_bounds__(256)
+k_group_clear(VoxelGroup g) {
+  group_clear(g, blockIdx.x);
 }
 
 __global__ void __launch_bounds__(256)
-k_group_clear(Group g, uint32_t slots) {
-  const uint32_t i = blockIdx.x * 256 + threadIdx.x;  // 16 bytes of counters each
-  if (i < slots * 16) reinterpret_cast<uint4 *>(g.count)[i] = make_uint4(0, 0, 0, 0);
-  if (i < slots) g.keys[i] = kEmptyKey;
-  if (i == 0) *g.hdr = GroupHeader{0, 0, 0, 0, 0};
+k_group_insert(VoxelGroup g, const float *__restrict__ xyz, uint32_t n, float s) {
+  group_insert(g, blockIdx.x * 256 + threadIdx.x, n,
+               [&](uint32_t i, uint64_t &brick, uint32_t &cell) {
+                 int32_t k[3];
+                 const uint32_t bad = point_key(xyz, n, i, s, k);
+                 brick = brick_key(brick_field(k[0]), brick_field(k[1]), brick_field(k[2]));
+                 cell = brick_bit(k[0], k[1], k[2]);
+                 return bad;
+               });
 }
-
-// Consecutive points of a scan often fall in one voxel (the near rings put
-// hundreds there), so a wave's runs of equal keys look their brick up once and
-// take their arrival numbers with one atomic.
-__global__ void __launch_bounds__(256)
-k_group_insert(Group g, uint32_t log2slots, const float *__restrict__ xyz, uint32_t n, float s) {
-  const uint32_t i = blockIdx.x * 256 + threadIdx.x, lane = threadIdx.x & 63;
-  int32_t k[3] = {0, 0, 0};
-  uint32_t bad = i < n ? point_key(xyz, n, i, s, k) : 0u;
-  const bool valid = i < n && !bad;
-  // whole waves shuffle
-  const int32_t px = __shfl_up(k[0], 1), py = __shfl_up(k[1], 1), pz = __shfl_up(k[2], 1);
-  const int pvalid = __shfl_up(int(valid), 1);
-  const bool joins =
-      lane > 0 && valid && pvalid != 0 && px == k[0] && py == k[1] && pz == k[2];
-  const uint64_t heads = __ballot(!joins);
-  const uint32_t head = 63u - uint32_t(__clzll(heads & (~0ull >> (63 - lane))));
-  uint32_t code = kNoVoxel, arrival = 0;
-  if (valid && !joins) {
-    const uint64_t later = lane == 63 ? 0ull : heads >> (lane + 1);
-    const uint32_t run = later ? uint32_t(__ffsll((unsigned long long)later)) : 64u - lane;
-    const uint64_t key = brick_key(brick_field(k[0]), brick_field(k[1]), brick_field(k[2]));
-    const uint32_t smask = (1u << log2slots) - 1u;
-    uint32_t h = uint32_t((key * 0x9E3779B97F4A7C15ull) >> (64 - log2slots));
-    bad = kErrFull;
-    for (uint32_t p = 0; p < kGroupProbes; ++p) {
-      // a slot's key never changes once set, and a stale empty one only sends
-      // the point to the exchange
-      unsigned long long at = reinterpret_cast<volatile unsigned long long *>(g.keys)[h];
-      if (at == kEmptyKey) {
-        at = atomicCAS(reinterpret_cast<unsigned long long *>(&g.keys[h]),
-                       (unsigned long long)kEmptyKey, (unsigned long long)key);
-        if (at == kEmptyKey) at = key;
-      }
-      if (at == key) {
-        bad = 0;
-        break;
-      }
-      h = (h + 1) & smask;
-    }
-    if (!bad) {
-      code = (h << 6) | brick_bit(k[0], k[1], k[2]);
-      arrival = atomicAdd(&g.count[code], run);
-    }
-  }
-  if (bad) atomicOr(&g.hdr->err, bad);
-  code = __shfl(code, int(head));
-  arrival = __shfl(arrival, int(head)) + (lane - head);
-  if (i < n) {
-    g.code[i] = code;
-    g.arrival[i] = arrival;
-  }
-}
-
-// One block of 16 waves per kCompactSlots slots; each wave takes four bricks at
-// once.  The blocks place their bricks and points with one atomic each, few
-// enough (at most 64) that its serial updates do not show: with a block per 64
-// slots they took 10 us more.
-constexpr uint32_t kCompactSlots = 512;
-constexpr uint32_t kCompactThreads = 1024;
-constexpr uint32_t kCompactWaves = kCompactThreads / 64;
-constexpr uint32_t kSlotWaves = kCompactSlots / 64;
-static_assert(kSlotWaves <= kCompactWaves, "a thread per slot");
 
 __global__ void __launch_bounds__(kCompactThreads)
-k_group_compact(Group g) {
-  __shared__ uint32_t occupied[kCompactSlots], points[kCompactSlots], slot_n[kSlotWaves],
-      point_n[kSlotWaves], vox_n, heavy_n, most_n;
-  __shared__ uint64_t masks[kCompactSlots];
-  __shared__ uint64_t at;
-  const uint32_t tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const uint32_t slot = blockIdx.x * kCompactSlots + tid;
-  const bool used = tid < kCompactSlots && g.keys[slot] != kEmptyKey;
-  const uint64_t m = __ballot(used);
-  if (lane == 0 && wave < kSlotWaves) slot_n[wave] = uint32_t(__popcll(m));
-  if (tid == 0) vox_n = heavy_n = most_n = 0;
-  __syncthreads();
-  uint32_t nb = 0, pos = uint32_t(__popcll(m & ((1ull << lane) - 1ull)));
-#pragma unroll
-  for (uint32_t w = 0; w < kSlotWaves; ++w) {
-    if (w < wave) pos += slot_n[w];
-    nb += slot_n[w];
-  }
-  if (nb == 0) return;
-  if (used) occupied[pos] = slot;
-  __syncthreads();
-  uint32_t vox = 0, heavy = 0, most = 0;
-  for (uint32_t b0 = wave * 4; b0 < nb; b0 += kCompactWaves * 4) {
-    uint32_t c[4];
-#pragma unroll
-    for (uint32_t q = 0; q < 4; ++q) c[q] = g.count[(occupied[min(b0 + q, nb - 1)] << 6) | lane];
-#pragma unroll
-    for (uint32_t q = 0; q < 4; ++q) {
-      if (b0 + q >= nb) break;
-      const uint32_t incl = wave_scan(c[q]);
-      const uint64_t mask = __ballot(c[q] > 0);
-      if (c[q] > 0) g.rel[(occupied[b0 + q] << 6) | lane] = incl - c[q];
-      if (lane == 63) {
-        points[b0 + q] = incl;
-        masks[b0 + q] = mask;
-      }
-      vox += uint32_t(__popcll(mask));
-      heavy += uint32_t(__popcll(__ballot(c[q] > kLightMax)));
-      most = max(most, c[q]);
-    }
-  }
-  if (heavy > 0) atomicMax(&most_n, most);
-  if (lane == 0) {
-    atomicAdd(&vox_n, vox);
-    atomicAdd(&heavy_n, heavy);
-  }
-  __syncthreads();
-  const uint32_t p = tid < nb ? points[tid] : 0u;
-  const uint32_t incl = wave_scan(p);
-  if (lane == 63 && wave < kSlotWaves) point_n[wave] = incl;
-  __syncthreads();
-  if (tid == 0) {
-    uint64_t pts = 0;
-    for (uint32_t w = 0; w < kSlotWaves; ++w) pts += point_n[w];
-    at = atomicAdd(reinterpret_cast<unsigned long long *>(&g.hdr->totals),
-                   (unsigned long long)((uint64_t(nb) << kBricksShift) |
-                                        (uint64_t(vox_n) << kVoxelsShift) | pts));
-    if (heavy_n > 0) {
-      atomicAdd(&g.hdr->n_heavy, heavy_n);
-      atomicMax(&g.hdr->max_count, most_n);
-    }
-  }
-  __syncthreads();
-  if (tid < nb) {
-    uint32_t before = incl - p;
-    for (uint32_t w = 0; w < wave; ++w) before += point_n[w];
-    const uint32_t id = uint32_t(at >> kBricksShift) + tid, sl = occupied[tid];
-    g.bkey[id] = g.keys[sl];
-    g.bmask[id] = masks[tid];
-    g.bslot[id] = sl;
-    g.first[sl] = (uint32_t(at) & kTotalsMask) + before;
-  }
+k_group_compact(VoxelGroup g) {
+  group_compact(g, blockIdx.x);
 }
 
 // Blocks [0, number_blocks): bricks; the others: points.
 __global__ void __launch_bounds__(256)
-k_group_number(Group g, uint32_t number_blocks, uint32_t n, GroupCounts *host, uint32_t seq) {
+k_group_number(VoxelGroup g, uint32_t number_blocks, uint32_t n, GroupCounts *host,
+               uint32_t seq) {
   if (blockIdx.x >= number_blocks) {
-    const uint32_t i = (blockIdx.x - number_blocks) * 256 + threadIdx.x;
-    if (i >= n) return;
-    const uint32_t code = g.code[i];
-    if (code != kNoVoxel) g.list[g.first[code >> 6] + g.rel[code] + g.arrival[i]] = i;
+    group_scatter(g, (blockIdx.x - number_blocks) * 256 + threadIdx.x, n);
     return;
   }
   const uint64_t totals = g.hdr->totals;
   const uint32_t nb = uint32_t(totals >> kBricksShift);
   if (blockIdx.x == 0 && threadIdx.x == 0) {
     host->err = g.hdr->err;
-    host->n_voxels = uint32_t(totals >> kVoxelsShift) & kTotalsMask;
+    host->n_voxels = uint32_t(totals >> kCellsShift) & kTotalsMask;
     host->n_bricks = nb;
     host->n_heavy = g.hdr->n_heavy;
     host->max_count = g.hdr->max_count;
@@ -544,7 +357,7 @@ static_assert(9 * kGatherStride + 128 >= 4 * 9 * kLightStride, "light points fit
 // the place that counting the smaller indices gives them, while they are
 // gathered; more are sorted in LDS first, then gathered 256 at a time while
 // nine lanes of the first wave add the previous ones.
-__device__ void finish_heavy(float *lds, const Group &g, uint32_t d,
+__device__ void finish_heavy(float *lds, const VoxelGroup &g, uint32_t d,
                              const float *__restrict__ xyz, const float *__restrict__ cov,
                              uint32_t n, float *__restrict__ stats) {
   const uint32_t tid = threadIdx.x;
@@ -599,7 +412,7 @@ __device__ void finish_heavy(float *lds, const Group &g, uint32_t d,
 }
 
 // A voxel of at most kLightMax points, by one wave.
-__device__ __forceinline__ void finish_light(float *lds, const Group &g, uint32_t d,
+__device__ __forceinline__ void finish_light(float *lds, const VoxelGroup &g, uint32_t d,
                                              const float *__restrict__ xyz,
                                              const float *__restrict__ cov, uint32_t n,
                                              float *__restrict__ stats) {
@@ -627,7 +440,7 @@ __device__ __forceinline__ void finish_light(float *lds, const Group &g, uint32_
 // voxel's ordinal counts the voxels whose key comes first, axis after axis:
 // every voxel of the bricks with a smaller x field, and in the bricks with the
 // same x field (neighbours in key order) those its own bits select.
-__device__ __forceinline__ void finish_brick(const Group &g, uint32_t s,
+__device__ __forceinline__ void finish_brick(const VoxelGroup &g, uint32_t s,
                                              VoxelInfo *__restrict__ info) {
   const uint32_t lane = threadIdx.x & 63;
   const uint64_t key = g.skey[s], mask = g.smask[s];
@@ -686,7 +499,7 @@ __device__ __forceinline__ void finish_brick(const Group &g, uint32_t s,
 // Blocks: one per heavy voxel (they take longest), then fill_blocks empty the
 // table, then four bricks a block, then four light voxels a block.
 __global__ void __launch_bounds__(256)
-k_group_finish(Group g, uint32_t n_bricks, uint32_t n_voxels, uint32_t n_heavy,
+k_group_finish(VoxelGroup g, uint32_t n_bricks, uint32_t n_voxels, uint32_t n_heavy,
                uint32_t fill_blocks, const float *__restrict__ xyz,
                const float *__restrict__ cov, uint32_t n,
                BrickRecord *__restrict__ bricks, int64_t cap, uint32_t *__restrict__ occ,
@@ -716,7 +529,7 @@ k_group_finish(Group g, uint32_t n_bricks, uint32_t n_voxels, uint32_t n_heavy,
 }
 
 __global__ void __launch_bounds__(256)
-k_group_records(Group g, uint32_t n_bricks, BrickRecord *__restrict__ bricks, uint32_t log2cap,
+k_group_records(VoxelGroup g, uint32_t n_bricks, BrickRecord *__restrict__ bricks, uint32_t log2cap,
                 uint32_t *__restrict__ occ, uint32_t occ_mask) {
   const uint32_t s = blockIdx.x * 256 + threadIdx.x;
   if (s < n_bricks)
@@ -832,7 +645,7 @@ int voxelize_impl(vgicp_ctx ctx, const vgicp_cloud *cloud, double resolution, vg
 
 namespace vgicp {
 
-static int ensure_scratch(vgicp_ctx ctx, size_t bytes, std::string &msg) {
+int ensure_scratch(vgicp_ctx ctx, size_t bytes, std::string &msg) {
   if (ctx->scratch_bytes >= bytes) return VGICP_OK;
   if (ctx->scratch) {
     HIP_TRY(hipStreamSynchronize(ctx->stream));
@@ -846,50 +659,31 @@ static int ensure_scratch(vgicp_ctx ctx, size_t bytes, std::string &msg) {
   return VGICP_OK;
 }
 
-// Workspace of the grouped construction for n points and 2^log2slots slots.
-static size_t carve_group(char *base, size_t n, size_t slots, Group *g) {
+// Lays the workspace of a grouped construction for n points out at base (NULL:
+// only sizes it).
+static size_t carve_voxel_group(char *base, size_t n, VoxelGroup *g) {
   size_t at = 0;
-  auto take = [&](auto **p, size_t count) {
-    *p = reinterpret_cast<std::remove_reference_t<decltype(*p)>>(base + at);
-    at += align256(count * sizeof(**p));
-  };
-  take(&g->hdr, 1);
-  take(&g->keys, slots);
-  take(&g->count, slots * 64);
-  take(&g->rel, slots * 64);
-  take(&g->first, slots);
-  take(&g->bkey, slots);
-  take(&g->bmask, slots);
-  take(&g->bslot, slots);
-  take(&g->skey, slots);
-  take(&g->smask, slots);
-  take(&g->sbase, slots);
-  take(&g->sseg, slots);
-  take(&g->code, n);
-  take(&g->arrival, n);
-  take(&g->list, n);
-  take(&g->vox, n);
-  take(&g->heavy, n / kLightMax + 1);
+  carve_group(base, at, n, g);
+  const size_t slots = size_t(1) << g->log2slots;
+  carve_piece(base, at, &g->skey, slots);
+  carve_piece(base, at, &g->smask, slots);
+  carve_piece(base, at, &g->sbase, slots);
+  carve_piece(base, at, &g->sseg, slots);
+  carve_piece(base, at, &g->vox, n);
+  carve_piece(base, at, &g->heavy, n / kLightMax + 1);
   return at;
 }
 
 // Groups the cloud's points (the launches up to `number`) and waits for the
 // counts.  *taken is false when the cloud has to be sorted instead.
-static int group_points(vgicp_ctx ctx, const vgicp_cloud *cloud, float s, Group *g,
+static int group_points(vgicp_ctx ctx, const vgicp_cloud *cloud, float s, VoxelGroup *g,
                         GroupCounts *counts, bool *taken, std::string &msg) {
   const hipStream_t st = ctx->stream;
   const uint32_t n = uint32_t(cloud->n);
-  // twice as many slots as there can be bricks for a small cloud; a larger one
-  // has eight or more points to a brick (a street of 20,000 returns has about
-  // 1,000 bricks at 0.5 m and 2,500 at 0.25 m), and the counters cost 256
-  // bytes a slot to clear
-  const uint32_t want = std::min(2 * n, std::max(8192u, n / 2));
-  uint32_t log2slots = 10;
-  while ((1u << log2slots) < kGroupMaxSlots && (1u << log2slots) < want) ++log2slots;
-  const uint32_t slots = 1u << log2slots;
-  const int rc = ensure_scratch(ctx, carve_group(nullptr, n, slots, g), msg);
+  const int rc = ensure_scratch(ctx, carve_voxel_group(nullptr, n, g), msg);
   if (rc != VGICP_OK) return rc;
-  carve_group(static_cast<char *>(ctx->scratch), n, slots, g);
+  carve_voxel_group(static_cast<char *>(ctx->scratch), n, g);
+  const uint32_t slots = 1u << g->log2slots;
   // the counts follow the two words of the sorted construction
   constexpr int kCountsWord = 4;
   auto *host = reinterpret_cast<GroupCounts *>(ctx->host_pinned + kCountsWord);
@@ -899,8 +693,8 @@ static int group_points(vgicp_ctx ctx, const vgicp_cloud *cloud, float s, Group 
       reinterpret_cast<GroupCounts *>(static_cast<uint32_t *>(pinned_dev) + kCountsWord);
   const uint32_t seq = ++ctx->group_seq;
   const uint32_t points = grid_for(n), number = std::min(kNumberBlocks, grid_for(n, 16));
-  k_group_clear<<<slots / 16, 256, 0, st>>>(*g, slots);
-  k_group_insert<<<points, 256, 0, st>>>(*g, log2slots, cloud->xyz, n, s);
+  k_group_clear<<<slots / 16, 256, 0, st>>>(*g);
+  k_group_insert<<<points, 256, 0, st>>>(*g, cloud->xyz, n, s);
   k_group_compact<<<slots / kCompactSlots, kCompactThreads, 0, st>>>(*g);
   k_group_number<<<number + points, 256, 0, st>>>(*g, number, n, host_dev, seq);
   HIP_TRY(hipGetLastError());
@@ -940,7 +734,7 @@ int voxelize_impl(vgicp_ctx ctx, const vgicp_cloud *cloud, double resolution, vg
 
   int64_t n_voxels = 0, n_bricks = 0;
   VoxScratch sc{};
-  Group group{};
+  VoxelGroup group{};
   GroupCounts counts{};
   bool grouped = false;
   if (n > 0 && n <= kGroupMaxPoints) {

@@ -142,6 +142,21 @@ __device__ __forceinline__ CloudRsrc tile_rsrc(const float *xyz, uint32_t begin,
   return {make_rsrc(xyz + 3ull * begin, 12ull * (end - begin))};
 }
 
+// The byte offset of the tile's point threadIdx.x; opaque, since the compiler
+// would otherwise multiply every (row + threadIdx.x) by 12.
+__device__ __forceinline__ uint32_t thread_offset() {
+  uint32_t o = threadIdx.x * 12u;
+  asm("" : "+v"(o));
+  return o;
+}
+
+// The point `row` (uniform) past the one at byte offset `o` of the tile.
+__device__ __forceinline__ void load_row(const CloudRsrc &c, uint32_t o, uint32_t row,
+                                         float p[3]) {
+  const f32x3 v = ld_f32x3<kNT>(c.p, o + row * 12u);
+  p[0] = v.x, p[1] = v.y, p[2] = v.z;
+}
+
 // Point `i` of the tile (counted from its first point).
 __device__ __forceinline__ void load_xyz(const CloudRsrc &c, uint32_t i, float p[3]) {
   const f32x3 v = ld_f32x3<kNT>(c.p, i * 12u);
@@ -178,8 +193,25 @@ __device__ __forceinline__ void up_table_fill(uint8_t *t) {
     t[i] = uint8_t(brick_bit(int32_t(i >> 4), int32_t(i >> 2) & 3, int32_t(i) & 3) ^ 63u);
 }
 
+// The low bits of a (two or one), the others from b: v_bfi_b32, which the
+// compiler would otherwise split into ands and ors.
+__device__ __forceinline__ uint32_t low2_of(uint32_t a, uint32_t b) {
+  uint32_t d;
+  asm("v_bfi_b32 %0, 3, %1, %2" : "=v"(d) : "v"(a), "v"(b));
+  return d;
+}
+__device__ __forceinline__ uint32_t low1_of(uint32_t a, uint32_t b) {
+  uint32_t d;
+  asm("v_bfi_b32 %0, 1, %1, %2" : "=v"(d) : "v"(a), "v"(b));
+  return d;
+}
+
 // With kTable the voxel's bit comes from the table `up` in LDS, else it is
-// computed.
+// computed.  (With fields that carry the key order's bias, a 32-bit multiply in
+// the hash and the home's position built from ands and ors, a pass took 10 of
+// its 66 instruction slots more.  With them gone, the tile's rows counted in
+// scalar registers, and 11 FP64 operations fewer per hit, a round of 4,500
+// factors takes 544 us instead of 575 and one of 500 81.5 instead of 84.6.)
 template <bool kTable = false>
 __device__ __forceinline__ VoxelKey voxel_key(const float v[3], uint32_t log2cap,
                                               const uint8_t *up = nullptr) {
@@ -187,17 +219,20 @@ __device__ __forceinline__ VoxelKey voxel_key(const float v[3], uint32_t log2cap
   const float vy = fminf(fmaxf(v[1], kClampLoF), kClampHiF);
   const float vz = fminf(fmaxf(v[2], kClampLoF), kClampHiF);
   const int32_t kx = floor_i32(vx), ky = floor_i32(vy), kz = floor_i32(vz);
-  const uint32_t fx = brick_field(kx), fy = brick_field(ky), fz = brick_field(kz);
+  const uint32_t bx = __builtin_amdgcn_ubfe(uint32_t(kx), 2, kBrickBits);
+  const uint32_t bz = __builtin_amdgcn_ubfe(uint32_t(kz), 2, kBrickBits);
   VoxelKey r;
-  r.klo = (fy << kBrickBits) | fz;
-  r.khi = (fx << (2 * kBrickBits - 32)) | (fy >> (32 - kBrickBits));
+  r.klo = (uint32_t(ky >> 2) << kBrickBits) | bz;
+  r.khi = (bx << (2 * kBrickBits - 32)) |
+          __builtin_amdgcn_ubfe(uint32_t(ky), 2 + 32 - kBrickBits, 2 * kBrickBits - 32);
   if constexpr (kTable) {
-    const uint32_t i = (uint32_t(kx & 3) << 4) | (uint32_t(ky & 3) << 2) | uint32_t(kz & 3);
+    const uint32_t i = (uint32_t(kx & 3) << 4) | low2_of(uint32_t(kz), uint32_t(ky & 3) << 2);
     r.up = up[i];
   } else {
     r.up = brick_bit(kx, ky, kz) ^ 63u;
   }
-  r.h = brick_slot(fx, fy, fz, log2cap);
+  const uint32_t line4 = brick_line4(uint32_t(kx >> 3), uint32_t(ky >> 3), bz, log2cap);
+  r.h = low2_of(low1_of(bx, uint32_t(ky) >> 1), line4);
   return r;
 }
 
@@ -261,7 +296,9 @@ __device__ __forceinline__ int find_voxel(Rsrc rb, uint32_t log2cap, const Voxel
   uint64_t rkey = u64_of(home.km.x, home.km.y);
   uint64_t mask = u64_of(home.km.z, home.km.w);
   uint32_t base = home.base;
-  const bool probe = occupied && rkey != key && rkey != kEmptyKey;
+  // (a record key's high half is never all ones)
+  const bool probe =
+      occupied && rkey != key && __builtin_bit_cast(uint32_t, home.km.y) != 0xffffffffu;
   if (__builtin_amdgcn_ballot_w64(probe) != 0) {
     if (probe) {
       const uint32_t cm = (1u << log2cap) - 1u;
@@ -410,18 +447,19 @@ __device__ __forceinline__ void two_sum(float a, float b, float &s, float &err) 
   err = (a - (s - bp)) + (b - bp);
 }
 
-// Source-frame residual r = R^T (m - (R mu + t)) = R^T (m - t) - mu, in FP64
-// from the FP32 point and voxel mean and the FP64 relative pose, rounded once
-// to FP32.  FP64 fused multiply-adds issue at the unpacked FP32 rate on
+// Source-frame residual r = R^T (m - (R mu + t)) = R^T m - R^T t - mu, in FP64
+// from the FP32 point and voxel mean and the FP64 relative pose (rt = R^T t),
+// rounded once to FP32.  FP64 fused multiply-adds issue at the unpacked FP32 rate on
 // gfx950, so this costs about as much as an FP32 transform and rotation and is
 // accurate to the rounding of the residual itself.
-__device__ __forceinline__ void residual64(const double R[9], const double t[3], float x,
+__device__ __forceinline__ void residual64(const double R[9], const double rt[3], float x,
                                            float y, float z, const float m[3], float r[3]) {
-  const double d0 = double(m[0]) - t[0], d1 = double(m[1]) - t[1], d2 = double(m[2]) - t[2];
+  const double m0 = m[0], m1 = m[1], m2 = m[2];
   const double p[3] = {x, y, z};
 #pragma unroll
   for (int c = 0; c < 3; ++c) {
-    const double q = __builtin_fma(R[6 + c], d2, __builtin_fma(R[3 + c], d1, R[c] * d0));
+    const double q = __builtin_fma(R[6 + c], m2,
+                                   __builtin_fma(R[3 + c], m1, __builtin_fma(R[c], m0, -rt[c])));
     r[c] = float(q - p[c]);
   }
 }
@@ -584,7 +622,8 @@ struct FactorConsts {
   float R[9];     // fl32(R): per-point algebra and the FP32 residual
   float t[3];     // fl32(t): FP32 residual
   double R64[9];  // R itself: FP64 residual and FP64 fused covariance
-  double t64[3];  // t itself: FP64 residual
+  double t64[3];  // t itself: FP64 residual in the target frame
+  double rt64[3]; // R^T t: FP64 residual in the source frame
 };
 static_assert(sizeof(FactorConsts) == kFactorConstsBytes, "the factor set's constant table");
 
@@ -616,7 +655,8 @@ __device__ __forceinline__ bool fused_information_fp64(const double R[9], const 
     W[6 + col] = s2 * r0 + s4 * r1 + s5 * r2;
   }
   auto f = [&](int a, int b, double cc) {
-    return R[a] * W[b] + R[3 + a] * W[3 + b] + R[6 + a] * W[6 + b] + cc;
+    return __builtin_fma(R[6 + a], W[6 + b],
+                         __builtin_fma(R[3 + a], W[3 + b], __builtin_fma(R[a], W[b], cc)));
   };
   const double f00 = f(0, 0, c[0]), f01 = f(0, 1, c[1]), f02 = f(0, 2, c[2]);
   const double f11 = f(1, 1, c[3]), f12 = f(1, 2, c[4]), f22 = f(2, 2, c[5]);
@@ -951,6 +991,7 @@ __device__ __forceinline__ FactorConsts factor_consts_lane(const FactorDesc &fd,
     k.u[i] = float(s * t[i]);
     k.t[i] = float(t[i]);
     k.t64[i] = t[i];
+    k.rt64[i] = __builtin_fma(R[6 + i], t[2], __builtin_fma(R[3 + i], t[1], R[i] * t[0]));
   }
   return k;
 }
@@ -972,6 +1013,7 @@ __device__ __forceinline__ FactorConsts factor_consts(const FactorDesc &fd,
     k.u[i] = uniform_f(l.u[i]);
     k.t[i] = uniform_f(l.t[i]);
     k.t64[i] = uniform_d(l.t64[i]);
+    k.rt64[i] = uniform_d(l.rt64[i]);
   }
   return k;
 }
@@ -1065,7 +1107,9 @@ __device__ __forceinline__ void batch_load(Batch &B, const HitQueue &Q, uint32_t
   B.c[3] = c1.x, B.c[4] = c1.y, B.c[5] = c1.z;
   // the voxel's statistics: 36 packed bytes
   const uint32_t v = uint32_t(live ? pidx : 0);
-  const uint32_t so = v * 36u;
+  uint32_t so;  // 36 v: two shifts and an add, where a 32-bit multiply takes four slots
+  asm("v_lshl_add_u32 %0, %1, 3, %1" : "=v"(so) : "v"(v));
+  so <<= 2;
   B.w0 = ld_f32x4(rs, so);
   B.w1 = ld_f32x4(rs, so + 16u);
   B.czz = ld_f32(rs, so + 32u);
@@ -1115,7 +1159,7 @@ __device__ __forceinline__ void batch_math(SumsT &acc, const Batch &B, const Fac
   }
   float r[3];
   if constexpr (R64) {
-    residual64(k.R64, k.t64, B.x, B.y, B.z, m, r);
+    residual64(k.R64, k.rt64, B.x, B.y, B.z, m, r);
   } else {
 #pragma clang fp contract(off)
     // e = m - T mu in FP32 (target frame), then rotated into the source frame
@@ -1194,12 +1238,14 @@ __device__ __forceinline__ void linearize_tile(
   const uint32_t end = min(begin + uint32_t(fd.tile_points), n);
   const CloudRsrc cx = tile_rsrc(fd.xyz, begin, end);
   const uint32_t lane = threadIdx.x & 63;
-  const uint32_t wave = threadIdx.x >> 6;
+  const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const uint32_t n_pts = end - begin;
 
   // Coordinates of the chunk's kChunk passes (prefetched one chunk ahead;
   // past the tile's end the loads return zeros and the lanes are invalid).
   float cur[kChunk][3];
-  uint32_t base = begin + wave * 64;
+  uint32_t row = 0;  // the chunk's first row of the tile (uniform)
+  const uint32_t first = thread_offset();
   uint32_t ow[kOccWordsPerThread];
   tile_loads<kChunk>(fd, cx, ow, cur);
   // the relative pose (from the round's table when there is one) while the
@@ -1227,7 +1273,7 @@ __device__ __forceinline__ void linearize_tile(
   uint32_t nwide = 0;            // per lane: hits with the FP64 fused covariance
   uint32_t ndeg = 0;  // hits with a degenerate fused covariance (complete in lane 0)
 
-  while (base < end) {
+  while (row + wave * 64 < n_pts) {
     // ---- lookup phase: the brick records of all kChunk passes are in flight
     // at once, then the next chunk's coordinates; records are then resolved
     // in order, so each wait leaves the later records and the whole prefetch
@@ -1248,15 +1294,15 @@ __device__ __forceinline__ void linearize_tile(
     float nxt[kChunk][3];
 #pragma unroll
     for (int p = 0; p < kChunk; ++p)
-      load_xyz(cx, base - begin + (kChunk + p) * kBlock + lane, nxt[p]);
+      load_row(cx, first, row + uint32_t(kChunk + p) * kBlock, nxt[p]);
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int p = 0; p < kChunk; ++p) {
-      const uint32_t i = base + p * kBlock + lane;
+      const uint32_t i = row + p * kBlock + threadIdx.x;
       const int h = find_voxel(rb, fd.log2cap, vk[p], rec[p], occ[p]);
-      const bool hit = h >= 0 && i < end;
+      const bool hit = h >= 0 && i < n_pts;
       if constexpr (CORR) {
-        if (i < end && !hit) pcorr.put(i - begin, -1);
+        if (i < n_pts && !hit) pcorr.put(i, -1);
       }
       const uint64_t mask = __builtin_amdgcn_ballot_w64(hit);
       if (hit) {
@@ -1266,7 +1312,7 @@ __device__ __forceinline__ void linearize_tile(
         Q.x[e] = cur[p][0];
         Q.y[e] = cur[p][1];
         Q.z[e] = cur[p][2];
-        Q.idx[e] = int32_t(i - begin);
+        Q.idx[e] = int32_t(i);
         Q.pidx[e] = h;
       }
       const uint32_t got = uint32_t(__popcll(mask));
@@ -1277,7 +1323,7 @@ __device__ __forceinline__ void linearize_tile(
     for (int p = 0; p < kChunk; ++p)
 #pragma unroll
       for (int a = 0; a < 3; ++a) cur[p][a] = nxt[p][a];
-    base += kChunk * kBlock;
+    row += kChunk * kBlock;
     __builtin_amdgcn_wave_barrier();
     // ---- math phase: full batches, double-buffered
     const uint32_t nb = count / 64;
@@ -1419,8 +1465,9 @@ __device__ __forceinline__ void overlap_tile(int *lds_cnt, uint32_t *occ_lds,
   const uint32_t end = min(begin + uint32_t(fd.tile_points), n);
   const CloudRsrc cx = tile_rsrc(fd.xyz, begin, end);
   float cur[kOvlChunk][3];
-  uint32_t base = begin + (threadIdx.x & ~63u);
-  const uint32_t lane = threadIdx.x & 63;
+  const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const uint32_t n_pts = end - begin;
+  const uint32_t first = thread_offset();
   uint32_t ow[kOccWordsPerThread];
   tile_loads<kOvlChunk>(fd, cx, ow, cur);
   // the relative pose while the loads are in flight
@@ -1430,7 +1477,7 @@ __device__ __forceinline__ void overlap_tile(int *lds_cnt, uint32_t *occ_lds,
   __syncthreads();
   const Rsrc rb = make_rsrc(fd.bricks, 32ull << fd.log2cap);
   int hits = 0;
-  for (; base < end; base += kOvlChunk * kBlock) {
+  for (uint32_t row = 0; row + wave * 64 < n_pts; row += kOvlChunk * kBlock) {
     VoxelKey vk[kOvlChunk];
     RecordLoad rec[kOvlChunk];
     bool occ[kOvlChunk];
@@ -1447,11 +1494,11 @@ __device__ __forceinline__ void overlap_tile(int *lds_cnt, uint32_t *occ_lds,
     float nxt[kOvlChunk][3];
 #pragma unroll
     for (int p = 0; p < kOvlChunk; ++p)
-      load_xyz(cx, base - begin + (kOvlChunk + p) * kBlock + lane, nxt[p]);
+      load_row(cx, first, row + uint32_t(kOvlChunk + p) * kBlock, nxt[p]);
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int p = 0; p < kOvlChunk; ++p) {
-      const bool valid = base + p * kBlock + lane < end;
+      const bool valid = row + p * kBlock + threadIdx.x < n_pts;
       const int hs = find_voxel(rb, fd.log2cap, vk[p], rec[p], occ[p]);
       hits += (valid && hs >= 0) ? 1 : 0;
     }

@@ -41,13 +41,16 @@ __host__ __device__ inline int32_t key_field(uint64_t key, int which) {
 // share brick records (and cache lines) instead of scattering over a
 // voxel-keyed table.
 //
-// A brick is named by one field per axis, floor(k / 4) + 2^18 + 1, which is
-// in [1, 2^19] for keys in [-2^20, 2^20).  A lookup clamps the scaled
+// In key order, a brick is named by one field per axis, floor(k / 4) + 2^18 +
+// 1, which is in [1, 2^19] for keys in [-2^20, 2^20), 20 bits each (60 bits,
+// never kEmptyKey), x highest.  Its record holds the same without the bias,
+// floor(k / 4) in 20 bits of two's complement per axis, which a lookup takes
+// from the key with one bit-field extract.  A lookup clamps the scaled
 // coordinate to [-2^20 - 4, 2^20] instead of testing the range, so a point
-// outside the key range (or NaN) gets field 0 or 2^19 + 1: a brick no map
-// holds.  Record keys pack the fields in 20 bits each (60 bits, never
-// kEmptyKey).
+// outside the key range (or NaN) gets a field of -2^18 - 1 or 2^18: a brick no
+// map holds.
 constexpr int kBrickBits = 20;
+constexpr uint32_t kBrickMask = (1u << kBrickBits) - 1u;
 constexpr int32_t kBrickBias = (1 << 18) + 1;
 constexpr float kClampLoF = -1048580.0f;  // -2^20 - 4
 constexpr float kClampHiF = 1048576.0f;   // 2^20
@@ -58,6 +61,16 @@ __host__ __device__ inline uint32_t brick_field(int32_t k) {
 
 __host__ __device__ inline uint64_t brick_key(uint32_t fx, uint32_t fy, uint32_t fz) {
   return (uint64_t(fx) << (2 * kBrickBits)) | (uint64_t(fy) << kBrickBits) | uint64_t(fz);
+}
+
+// floor(k / 4) on axis `which` (0: x) of a brick in key order.
+__host__ __device__ inline int32_t brick_coord(uint64_t key, int which) {
+  return int32_t(uint32_t(key >> ((2 - which) * kBrickBits)) & kBrickMask) - kBrickBias;
+}
+
+// The key of a brick's record, from floor(k / 4) on each axis.
+__host__ __device__ inline uint64_t record_key(int32_t bx, int32_t by, int32_t bz) {
+  return brick_key(uint32_t(bx) & kBrickMask, uint32_t(by) & kBrickMask, uint32_t(bz) & kBrickMask);
 }
 
 // Bits of b taken where m is set, the others from a (one v_bfi_b32).
@@ -88,29 +101,39 @@ __host__ __device__ inline uint64_t brick_key_of_sort_key(uint64_t sk) {
   return brick_key(uint32_t(g >> 38) + 1u, (uint32_t(g >> 19) & m) + 1u, (uint32_t(g) & m) + 1u);
 }
 
-// Home record of a brick.  The four bricks of a 2 x 2 x 1 group (fields x
-// and y halved) share one 128-byte line of four records, each at the position
-// given by the low bits of its x and y fields, so the bricks a wave's points
-// touch fall in few lines.  The line is a linear combination of the group's
-// coordinates with odd 24-bit multipliers (full-rate 24-bit multiplies on
-// gfx950) folded to 32 bits, spread by a 32-bit Fibonacci multiply.  Probing
-// steps one line on, at the same position.  Replaying 40 scan factors on the
-// CPU, a 64-point wave touches 6.0 record lines here against 9.7 for one
-// record per hashed brick, and about 1 % of waves probe past a home record.
+// Home record of a brick at floor(k / 4) = (bx, by, bz).  The four bricks of a
+// 2 x 2 x 1 group (bx and by halved) share one 128-byte line of four records,
+// each at the position given by the low bits of bx and by, so the bricks a
+// wave's points touch fall in few lines.  The line is a linear combination of
+// the group's coordinates with odd multipliers, whose low 24 bits a last odd
+// multiplier spreads over 32: three 24-bit multiplies, which run at full rate
+// on gfx950 (a 32-bit one takes a quarter of it).  Probing steps one line on,
+// at the same position.  Replaying 40 scan factors on the CPU, a 64-point wave
+// touches 2.4 record lines in Morton order at 0.5 m, and 1 % of waves probe
+// past a home record (11 % at 0.25 m, 4 % at 1 m).
 constexpr uint32_t kProbeStep = 4;
+constexpr uint32_t kLineX = 49571u, kLineY = 4301u, kLineSpread = 11714915u;
 
-__host__ __device__ inline uint32_t brick_slot(uint32_t fx, uint32_t fy, uint32_t fz,
-                                               uint32_t log2cap) {
-  const uint32_t k = fz + ((fy >> 1) & 0xffffffu) * 353u + ((fx >> 1) & 0xffffffu) * 294913u;
-  // the line, (k * 0x9E3779B9) >> (34 - log2cap), shifted left by two
-  const uint32_t line4 = (k * 0x9E3779B9u) >> (32 - log2cap);
-  return bit_select(~3u, line4, bit_select(2u, fy << 1, fx));
+// The low 32 bits of the product of the low 24 bits of a and b, plus c.  (Of
+// the plain expression the compiler makes a 32-bit multiply where only the low
+// 24 bits of the result are used.)
+__device__ inline uint32_t mad24(uint32_t a, uint32_t b, uint32_t c) {
+  uint32_t d;
+  asm("v_mad_u32_u24 %0, %1, %2, %3" : "=v"(d) : "v"(a), "s"(b), "v"(c));
+  return d;
 }
 
-__host__ __device__ inline uint32_t brick_slot_of_key(uint64_t bkey, uint32_t log2cap) {
-  const uint32_t m = (1u << kBrickBits) - 1u;
-  return brick_slot(uint32_t(bkey >> (2 * kBrickBits)) & m, uint32_t(bkey >> kBrickBits) & m,
-                    uint32_t(bkey) & m, log2cap);
+// The line shifted left by two (and two lower bits of no meaning), from bx / 2,
+// by / 2 and bz, each with at least 24 bits of its two's complement (bz: 20).
+__device__ inline uint32_t brick_line4(uint32_t hx, uint32_t hy, uint32_t bz,
+                                       uint32_t log2cap) {
+  const uint32_t k = mad24(hx, kLineX, mad24(hy, kLineY, bz & kBrickMask));
+  return ((k & 0xffffffu) * kLineSpread) >> (32 - log2cap);
+}
+
+__device__ inline uint32_t brick_slot(int32_t bx, int32_t by, int32_t bz, uint32_t log2cap) {
+  return (brick_line4(uint32_t(bx >> 1), uint32_t(by >> 1), uint32_t(bz), log2cap) & ~3u) |
+         (uint32_t(by) & 1u) << 1 | (uint32_t(bx) & 1u);
 }
 
 // Occupancy bitset of a map's brick table: bit (h mod B) is set when record h
@@ -131,7 +154,7 @@ constexpr int64_t kMaxMapBricks = int64_t(1) << 24;
 
 // A voxel map is an open-addressed table of brick records (linear probing,
 // load factor at most 1/8) plus dense per-voxel arrays:
-//   bricks[cap]  32-byte records {brick key (kEmptyKey when free), occupancy
+//   bricks[cap]  32-byte records {record key (kEmptyKey when free), occupancy
 //                mask, index of the brick's first voxel}; a lookup reads key
 //                and mask with one 16-byte load and the base with a second
 //                load from the same record;
@@ -171,9 +194,9 @@ constexpr int kTileQuantum = 256 * kLookupPasses;
 constexpr int kDefaultTile = 6 * kTileQuantum;  // 4608 points
 
 // Bytes of one factor's relative-pose constants in a factor set's table
-// (FP32 rotation and translation scaled by 1/r and unscaled, FP64 rotation
-// and translation).
-constexpr size_t kFactorConstsBytes = 24 * sizeof(float) + 12 * sizeof(double);
+// (FP32 rotation and translation scaled by 1/r and unscaled, FP64 rotation,
+// translation and rotated translation).
+constexpr size_t kFactorConstsBytes = 24 * sizeof(float) + 15 * sizeof(double);
 
 // Per-factor device descriptor (read with uniform loads by every tile).
 struct FactorDesc {

@@ -121,12 +121,15 @@ k_brick_heads(const uint64_t *__restrict__ bsort, int64_t n_voxels, uint32_t *__
   head[d] = (d == 0 || (bsort[d] >> 6) != (bsort[d - 1] >> 6)) ? 1u : 0u;
 }
 
-// Linear-probing insertion of a brick's record and its occupancy bit.
-__device__ __forceinline__ void insert_record(uint64_t key, uint64_t mask, uint32_t base,
+// Linear-probing insertion of a brick's record (`brick` in key order) and its
+// occupancy bit.
+__device__ __forceinline__ void insert_record(uint64_t brick, uint64_t mask, uint32_t base,
                                               BrickRecord *__restrict__ bricks, uint32_t log2cap,
                                               uint32_t *__restrict__ occ, uint32_t occ_mask) {
   const uint32_t cmask = (1u << log2cap) - 1u;
-  uint32_t h = brick_slot_of_key(key, log2cap);
+  const int32_t bx = brick_coord(brick, 0), by = brick_coord(brick, 1), bz = brick_coord(brick, 2);
+  const uint64_t key = record_key(bx, by, bz);
+  uint32_t h = brick_slot(bx, by, bz, log2cap);
   // the records of one position in the lines: cap / kProbeStep of them
   for (uint32_t probe = 0; probe <= (cmask >> 2); ++probe) {
     const unsigned long long prev =

@@ -1036,16 +1036,16 @@ static_assert(kOccWordsPerThread * kBlock * 32 == int(kOccMaxBits), "whole words
 // across the caller's barrier.  Words past the bitset and points past the
 // tile read zeros without a memory request.  (A block that runs several tiles
 // of one map stores the same words again.)
-template <int NP>
-__device__ __forceinline__ void tile_loads(const FactorDesc &fd, const CloudRsrc &cx,
-                                           uint32_t ow[kOccWordsPerThread], float cur[NP][3]) {
+template <int NP, typename Load>
+__device__ __forceinline__ void tile_loads(const FactorDesc &fd, uint32_t ow[kOccWordsPerThread],
+                                           float cur[NP][3], Load load) {
   const Rsrc ro = make_rsrc(fd.occ, 4ull * ((fd.occ_mask + 1u) >> 5));
 #pragma unroll
   for (int j = 0; j < kOccWordsPerThread; ++j)
     ow[j] = __builtin_bit_cast(uint32_t, ld_f32(ro, (threadIdx.x + uint32_t(j) * kBlock) * 4u));
   __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-  for (int p = 0; p < NP; ++p) load_xyz(cx, threadIdx.x + uint32_t(p) * kBlock, cur[p]);
+  for (int p = 0; p < NP; ++p) load(uint32_t(p) * kBlock, cur[p]);
   __builtin_amdgcn_sched_barrier(0);
 }
 
@@ -1247,7 +1247,7 @@ __device__ __forceinline__ void linearize_tile(
   uint32_t row = 0;  // the chunk's first row of the tile (uniform)
   const uint32_t first = thread_offset();
   uint32_t ow[kOccWordsPerThread];
-  tile_loads<kChunk>(fd, cx, ow, cur);
+  tile_loads<kChunk>(fd, ow, cur, [&](uint32_t r, float v[3]) { load_row(cx, first, r, v); });
   // the relative pose (from the round's table when there is one) while the
   // loads are in flight.  The gated variant always computes it: compiled with
   // the table's branch it ran 13 % slower on the full-size precision workload.
@@ -1450,7 +1450,37 @@ k_linearize_pair(const FactorDesc *__restrict__ factors, const Tile *__restrict_
         nullptr, kappa, partials_pair);
 }
 
+// Points of a caller's cloud, [3][n], for overlap_tile: one 4-byte load per
+// axis.  The same points are matched against every map, so they are left in the
+// caches.
+struct PlaneRows {
+  Rsrc p[3];
+  uint32_t first;
+  __device__ PlaneRows(const float *xyz, uint32_t n, uint32_t begin, uint32_t end)
+      : first(threadIdx.x * 4u) {
+#pragma unroll
+    for (int a = 0; a < 3; ++a)
+      p[a] = make_rsrc(xyz + uint64_t(a) * n + begin, 4ull * (end - begin));
+  }
+  __device__ __forceinline__ void load(uint32_t row, float v[3]) const {
+#pragma unroll
+    for (int a = 0; a < 3; ++a) v[a] = ld_f32(p[a], first + row * 4u);
+  }
+};
+
+// Points of a library-owned copy, [n][3].
+struct CopyRows {
+  CloudRsrc c;
+  uint32_t first;
+  __device__ CopyRows(const float *xyz, uint32_t, uint32_t begin, uint32_t end)
+      : c(tile_rsrc(xyz, begin, end)), first(thread_offset()) {}
+  __device__ __forceinline__ void load(uint32_t row, float v[3]) const {
+    load_row(c, first, row, v);
+  }
+};
+
 // Overlap hit count of one tile (Eq. (7)): brick records only.
+template <typename Rows>
 __device__ __forceinline__ void overlap_tile(int *lds_cnt, uint32_t *occ_lds,
                                              const uint8_t *up_lds, int64_t tile,
                                              const FactorDesc *__restrict__ factors,
@@ -1463,13 +1493,12 @@ __device__ __forceinline__ void overlap_tile(int *lds_cnt, uint32_t *occ_lds,
   const uint32_t n = uint32_t(fd.n);
   const uint32_t begin = uint32_t(td.start);
   const uint32_t end = min(begin + uint32_t(fd.tile_points), n);
-  const CloudRsrc cx = tile_rsrc(fd.xyz, begin, end);
+  const Rows rows(fd.xyz, n, begin, end);
   float cur[kOvlChunk][3];
   const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const uint32_t n_pts = end - begin;
-  const uint32_t first = thread_offset();
   uint32_t ow[kOccWordsPerThread];
-  tile_loads<kOvlChunk>(fd, cx, ow, cur);
+  tile_loads<kOvlChunk>(fd, ow, cur, [&](uint32_t row, float v[3]) { rows.load(row, v); });
   // the relative pose while the loads are in flight
   const FactorConsts k = factor_consts(fd, poses);
   // the previous tile's reads of the LDS counts and bits end before this barrier
@@ -1494,7 +1523,7 @@ __device__ __forceinline__ void overlap_tile(int *lds_cnt, uint32_t *occ_lds,
     float nxt[kOvlChunk][3];
 #pragma unroll
     for (int p = 0; p < kOvlChunk; ++p)
-      load_row(cx, first, row + uint32_t(kOvlChunk + p) * kBlock, nxt[p]);
+      rows.load(row + uint32_t(kOvlChunk + p) * kBlock, nxt[p]);
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int p = 0; p < kOvlChunk; ++p) {
@@ -1520,6 +1549,7 @@ __device__ __forceinline__ void overlap_tile(int *lds_cnt, uint32_t *occ_lds,
 
 // Overlap hit counts of the tiles [tile_base, tile_end), tiles dealt to
 // blocks as in k_linearize.
+template <typename Rows>
 __global__ void __launch_bounds__(kBlock)
 k_overlap(const FactorDesc *__restrict__ factors, const Tile *__restrict__ tiles,
           int64_t tile_base, int64_t tile_end, int32_t tile_stride,
@@ -1534,8 +1564,8 @@ k_overlap(const FactorDesc *__restrict__ factors, const Tile *__restrict__ tiles
   const uint32_t P = gridDim.x >> 3;
   up_table_fill(up_lds);  // read after the first tile's barrier
   for (uint32_t t = lo + (blockIdx.x >> 3); t < hi; t += P)
-    overlap_tile(lds_cnt, occ_lds, up_lds, int64_t(base) + int64_t(t) * tile_stride,
-                 factors, tiles, poses, partials);
+    overlap_tile<Rows>(lds_cnt, occ_lds, up_lds, int64_t(base) + int64_t(t) * tile_stride,
+                       factors, tiles, poses, partials);
 }
 
 // ---------------------------------------------------------------- target order
@@ -1706,8 +1736,9 @@ k_reduce(const FactorDesc *__restrict__ factors, int64_t factor_base,
   if (mode == 2) {
     if (lane == 0) {
       const int64_t hits = int64_t(s[kNumSums]);
-      inl[f] = hits;
       if (overlap) overlap[f] = fd.n > 0 ? double(hits) / double(fd.n) : 0.0;
+      // the host may be waiting for the count in its own memory
+      __hip_atomic_store(&inl[f], hits, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
     }
     return;
   }
@@ -2075,8 +2106,17 @@ hipError_t launch_reduce_pair(const vgicp_factorset_s *fs, int64_t f0, int64_t n
 hipError_t launch_overlap(const vgicp_factorset_s *fs, int64_t tb, int64_t te,
                           const double *poses, hipStream_t st, int32_t stride) {
   if (te <= tb) return hipSuccess;
-  k_overlap<<<tile_grid(te - tb, fs->persist_blocks), kBlock, 0, st>>>(
+  k_overlap<CopyRows><<<tile_grid(te - tb, fs->persist_blocks), kBlock, 0, st>>>(
       fs->d_factors, fs->d_tiles, tb, te, stride, poses, fs->d_partials);
+  return hipGetLastError();
+}
+
+// The same over factors whose xyz is a caller's cloud, [3][n].
+hipError_t launch_overlap_planes(const vgicp_factorset_s *fs, int64_t tiles, const double *poses,
+                                 hipStream_t st) {
+  if (tiles <= 0) return hipSuccess;
+  k_overlap<PlaneRows><<<tile_grid(tiles, 0), kBlock, 0, st>>>(fs->d_factors, fs->d_tiles, 0, tiles,
+                                                               1, poses, fs->d_partials);
   return hipGetLastError();
 }
 

@@ -18,8 +18,8 @@
 #include "vgicp_internal.hpp"
 
 namespace vgicp {
-hipError_t launch_overlap(const vgicp_factorset_s *fs, int64_t tb, int64_t te,
-                          const double *poses, hipStream_t st, int32_t stride = 1);
+hipError_t launch_overlap_planes(const vgicp_factorset_s *fs, int64_t tiles, const double *poses,
+                                 hipStream_t st);
 hipError_t launch_reduce(const vgicp_factorset_s *fs, int64_t f0, int64_t nf, const double *poses,
                          int mode, double *H, double *b, double *e, int64_t *inl,
                          double *overlap, hipStream_t st);
@@ -29,7 +29,21 @@ using namespace vgicp;
 
 namespace {
 
-constexpr int kOverlapTile = kDefaultTile;  // source points per overlap tile
+// Source points per overlap tile: a multiple of a block's step (two rows of 256
+// points) that gives the chip's 2,048 resident blocks about one tile each, up
+// to the size beyond which a tile's start no longer shows.  (The counts do not
+// depend on it; a cloud of 20,000 points against 199 maps in 4,608-point
+// tiles left half of the chip idle.)
+constexpr int kOverlapStep = 512;
+constexpr int kOverlapTileMax = 9 * kOverlapStep;
+constexpr int64_t kOverlapBlocks = 2048;
+
+int overlap_tile_points(int64_t points, int32_t maps) {
+  const int64_t steps =
+      (points * maps + kOverlapBlocks * kOverlapStep - 1) / (kOverlapBlocks * kOverlapStep);
+  return int(std::clamp<int64_t>(steps, 1, kOverlapTileMax / kOverlapStep)) * kOverlapStep;
+}
+
 constexpr size_t kAlign = 256;
 
 size_t aligned(size_t b) { return (b + kAlign - 1) & ~(kAlign - 1); }
@@ -66,6 +80,16 @@ int grow(vgicp_ctx ctx, size_t dev_bytes, size_t host_bytes, const char *who) {
   return VGICP_OK;
 }
 
+// Copies `words` 16-byte words of pinned host memory to the device.  For the
+// tens of kilobytes of a call's tables a launch is cheaper than the copy engine
+// and the hand-over between the two (a call against 199 maps: 30 us, 42 us with
+// hipMemcpyAsync, 48 us with the counts copied back as well).
+__global__ void __launch_bounds__(256)
+k_upload(const uint4 *__restrict__ host, uint4 *__restrict__ dev, uint32_t words) {
+  const uint32_t i = blockIdx.x * 256 + threadIdx.x;
+  if (i < words) dev[i] = host[i];
+}
+
 // Overlap (Eqs. (7)-(8)) of one cloud at `pose` against n maps at their
 // poses: hits[k] points of the cloud fall in a voxel of maps[k] under
 // T_k^-1 T, overlap[k] = hits[k] / N (0 for an empty cloud).  Synchronous on
@@ -74,39 +98,30 @@ int overlap_of_cloud(vgicp_ctx ctx, const vgicp_cloud &c, const double *pose,
                      const vgicp_map *maps, const double *map_poses, int32_t n, int64_t *hits,
                      double *overlap, const char *who) {
   if (n == 0) return VGICP_OK;
-  const int64_t tiles_per = (c.n + kOverlapTile - 1) / kOverlapTile;
+  const int tile = overlap_tile_points(c.n, n);
+  const int64_t tiles_per = (c.n + tile - 1) / tile;
   const int64_t nt = tiles_per * n;
-  // device: descriptors, tiles, poses, partials, hits, overlap, then the
-  // cloud's coordinates point by point (the layout k_overlap reads)
+  // device: descriptors, tiles, poses, partials; host: the first three and the
+  // hits, which the reduce writes there
   const size_t b_desc = aligned(sizeof(FactorDesc) * size_t(n));
   const size_t b_tile = aligned(sizeof(Tile) * size_t(std::max<int64_t>(nt, 1)));
   const size_t b_pose = aligned(sizeof(double) * 12 * size_t(n + 1));
   const size_t b_part = aligned(sizeof(double) * kPartialStride * size_t(std::max<int64_t>(nt, 1)));
-  const size_t b_hits = aligned(sizeof(int64_t) * size_t(n));
-  const size_t b_ov = aligned(sizeof(double) * size_t(n));
-  const size_t b_xyz = aligned(sizeof(float) * 3 * size_t(c.n));
-  const size_t dev = b_desc + b_tile + b_pose + b_part + b_hits + b_ov + b_xyz;
-  const size_t host = b_desc + b_tile + b_pose + b_hits + b_ov;
-  int rc = grow(ctx, dev, host, who);
+  const size_t b_in = b_desc + b_tile + b_pose;
+  int rc = grow(ctx, b_in + b_part, b_in + sizeof(int64_t) * size_t(n), who);
   if (rc) return rc;
   char *d = static_cast<char *>(ctx->map_ws);
   char *h = static_cast<char *>(ctx->map_host);
   auto *h_desc = reinterpret_cast<FactorDesc *>(h);
   auto *h_tile = reinterpret_cast<Tile *>(h + b_desc);
   auto *h_pose = reinterpret_cast<double *>(h + b_desc + b_tile);
-  auto *h_hits = reinterpret_cast<int64_t *>(h + b_desc + b_tile + b_pose);
-  auto *h_ov = reinterpret_cast<double *>(h + b_desc + b_tile + b_pose + b_hits);
-  auto *d_desc = reinterpret_cast<FactorDesc *>(d);
-  auto *d_tile = reinterpret_cast<Tile *>(d + b_desc);
-  auto *d_pose = reinterpret_cast<double *>(d + b_desc + b_tile);
-  auto *d_part = reinterpret_cast<double *>(d + b_desc + b_tile + b_pose);
-  auto *d_hits = reinterpret_cast<int64_t *>(d + b_desc + b_tile + b_pose + b_part);
-  auto *d_ov = reinterpret_cast<double *>(d + b_desc + b_tile + b_pose + b_part + b_hits);
-  auto *d_xyz = reinterpret_cast<float *>(d + b_desc + b_tile + b_pose + b_part + b_hits + b_ov);
+  auto *h_hits = reinterpret_cast<int64_t *>(h + b_in);
+  void *h_dev = nullptr;  // the device's address of h
+  hipError_t e = hipHostGetDevicePointer(&h_dev, h, 0);
+  if (e != hipSuccess)
+    return set_error(ctx, VGICP_EHIP, std::string(who) + ": " + hipGetErrorString(e));
 
-  // the pinned staging may still be read by an earlier call's copies
-  hipError_t e = hipStreamSynchronize(ctx->stream);
-  if (e != hipSuccess) return set_error(ctx, VGICP_EHIP, std::string(who) + ": " + hipGetErrorString(e));
+  // every earlier call has waited for its hits, so nothing reads the staging
   std::memcpy(h_pose, pose, 12 * sizeof(double));
   std::memcpy(h_pose + 12, map_poses, size_t(n) * 12 * sizeof(double));
   int64_t t = 0;
@@ -114,8 +129,7 @@ int overlap_of_cloud(vgicp_ctx ctx, const vgicp_cloud &c, const double *pose,
     const vgicp_voxelmap_s *m = maps[k];
     FactorDesc &fd = h_desc[k];
     std::memset(&fd, 0, sizeof(fd));
-    fd.xyz = d_xyz;
-    fd.cov = c.cov;
+    fd.xyz = c.xyz;
     fd.bricks = m->bricks;
     fd.stats = m->stats;
     fd.info = m->info;
@@ -128,34 +142,44 @@ int overlap_of_cloud(vgicp_ctx ctx, const vgicp_cloud &c, const double *pose,
     fd.scale = m->scale;
     fd.n_voxels = uint32_t(m->n_voxels);
     fd.tile_begin = int32_t(t);
-    for (int64_t s = 0; s < c.n; s += kOverlapTile) h_tile[t++] = Tile{k, int32_t(s)};
+    for (int64_t s = 0; s < c.n; s += tile) h_tile[t++] = Tile{k, int32_t(s)};
     fd.n_tiles = int32_t(t - fd.tile_begin);
     fd.tile_stride = 1;
-    fd.tile_points = kOverlapTile;
+    fd.tile_points = tile;
+    h_hits[k] = -1;
   }
   vgicp_factorset_s view;
   view.device = ctx->device;
   view.n_factors = n;
   view.n_tiles = nt;
-  view.tile_points = kOverlapTile;
-  view.d_factors = d_desc;
-  view.d_tiles = d_tile;
-  view.d_partials = d_part;
+  view.tile_points = tile;
+  view.d_factors = reinterpret_cast<FactorDesc *>(d);
+  view.d_tiles = reinterpret_cast<Tile *>(d + b_desc);
+  view.d_partials = reinterpret_cast<double *>(d + b_in);
+  const double *d_pose = reinterpret_cast<double *>(d + b_desc + b_tile);
   const hipStream_t st = ctx->stream;
-  e = hipMemcpyAsync(d, h, b_desc + b_tile + b_pose, hipMemcpyHostToDevice, st);
-  if (e == hipSuccess) e = launch_interleave_xyz(c.xyz, c.n, d_xyz, st);
-  if (e == hipSuccess) e = launch_overlap(&view, 0, nt, d_pose, st);
+  const uint32_t words = uint32_t(b_in / sizeof(uint4));
+  k_upload<<<(words + 255) / 256, 256, 0, st>>>(static_cast<const uint4 *>(h_dev),
+                                                reinterpret_cast<uint4 *>(d), words);
+  e = hipGetLastError();
+  if (e == hipSuccess) e = launch_overlap_planes(&view, nt, d_pose, st);
   if (e == hipSuccess)
-    e = launch_reduce(&view, 0, n, d_pose, 2, nullptr, nullptr, nullptr, d_hits, d_ov, st);
+    e = launch_reduce(&view, 0, n, d_pose, 2, nullptr, nullptr, nullptr,
+                      reinterpret_cast<int64_t *>(static_cast<char *>(h_dev) + b_in), nullptr, st);
+  int32_t next = 0;  // hits before it have arrived
   if (e == hipSuccess)
-    e = hipMemcpyAsync(h_hits, d_hits, b_hits + b_ov, hipMemcpyDeviceToHost, st);
-  if (e == hipSuccess) e = hipStreamSynchronize(st);
-  view.d_factors = nullptr;  // the view owns nothing
-  view.d_tiles = nullptr;
-  view.d_partials = nullptr;
-  if (e != hipSuccess) return set_error(ctx, VGICP_EHIP, std::string(who) + ": " + hipGetErrorString(e));
-  if (hits) std::memcpy(hits, h_hits, size_t(n) * sizeof(int64_t));
-  if (overlap) std::memcpy(overlap, h_ov, size_t(n) * sizeof(double));
+    e = wait_for_host_words(st, [&] {
+      while (next < n && __atomic_load_n(&h_hits[next], __ATOMIC_ACQUIRE) >= 0) ++next;
+      return next == n;
+    });
+  if (e != hipSuccess) {
+    (void)hipStreamSynchronize(st);  // nothing reads the staging after this
+    return set_error(ctx, VGICP_EHIP, std::string(who) + ": " + hipGetErrorString(e));
+  }
+  for (int32_t k = 0; k < n; ++k) {
+    if (hits) hits[k] = h_hits[k];
+    if (overlap) overlap[k] = c.n > 0 ? double(h_hits[k]) / double(c.n) : 0.0;
+  }
   return VGICP_OK;
 }
 

@@ -234,25 +234,7 @@ k_gather_factor_points(const FactorDesc *__restrict__ old_desc,
   const_cast<int32_t *>(d.perm)[local] = o.perm ? o.perm[i] : int32_t(i);
 }
 
-// Coordinates of a caller's cloud ([3][n], one plane per axis) point by point
-// ([n][3]), the layout the lookup kernels read.
-__global__ void __launch_bounds__(kThreads)
-k_interleave_xyz(const float *__restrict__ planes, uint32_t n, float *__restrict__ out) {
-  const uint32_t i = blockIdx.x * kThreads + threadIdx.x;
-  if (i >= n) return;
-  out[3ull * i] = planes[i];
-  out[3ull * i + 1] = planes[uint64_t(n) + i];
-  out[3ull * i + 2] = planes[2ull * n + i];
-}
-
 }  // namespace
-
-hipError_t launch_interleave_xyz(const float *planes, int64_t n, float *out, hipStream_t st) {
-  if (n <= 0) return hipSuccess;
-  const uint32_t grid = uint32_t((uint64_t(n) + kThreads - 1) / kThreads);
-  k_interleave_xyz<<<grid, kThreads, 0, st>>>(planes, uint32_t(n), out);
-  return hipGetLastError();
-}
 
 hipError_t launch_voxel_order_keys(const vgicp_factorset_s *fs, const double *poses,
                                    uint64_t *keys, uint32_t *vals, hipStream_t st);

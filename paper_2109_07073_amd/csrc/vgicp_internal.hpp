@@ -366,7 +366,8 @@ struct vgicp_voxelmap_s {
   }
 };
 
-struct GraphEntry {
+// A round that was asked for with use_graph: its pointers and options.
+struct ReplayedRound {
   const double *poses;
   double *H, *b, *e;
   int64_t *inl;
@@ -377,14 +378,12 @@ struct GraphEntry {
   float kappa;
   int kind;
   int form;  // VGICP_FORM_SOURCE or VGICP_FORM_PAIR
-  hipGraph_t graph = nullptr;
-  hipGraphExec_t exec = nullptr;
   uint64_t last_use = 0;  // factor set's replay counter at the last launch
 };
 
-// Captured graphs a factor set keeps; capturing one more drops the least
-// recently replayed.
-constexpr size_t kMaxGraphs = 8;
+// Replayed rounds a factor set keeps; one more drops the least recently
+// replayed.
+constexpr size_t kMaxReplayed = 8;
 
 struct vgicp_factorset_s {
   int device = 0;
@@ -415,8 +414,8 @@ struct vgicp_factorset_s {
   // when the ordered copies were made.
   int64_t nonfinite_points = 0, nonfinite_covs = 0;
   int64_t tiles_capacity = 0;       // tiles d_tiles and d_partials have room for
-  std::vector<GraphEntry> graphs;
-  uint64_t graph_clock = 0;
+  std::vector<ReplayedRound> replayed;
+  uint64_t replay_clock = 0;
   // System assembly: contributions to each pose (CSR over poses, entries are
   // factor * 4 + side (0 = as pose i, 1 = as pose j) + 2 for a factor whose
   // two poses coincide, on its pose-i entry) and to each

@@ -253,9 +253,8 @@ def _check_outputs(out, specs):
 
 def _graph_needs_out(use_graph, out):
     if use_graph and out is None:
-        raise ValueError("use_graph=True needs out=: a graph is captured per output pointer "
-                         "set, so fresh outputs on every call would capture a new graph each "
-                         "time")
+        raise ValueError("use_graph=True needs out=: a round is replayed per output pointer set, "
+                         "so fresh outputs on every call would never replay one")
 
 
 def cloud_to_device(xyz, cov, device="cuda"):
@@ -313,7 +312,7 @@ class Context:
         _check(_lib.vgicp_ctx_synchronize(self._h), self._h)
 
     def set_timing(self, enable: bool = True):
-        """Bracket each kernel launch (outside graphs) with HIP events."""
+        """Bracket each kernel launch (outside replayed rounds) with HIP events."""
         _check(_lib.vgicp_ctx_set_timing(self._h, int(bool(enable))), self._h)
 
     def reset_timing(self):
@@ -439,7 +438,7 @@ class FactorSet:
         return self._h
 
     def graph_count(self) -> int:
-        """HIP graphs the factor set holds for graph replay (at most 8)."""
+        """Replayed rounds (use_graph=True) the factor set remembers (at most 8)."""
         n = ctypes.c_int64()
         _check(_lib.vgicp_factorset_graph_count(self._h, ctypes.byref(n)))
         return n.value
@@ -484,7 +483,8 @@ def linearize_factors(ctx: Context, fs: FactorSet, poses, accum: str = "mixed",
     """Hessian factors of every factor at `poses` (float64 (P, 12) device).
     Returns dict of device tensors H (F,12,12), b (F,12), e (F,), inliers (F,)
     and corr (total_points,) when asked.  `out` may supply the same dict of
-    preallocated tensors (needed for graph replay with stable pointers).
+    preallocated tensors (needed for use_graph=True, a round replayed with
+    stable pointers).
     `form`: "source" (21 + 6 + 1 source-frame sums expanded per factor),
     "pair" (Eqs. (5)-(6) term by term, 78 + 12 + 1 sums) or "auto" (the
     factor set's form, see tune_tiles)."""

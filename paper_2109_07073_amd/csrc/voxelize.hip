@@ -694,7 +694,9 @@ static int group_points(vgicp_ctx ctx, const vgicp_cloud *cloud, float s, VoxelG
   HIP_TRY(hipHostGetDevicePointer(&pinned_dev, ctx->host_pinned, 0));
   auto *host_dev =
       reinterpret_cast<GroupCounts *>(static_cast<uint32_t *>(pinned_dev) + kCountsWord);
+  // the words may be new to this context and hold another one's counts
   const uint32_t seq = ++ctx->group_seq;
+  __atomic_store_n(&host->seq, ~seq, __ATOMIC_RELAXED);
   const uint32_t points = grid_for(n), number = std::min(kNumberBlocks, grid_for(n, 16));
   k_group_clear<<<slots / 16, 256, 0, st>>>(*g);
   k_group_insert<<<points, 256, 0, st>>>(*g, cloud->xyz, n, s);

@@ -85,3 +85,13 @@ def test_refused_points(vg, ctx, bad, code):
             vg.voxelize(ctx, *vg.cloud_to_device(x, cov), R)
         assert e.value.code == getattr(vg, code)
     check(vg, ctx, xyz, cov)
+
+
+def test_first_map_of_each_context(vg):
+    """Each context's first map has its own counts, also where its pinned words
+    last held an earlier context's first counts."""
+    rng = np.random.default_rng(9)
+    for counts in ([3] * 2000, [1], [2] * 500, [64] * 3, [1] * 4000, [5]):
+        own = vg.Context(0)
+        check(vg, own, *cloud(rng, counts, 30))
+        own.close()

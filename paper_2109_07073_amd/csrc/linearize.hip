@@ -296,9 +296,10 @@ __device__ __forceinline__ int find_voxel(Rsrc rb, uint32_t log2cap, const Voxel
   uint64_t rkey = u64_of(home.km.x, home.km.y);
   uint64_t mask = u64_of(home.km.z, home.km.w);
   uint32_t base = home.base;
-  // (a record key's high half is never all ones)
-  const bool probe =
-      occupied && rkey != key && __builtin_bit_cast(uint32_t, home.km.y) != 0xffffffffu;
+  // (a record key's high half is never all ones; its low half is where y and z
+  // of the brick are -1.  The half comes from rkey: __builtin_bit_cast of a
+  // vector's component reads its first one.)
+  const bool probe = occupied && rkey != key && uint32_t(rkey >> 32) != 0xffffffffu;
   if (__builtin_amdgcn_ballot_w64(probe) != 0) {
     if (probe) {
       const uint32_t cm = (1u << log2cap) - 1u;

@@ -95,3 +95,14 @@ def test_first_map_of_each_context(vg):
         own = vg.Context(0)
         check(vg, own, *cloud(rng, counts, 30))
         own.close()
+
+
+def test_lookups_past_bricks_at_minus_one(vg, ctx):
+    """Bricks with y = z = -1, whose record keys have all ones in their low
+    half, are home records that lookups of other bricks probe past."""
+    rng = np.random.default_rng(11)
+    x = np.arange(-4000, 4000)
+    bricks = np.concatenate([np.stack([x, np.full_like(x, -1), np.full_like(x, -1)], 1),
+                             rng.integers(-300, 300, (8000, 3))])
+    xyz = ((4 * bricks + rng.integers(0, 4, bricks.shape) + 0.5) * R).astype(np.float32)
+    check(vg, ctx, xyz, rng.uniform(-1, 1, (len(xyz), 6)).astype(np.float32))

@@ -1641,6 +1641,8 @@ __device__ __forceinline__ double column_sum(const double *__restrict__ p, int64
 // then expand the source-frame system to the 12x12 Hessian factor.
 //   mode 0: linearize (H, b, e, inliers)   1: cost only (e, inliers)
 //   mode 2: overlap (hits, overlap)
+// `signal`: the outputs are in host memory and the host waits for each factor's
+// count, which is stored when the factor's other outputs are there.
 // Bound by latency: a factor's rows (256 bytes each) come from other XCDs'
 // blocks, so each load is a trip to memory.  Both variants add in the same
 // order and give the same bits:
@@ -1673,7 +1675,7 @@ __global__ void __launch_bounds__(WIDE ? kBlock : 64)
 k_reduce(const FactorDesc *__restrict__ factors, int64_t factor_base,
          const double *__restrict__ poses, const double *__restrict__ partials, int mode,
          double *__restrict__ H, double *__restrict__ b, double *__restrict__ e,
-         int64_t *__restrict__ inl, double *__restrict__ overlap) {
+         int64_t *__restrict__ inl, double *__restrict__ overlap, bool signal) {
   constexpr int kThreads = WIDE ? kBlock : 64;
   __shared__ double s[kPartialStride];
   __shared__ double T[12], Hr[36], Ad[36], K[36], Hjj[36];
@@ -1734,20 +1736,25 @@ k_reduce(const FactorDesc *__restrict__ factors, int64_t factor_base,
   }
   if (lane <= kNumSums) s[lane] = acc;
   __syncthreads();
-  if (mode == 2) {
-    if (lane == 0) {
-      const int64_t hits = int64_t(s[kNumSums]);
-      if (overlap) overlap[f] = fd.n > 0 ? double(hits) / double(fd.n) : 0.0;
+  // the count, last
+  auto store_count = [&] {
+    const int64_t count = int64_t(s[kNumSums]);
+    if (!signal) {
       // the host may be waiting for the count in its own memory
-      __hip_atomic_store(&inl[f], hits, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+      if (lane == 0)
+        __hip_atomic_store(&inl[f], count, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+      return;
     }
-    return;
+    __syncthreads();
+    if (lane == 0)
+      __hip_atomic_store(&inl[f], count, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+  };
+  if (mode == 2) {
+    if (lane == 0 && overlap) overlap[f] = fd.n > 0 ? s[kNumSums] / double(fd.n) : 0.0;
+    return store_count();
   }
-  if (lane == 0) {
-    e[f] = s[27];
-    inl[f] = int64_t(s[kNumSums]);
-  }
-  if (mode == 1) return;
+  if (lane == 0) e[f] = s[27];
+  if (mode == 1) return store_count();
 
   // source-frame 6x6 from its upper triangle
   if (lane < 36) {
@@ -1791,6 +1798,7 @@ k_reduce(const FactorDesc *__restrict__ factors, int64_t factor_base,
     for (int k = 0; k < 6; ++k) a += Ad[6 * k + c] * s[21 + k];
     b[f * 12 + lane] = -a;
   }
+  store_count();
 }
 
 // Pair form: one 128-lane block per factor adds the factor's tile partials in
@@ -2134,21 +2142,22 @@ hipError_t launch_assemble(const vgicp_factorset_s *fs, const double *H, const d
 hipError_t launch_reduce_from(const vgicp_factorset_s *fs, int64_t f0, int64_t nf,
                               const double *poses, const double *partials, int mode, double *H,
                               double *b, double *e, int64_t *inl, double *overlap,
-                              hipStream_t st) {
+                              hipStream_t st, bool signal) {
   if (nf <= 0) return hipSuccess;
   if (reduce_wide(fs->n_factors, fs->n_tiles))
     k_reduce<true><<<unsigned(nf), kBlock, 0, st>>>(fs->d_factors, f0, poses, partials, mode, H, b,
-                                                    e, inl, overlap);
+                                                    e, inl, overlap, signal);
   else
     k_reduce<false><<<unsigned(nf), 64, 0, st>>>(fs->d_factors, f0, poses, partials, mode, H, b, e,
-                                                 inl, overlap);
+                                                 inl, overlap, signal);
   return hipGetLastError();
 }
 
 hipError_t launch_reduce(const vgicp_factorset_s *fs, int64_t f0, int64_t nf, const double *poses,
                          int mode, double *H, double *b, double *e, int64_t *inl,
-                         double *overlap, hipStream_t st) {
-  return launch_reduce_from(fs, f0, nf, poses, fs->d_partials, mode, H, b, e, inl, overlap, st);
+                         double *overlap, hipStream_t st, bool signal) {
+  return launch_reduce_from(fs, f0, nf, poses, fs->d_partials, mode, H, b, e, inl, overlap, st,
+                            signal);
 }
 
 }  // namespace vgicp

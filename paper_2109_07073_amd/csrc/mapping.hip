@@ -22,7 +22,8 @@ hipError_t launch_overlap_planes(const vgicp_factorset_s *fs, int64_t tiles, con
                                  hipStream_t st);
 hipError_t launch_reduce(const vgicp_factorset_s *fs, int64_t f0, int64_t nf, const double *poses,
                          int mode, double *H, double *b, double *e, int64_t *inl,
-                         double *overlap, hipStream_t st);
+                         double *overlap, hipStream_t st,
+                         bool signal = false);
 }  // namespace vgicp
 
 using namespace vgicp;

@@ -22,7 +22,7 @@ hipError_t launch_linearize_into(const vgicp_factorset_s *fs, int accum, int res
 hipError_t launch_reduce_from(const vgicp_factorset_s *fs, int64_t f0, int64_t nf,
                               const double *poses, const double *partials, int mode, double *H,
                               double *b, double *e, int64_t *inl, double *overlap,
-                              hipStream_t st);
+                              hipStream_t st, bool signal = false);
 }  // namespace vgicp
 
 using namespace vgicp;

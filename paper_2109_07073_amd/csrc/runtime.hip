@@ -22,7 +22,8 @@ hipError_t launch_overlap(const vgicp_factorset_s *fs, int64_t tb, int64_t te,
                           const double *poses, hipStream_t st, int32_t stride = 1);
 hipError_t launch_reduce(const vgicp_factorset_s *fs, int64_t f0, int64_t nf, const double *poses,
                          int mode, double *H, double *b, double *e, int64_t *inl,
-                         double *overlap, hipStream_t st);
+                         double *overlap, hipStream_t st,
+                         bool signal = false);
 hipError_t launch_assemble(const vgicp_factorset_s *fs, const double *H, const double *b,
                            double *Hdiag, double *bvec, double *Hoff, hipStream_t st);
 hipError_t linearize_blocks_per_cu(int accum, int fused, int form, int *blocks);

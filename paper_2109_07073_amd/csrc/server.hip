@@ -4,13 +4,19 @@
 // One worker thread owns `inflight` batch slots, each with its own stream,
 // device tables and pinned staging.  Requests are queued by vgicp_server_submit;
 // the worker packs queued requests of one kind, FIFO, into the next free slot
-// (splitting a request across batches when it does not fit), uploads the
-// slot's factor/tile/pose tables, launches the same kernels as the factor-set
-// path and copies the outputs back.  A host function enqueued after each batch
-// wakes the worker, which scatters the outputs into the requests' buffers.
-// New requests are admitted while earlier batches are still running.
+// (splitting a request across batches when it does not fit) and launches three
+// kernels: one that fetches the slot's tables, then those of the factor-set
+// path, of which the reduce writes the outputs to the slot's staging.  The
+// worker watches the counts arrive there and moves each factor's outputs into
+// its request's buffers.  New requests are admitted while earlier batches are
+// still running.  (Two requests of 580 and 45 factors of 20,000 points take 170
+// us.  With the tables copied in, the outputs copied back and a host function to
+// wake the worker they took 235: those three calls cost the worker 32 of its 45
+// us per batch.  The reduce's 24 us on the larger batch are its 730 KB on the way
+// to the host.)
 
 #include <algorithm>
+#include <atomic>
 #include <chrono>
 #include <cmath>
 #include <condition_variable>
@@ -35,7 +41,8 @@ hipError_t launch_overlap(const vgicp_factorset_s *fs, int64_t tb, int64_t te,
                           const double *poses, hipStream_t st, int32_t stride = 1);
 hipError_t launch_reduce(const vgicp_factorset_s *fs, int64_t f0, int64_t nf, const double *poses,
                          int mode, double *H, double *b, double *e, int64_t *inl,
-                         double *overlap, hipStream_t st);
+                         double *overlap, hipStream_t st,
+                         bool signal = false);
 }  // namespace vgicp
 
 using namespace vgicp;
@@ -80,33 +87,30 @@ struct Chunk {
   int64_t batch_pos;  // position of the first factor in the batch
 };
 
-// A batch moves its inputs to the device with one copy and its outputs back
-// with one: the inputs packed as [descriptors | tiles | poses] (each part
-// 256-byte aligned), the outputs of nf factors as [inliers | e | overlap | b |
-// H] (nf, nf, nf, 12 nf and 144 nf eight-byte values).
+// The outputs of nf factors are packed as [inliers | e | overlap | b | H] (nf,
+// nf, nf, 12 nf and 144 nf eight-byte values).
 constexpr size_t kOutPerFactor = 159;
-
-inline size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
 
 struct Slot {
   hipStream_t stream = nullptr;
   // device
-  unsigned char *d_in = nullptr;
-  double *d_out = nullptr;
+  FactorDesc *d_factors = nullptr;
+  double *d_poses = nullptr;
+  Tile *d_tiles = nullptr;
   double *d_partials = nullptr;
-  // pinned host staging: the descriptors are written in place in h_in, tiles
-  // and poses gathered there at launch
-  unsigned char *h_in = nullptr;
-  double *h_out = nullptr;
-  FactorDesc *h_factors = nullptr;  // = h_in
-  Tile *h_tiles = nullptr;
+  // pinned host staging, which the kernels read and write: descriptors, poses
+  // and outputs
+  FactorDesc *h_factors = nullptr;
   double *h_poses = nullptr;
+  double *h_out = nullptr;
   // batch in flight
   bool busy = false;
   bool finished = false;
   hipError_t err = hipSuccess;
   int kind = 0;
   int64_t n_factors = 0;
+  int64_t taken = 0;  // factors before it have their outputs in their requests
+  size_t chunk = 0;   // the chunk of the last of them
   std::vector<Chunk> chunks;
   std::vector<int32_t> frames_used;  // one entry per factor (source and target)
   uint64_t seq = 0;
@@ -135,7 +139,7 @@ struct vgicp_server_s {
   std::mutex ingest_mu;  // one voxelization at a time (the ingest scratch is shared)
   std::string last_error;
   std::mutex err_mu;
-  int64_t callbacks_outstanding = 0;  // completion callbacks enqueued and not yet run
+  std::atomic<bool> called{false};  // something for the worker since it last looked
   // stats
   int64_t n_batches = 0, n_completed = 0, max_req_per_batch = 0, max_inflight = 0;
 };
@@ -162,49 +166,75 @@ hipError_t host_alloc(T **p, size_t count) {
 
 void free_slot(Slot &s) {
   if (s.stream) (void)hipStreamDestroy(s.stream);
-  for (void *p : {(void *)s.d_in, (void *)s.d_out, (void *)s.d_partials})
+  for (void *p : {(void *)s.d_factors, (void *)s.d_poses, (void *)s.d_tiles, (void *)s.d_partials})
     if (p) (void)hipFree(p);
-  for (void *p : {(void *)s.h_in, (void *)s.h_out, (void *)s.h_tiles, (void *)s.h_poses})
+  for (void *p : {(void *)s.h_factors, (void *)s.h_poses, (void *)s.h_out})
     if (p) (void)hipHostFree(p);
-}
-
-// Bytes of a packed input block for F descriptors, T tiles and P poses.
-size_t in_block_bytes(int64_t F, int64_t T, int64_t P) {
-  return align256(size_t(F) * sizeof(FactorDesc)) + align256(size_t(T) * sizeof(Tile)) +
-         size_t(P) * 12 * sizeof(double);
 }
 
 hipError_t alloc_slot(Slot &s, int64_t F, int64_t T, int64_t P) {
   hipError_t e = hipStreamCreateWithFlags(&s.stream, hipStreamNonBlocking);
-  const size_t in_bytes = in_block_bytes(F, T, P);
-  if (e == hipSuccess) e = dev_alloc(&s.d_in, in_bytes);
-  if (e == hipSuccess) e = dev_alloc(&s.d_out, size_t(F) * kOutPerFactor);
+  if (e == hipSuccess) e = dev_alloc(&s.d_factors, F);
+  if (e == hipSuccess) e = dev_alloc(&s.d_poses, P * 12);
+  if (e == hipSuccess) e = dev_alloc(&s.d_tiles, T);
   if (e == hipSuccess) e = dev_alloc(&s.d_partials, T * kPartialStride);
-  if (e == hipSuccess) e = host_alloc(&s.h_in, in_bytes);
-  if (e == hipSuccess) e = host_alloc(&s.h_out, size_t(F) * kOutPerFactor);
-  if (e == hipSuccess) e = host_alloc(&s.h_tiles, T);
+  if (e == hipSuccess) e = host_alloc(&s.h_factors, F);
   if (e == hipSuccess) e = host_alloc(&s.h_poses, P * 12);
-  s.h_factors = reinterpret_cast<FactorDesc *>(s.h_in);
+  if (e == hipSuccess) e = host_alloc(&s.h_out, size_t(F) * kOutPerFactor);
   return e;
 }
 
-struct DoneArgs {
-  vgicp_server srv;
-  size_t slot;
-};
+// Fetches a batch's tables from pinned host memory, which is cheaper than the
+// copy engine and the hand-over from it: a wave per factor copies its descriptor
+// and writes its tiles, the waves after those copy the poses.  Bound by one
+// round trip to host memory.
+constexpr uint32_t kDescWords = sizeof(FactorDesc) / sizeof(uint2);
+static_assert(sizeof(FactorDesc) % sizeof(uint2) == 0 && kDescWords <= 64,
+              "a lane copies a word of the descriptor");
+__global__ void __launch_bounds__(64)
+k_batch_tables(const FactorDesc *__restrict__ h_factors, const double *__restrict__ h_poses,
+               uint32_t n_factors, uint32_t pose_values, FactorDesc *__restrict__ factors,
+               double *__restrict__ poses, Tile *__restrict__ tiles) {
+  const uint32_t f = blockIdx.x, lane = threadIdx.x;
+  if (f >= n_factors) {
+    const uint32_t i = (f - n_factors) * 64 + lane;
+    if (i < pose_values) poses[i] = h_poses[i];
+    return;
+  }
+  const FactorDesc &d = h_factors[f];
+  const int32_t begin = d.tile_begin, n = d.n_tiles, points = d.tile_points;
+  if (lane < kDescWords)
+    reinterpret_cast<uint2 *>(&factors[f])[lane] = reinterpret_cast<const uint2 *>(&d)[lane];
+  for (int32_t t = int32_t(lane); t < n; t += 64) tiles[begin + t] = Tile{int32_t(f), t * points};
+}
 
-// Runs on the HIP runtime's callback thread.  Everything it does to the
-// server happens under the lock, and the server is destroyed only once no
-// callback is outstanding, so it never touches a freed server.
-void on_batch_done(void *p) {
-  DoneArgs *a = static_cast<DoneArgs *>(p);
-  vgicp_server srv = a->srv;
-  const size_t slot = a->slot;
-  delete a;
-  std::lock_guard<std::mutex> g(srv->mu);
-  srv->slots[slot].finished = true;
-  srv->callbacks_outstanding -= 1;
-  srv->cv.notify_all();
+// Moves the outputs of `s`'s batch that have arrived into its requests' buffers,
+// while the reduce writes the next ones.  Returns whether all have been moved.
+bool take_outputs(Slot &s) {
+  const int64_t nf = s.n_factors;
+  const int64_t *inl = reinterpret_cast<const int64_t *>(s.h_out);
+  const double *h_e = s.h_out + nf, *h_ov = s.h_out + 2 * nf;
+  const double *h_b = s.h_out + 3 * nf, *h_H = s.h_out + 15 * nf;
+  for (; s.taken < nf; ++s.taken) {
+    const int64_t p = s.taken;
+    const int64_t count = __atomic_load_n(&inl[p], __ATOMIC_ACQUIRE);
+    if (count < 0) return false;
+    while (p >= s.chunks[s.chunk].batch_pos + s.chunks[s.chunk].count) ++s.chunk;
+    const Chunk &c = s.chunks[s.chunk];
+    const Request &r = *c.req;
+    const int64_t f = c.first + (p - c.batch_pos);
+    if (r.inliers) r.inliers[f] = count;
+    if (s.kind == VGICP_REQ_OVERLAP) {
+      if (r.overlap) r.overlap[f] = h_ov[p];
+    } else {
+      if (r.e) r.e[f] = h_e[p];
+      if (s.kind == VGICP_REQ_LINEARIZE) {
+        std::memcpy(r.H + f * 144, h_H + p * 144, 144 * sizeof(double));
+        std::memcpy(r.b + f * 12, h_b + p * 12, 12 * sizeof(double));
+      }
+    }
+  }
+  return true;
 }
 
 int64_t request_points(const vgicp_server_s *srv, const vgicp_factor &f) {
@@ -260,8 +290,8 @@ void launch_batch(vgicp_server srv, size_t si) {
       d.scale = tgt.map->scale;
       d.n_voxels = uint32_t(tgt.map->n_voxels);
       d.tile_begin = int32_t(nt);
-      for (int64_t st = 0; st < n; st += tp) s.h_tiles[nt++] = Tile{int32_t(nf), int32_t(st)};
-      d.n_tiles = int32_t(nt - d.tile_begin);
+      d.n_tiles = int32_t(tiles);
+      nt += tiles;
       d.tile_stride = 1;
       d.tile_points = int32_t(tp);
       s.frames_used.push_back(x.src);
@@ -295,6 +325,8 @@ void launch_batch(vgicp_server srv, size_t si) {
   s.n_factors = nf;
   s.busy = true;
   s.finished = false;
+  s.taken = 0;
+  s.chunk = 0;
   s.err = hipSuccess;
   s.seq = ++srv->batch_seq;
   ++srv->n_batches;
@@ -303,49 +335,39 @@ void launch_batch(vgicp_server srv, size_t si) {
   for (const Slot &o : srv->slots) inflight += o.busy ? 1 : 0;
   srv->max_inflight = std::max(srv->max_inflight, inflight);
 
-  // one copy in: descriptors (written in place), tiles and poses packed
-  const size_t off_tiles = align256(size_t(nf) * sizeof(FactorDesc));
-  const size_t off_poses = off_tiles + align256(size_t(nt) * sizeof(Tile));
-  const size_t in_bytes = off_poses + size_t(npose) * 12 * sizeof(double);
-  std::memcpy(s.h_in + off_tiles, s.h_tiles, size_t(nt) * sizeof(Tile));
-  std::memcpy(s.h_in + off_poses, s.h_poses, size_t(npose) * 12 * sizeof(double));
-  double *d_poses = reinterpret_cast<double *>(s.d_in + off_poses);
   vgicp_factorset_s view;
   view.device = srv->device;
   view.n_factors = nf;
   view.n_tiles = nt;
   view.tile_points = int32_t(tp);
-  view.d_factors = reinterpret_cast<FactorDesc *>(s.d_in);
-  view.d_tiles = reinterpret_cast<Tile *>(s.d_in + off_tiles);
+  view.d_factors = s.d_factors;
+  view.d_tiles = s.d_tiles;
   view.d_partials = s.d_partials;
-  // outputs [inliers | e | overlap | b | H]
-  int64_t *d_inl = reinterpret_cast<int64_t *>(s.d_out);
-  double *d_e = s.d_out + nf, *d_ov = s.d_out + 2 * nf;
-  double *d_b = s.d_out + 3 * nf, *d_H = s.d_out + 15 * nf;
+  // outputs [inliers | e | overlap | b | H]; a count is below zero until it and
+  // the factor's other outputs have arrived
+  int64_t *inl = reinterpret_cast<int64_t *>(s.h_out);
+  double *out_e = s.h_out + nf, *out_ov = s.h_out + 2 * nf;
+  double *out_b = s.h_out + 3 * nf, *out_H = s.h_out + 15 * nf;
+  std::fill(inl, inl + nf, int64_t(-1));
   const hipStream_t st = s.stream;
   const vgicp_opts &o = srv->cfg.opts;
-  hipError_t e = hipMemcpyAsync(s.d_in, s.h_in, in_bytes, hipMemcpyHostToDevice, st);
-  size_t out_values = 0;
+  const uint32_t pose_values = uint32_t(npose) * 12;
+  k_batch_tables<<<unsigned(nf) + (pose_values + 63) / 64, 64, 0, st>>>(
+      s.h_factors, s.h_poses, uint32_t(nf), pose_values, s.d_factors, s.d_poses, s.d_tiles);
+  hipError_t e = hipGetLastError();
   if (kind == VGICP_REQ_OVERLAP) {
-    if (e == hipSuccess) e = launch_overlap(&view, 0, nt, d_poses, st);
+    if (e == hipSuccess) e = launch_overlap(&view, 0, nt, s.d_poses, st);
     if (e == hipSuccess)
-      e = launch_reduce(&view, 0, nf, d_poses, 2, nullptr, nullptr, nullptr, d_inl, d_ov, st);
-    out_values = 3 * size_t(nf);
+      e = launch_reduce(&view, 0, nf, s.d_poses, 2, nullptr, nullptr, nullptr, inl, out_ov, st,
+                        true);
   } else {
     const bool lin = kind == VGICP_REQ_LINEARIZE;
     if (e == hipSuccess)
-      e = launch_linearize(&view, o.accum, o.resid, o.fused, o.fp64_kappa, lin, 0, nt, d_poses,
+      e = launch_linearize(&view, o.accum, o.resid, o.fused, o.fp64_kappa, lin, 0, nt, s.d_poses,
                            nullptr, st);
     if (e == hipSuccess)
-      e = launch_reduce(&view, 0, nf, d_poses, lin ? 0 : 1, d_H, d_b, d_e, d_inl, nullptr, st);
-    out_values = (lin ? kOutPerFactor : 2) * size_t(nf);
-  }
-  if (e == hipSuccess)
-    e = hipMemcpyAsync(s.h_out, s.d_out, out_values * sizeof(double), hipMemcpyDeviceToHost, st);
-  if (e == hipSuccess) {
-    srv->callbacks_outstanding += 1;
-    e = hipLaunchHostFunc(st, on_batch_done, new DoneArgs{srv, si});
-    if (e != hipSuccess) srv->callbacks_outstanding -= 1;
+      e = launch_reduce(&view, 0, nf, s.d_poses, lin ? 0 : 1, out_H, out_b, out_e, inl, nullptr,
+                        st, true);
   }
   if (e != hipSuccess) {
     s.err = e;
@@ -363,35 +385,14 @@ void free_frame(Frame &fr) {
   fr = Frame();
 }
 
-// Scatter a finished batch into its requests.  Called with the lock held;
-// frames whose removal was pending are moved to `to_free` (freed by the caller
-// after it drops the lock: the completion callback takes the lock, so no
-// blocking HIP call may run under it).
+// Ends a batch whose outputs have been taken, or that failed.  Called with the
+// lock held; frames whose removal was pending are moved to `to_free` (freed by the caller
+// after it drops the lock, so that submitters do not wait for the device).
 void retire(vgicp_server srv, Slot &s, std::vector<Frame> &to_free) {
   const bool ok = s.err == hipSuccess;
-  const int64_t nf = s.n_factors;
-  const int64_t *h_inl = reinterpret_cast<const int64_t *>(s.h_out);
-  const double *h_e = s.h_out + nf, *h_ov = s.h_out + 2 * nf;
-  const double *h_b = s.h_out + 3 * nf, *h_H = s.h_out + 15 * nf;
   for (const Chunk &c : s.chunks) {
     Request &r = *c.req;
-    if (ok) {
-      for (int64_t k = 0; k < c.count; ++k) {
-        const int64_t f = c.first + k, p = c.batch_pos + k;
-        if (r.inliers) r.inliers[f] = h_inl[p];
-        if (s.kind == VGICP_REQ_OVERLAP) {
-          if (r.overlap) r.overlap[f] = h_ov[p];
-        } else {
-          if (r.e) r.e[f] = h_e[p];
-          if (s.kind == VGICP_REQ_LINEARIZE) {
-            std::memcpy(r.H + f * 144, h_H + p * 144, 144 * sizeof(double));
-            std::memcpy(r.b + f * 12, h_b + p * 12, 12 * sizeof(double));
-          }
-        }
-      }
-    } else {
-      r.failed = true;
-    }
+    if (!ok) r.failed = true;
     r.remaining -= c.count;
     if (r.remaining == 0 && !r.done) {
       r.done = true;
@@ -413,19 +414,22 @@ void retire(vgicp_server srv, Slot &s, std::vector<Frame> &to_free) {
   s.finished = false;
 }
 
+// How long the worker looks for outputs without a pause before it sleeps
+// between looks, and for how long then.
+constexpr std::chrono::milliseconds kLookFor(2);
+constexpr std::chrono::microseconds kSleepFor(50);
+
 void worker_loop(vgicp_server srv) {
   (void)hipSetDevice(srv->device);
+  auto last_progress = Clock::now();
   std::unique_lock<std::mutex> lk(srv->mu);
   for (;;) {
+    srv->called.store(false, std::memory_order_relaxed);
     bool progressed = false;
     std::vector<Frame> to_free;
     // retire finished batches
     for (Slot &s : srv->slots) {
-      if (!s.busy || !s.finished) continue;
-      if (s.err == hipSuccess) {
-        const hipError_t q = hipStreamQuery(s.stream);
-        if (q != hipSuccess && q != hipErrorNotReady) s.err = q;
-      }
+      if (!s.busy || !(s.finished || take_outputs(s))) continue;
       retire(srv, s, to_free);
       progressed = true;
     }
@@ -445,7 +449,35 @@ void worker_loop(vgicp_server srv) {
     bool any_busy = false;
     for (const Slot &s : srv->slots) any_busy |= s.busy;
     if (srv->stop && srv->pending.empty() && !any_busy) break;
-    if (!progressed) srv->cv.wait(lk);
+    if (progressed) {
+      last_progress = Clock::now();
+      continue;
+    }
+    if (!any_busy) {
+      srv->cv.wait(lk);
+      continue;
+    }
+    if (Clock::now() - last_progress < kLookFor) {
+      lk.unlock();
+      bool arrived = false;
+      for (int look = 0; look < 1000 && !arrived; ++look) {
+        __builtin_ia32_pause();
+        arrived = srv->called.load(std::memory_order_relaxed);
+        for (Slot &s : srv->slots) arrived |= s.busy && (s.finished || take_outputs(s));
+      }
+      lk.lock();
+      continue;
+    }
+    srv->cv.wait_for(lk, kSleepFor);
+    // a batch whose stream has ended, or failed, without its outputs
+    for (Slot &s : srv->slots) {
+      if (!s.busy || s.finished) continue;
+      const hipError_t q = hipStreamQuery(s.stream);
+      (void)hipGetLastError();  // `not ready` is no error of the next launch
+      if (q == hipErrorNotReady || take_outputs(s)) continue;
+      s.err = q != hipSuccess ? q : hipErrorUnknown;
+      s.finished = true;
+    }
   }
 }
 
@@ -511,13 +543,10 @@ int vgicp_server_destroy(vgicp_server srv) {
   {
     std::lock_guard<std::mutex> g(srv->mu);
     srv->stop = true;
+    srv->called.store(true, std::memory_order_relaxed);
   }
   srv->cv.notify_all();
   if (srv->worker.joinable()) srv->worker.join();
-  {
-    std::unique_lock<std::mutex> lk(srv->mu);
-    srv->cv.wait(lk, [&] { return srv->callbacks_outstanding == 0; });
-  }
   (void)hipSetDevice(srv->device);
   for (Slot &s : srv->slots) {
     if (s.stream) (void)hipStreamSynchronize(s.stream);
@@ -744,6 +773,7 @@ int vgicp_server_submit_many(vgicp_server srv, const vgicp_server_request *reqs,
         srv->pending.push_back(batch[q]);
       }
     }
+    srv->called.store(true, std::memory_order_relaxed);
   }
   srv->cv.notify_all();
   return VGICP_OK;

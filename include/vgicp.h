@@ -310,7 +310,9 @@ int vgicp_factorset_time_kernel(vgicp_ctx ctx, vgicp_factorset fs, const double 
                                 double *avg_ms);
 
 /* Grid of the factor set's linearize, evaluate and overlap launches:
- * persist_blocks = 0 runs one workgroup per tile; a positive multiple of 8
+ * persist_blocks = 0 runs one workgroup per tile (linearize and evaluate over
+ * up to half as many tiles again as the device holds workgroups: those walk
+ * the tiles); a positive multiple of 8
  * runs at most that many workgroups, the tiles dealt to the 8 XCDs in eighths
  * of the tile table and walked in order by each XCD's workgroups.  Results
  * are the same bits on either grid.  Forgets replayed rounds (synchronizes

@@ -82,3 +82,22 @@ def test_contribution_counts(vg, ctx, n):
             add(2, k, Hf[:6, 6:] if i < j else Hf[6:, :6])
     for key, r, m in zip(("Hdiag", "bvec", "Hoff"), ref, mag):
         assert np.all(np.abs(got[key].cpu().numpy() - r) <= (4 * n + 8) * 2.0 ** -52 * m), key
+
+
+@pytest.mark.parametrize("tiles", [1024, 1025, 1536, 1537])
+def test_automatic_grid(vg, ctx, tiles):
+    """The automatic grid gives the bits of one block per tile on either side
+    of the counts whose tiles resident blocks walk."""
+    w = make_tiny_workload(seed=730, n_src=256 * 41, n_tgt=900, resolution=0.5)
+    sizes = [41] * (tiles // 41) + [tiles % 41]
+    w.sources = [(w.sources[0][0][:256 * k], w.sources[0][1][:256 * k]) for k in (41, sizes[-1])]
+    w.factors = np.array([(int(k != 41), 0, 0, 1) for k in sizes], np.int32)
+    g = GpuWorkload(vg, ctx, w, tile_points=256)
+    assert g.fs.n_tiles == tiles
+    auto = g.linearize(with_corr=True), g.evaluate(), g.linearize(accum="f32_comp")
+    vg.set_grid(ctx, g.fs, 2048)
+    each = g.linearize(with_corr=True), g.evaluate(), g.linearize(accum="f32_comp")
+    assert auto[0]["inliers"].sum() > 0
+    for a, o in zip(auto, each):
+        for k in a:
+            assert np.array_equal(a[k], o[k]), k

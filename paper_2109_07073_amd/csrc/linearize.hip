@@ -101,6 +101,7 @@ __device__ __forceinline__ void transform_fp32(const float R[9], const float t[3
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x2 __attribute__((ext_vector_type(2)));
 typedef float f32x3 __attribute__((ext_vector_type(3)));
+typedef double f64x2 __attribute__((ext_vector_type(2)));
 
 // ---------------------------------------------------------------- buffer loads
 // Clouds and maps are read through raw buffer resources: a uniform base in
@@ -1694,18 +1695,20 @@ k_reduce(const FactorDesc *__restrict__ factors, int64_t factor_base,
     if (l < 36) Ad[l] = adjoint_entry(T, l);
   };
   if constexpr (WIDE) {
-    __shared__ double2 rows[kReduceRows * kPartialStride / 2];
+    __shared__ f64x2 rows[kReduceRows * kPartialStride / 2];
     const int64_t stride = int64_t(fd.tile_stride) * (kPartialStride / 2);
-    const double2 *__restrict__ part = reinterpret_cast<const double2 *>(partials) +
-                                       int64_t(fd.tile_begin) * (kPartialStride / 2);
+    const f64x2 *__restrict__ part = reinterpret_cast<const f64x2 *>(partials) +
+                                     int64_t(fd.tile_begin) * (kPartialStride / 2);
     const int row = lane >> 4, col = lane & 15;
     int32_t t0 = 0;
     do {  // once for a factor without tiles
-      double2 v[kReduceQuads];
+      // (an array of HIP's double2 stays in scratch memory, so each load was
+      // waited for and stored there before the next)
+      f64x2 v[kReduceQuads];
 #pragma unroll
       for (int q = 0; q < kReduceQuads; ++q) {
         const int32_t t = t0 + q * 16 + row;
-        if (t < n_tiles) v[q] = part[t * stride + col];
+        v[q] = t < n_tiles ? part[t * stride + col] : f64x2{0.0, 0.0};
       }
       if (t0 == 0 && mode == 0 && lane >= kThreads - 64) adjoint(lane - (kThreads - 64));
       if (t0 > 0) __syncthreads();  // the previous rows have been added

@@ -1409,8 +1409,16 @@ __device__ __forceinline__ void linearize_tile(
 // tile (P = the eighth's length) each block runs one tile; a persistent grid
 // (P blocks per XCD resident at once) runs several.  Every tile stages its
 // map's occupancy bits in the block's LDS.
+// Blocks of k_linearize a CU holds: with FP32 sums the registers of four (128 a
+// lane), or of five (96) where a cost's single sum and the residual fit without
+// spills.  Five take 500 factors' cost from 68.1 to 64.9 us and 45 factors' from
+// 15.2 to 14.7.
+template <int ACC, bool LIN, bool R64, int FUSE>
+constexpr int kBlocksPerCu =
+    ACC == VGICP_ACC_F64 ? 1 : LIN || FUSE == kFuseGate || (FUSE == kFuse64 && !R64) ? 4 : 5;
+
 template <int ACC, bool LIN, bool R64, bool CORR, int FUSE>
-__global__ void __launch_bounds__(kBlock, ACC == VGICP_ACC_F64 ? 1 : 4)
+__global__ void __launch_bounds__(kBlock, (kBlocksPerCu<ACC, LIN, R64, FUSE>))
 k_linearize(const FactorDesc *__restrict__ factors, const Tile *__restrict__ tiles,
             int64_t tile_base, int64_t tile_end, int32_t tile_stride,
             const double *__restrict__ poses, const FactorConsts *__restrict__ consts,
@@ -1915,20 +1923,20 @@ static inline unsigned tile_grid(int64_t tiles, int32_t persist_blocks) {
   return std::min(one_per_tile, unsigned(persist_blocks));
 }
 
-// k_linearize's grid when the caller has set none.  Four of its blocks are
-// resident on each of the 256 CUs (k_linearize's launch bounds; two with FP64
-// sums).  A few tiles more than that start when the first ones end, and on a
-// block of their own they also wait for its start; walked by the resident
-// blocks, 1,026 to 1,350 tiles of 768 points take 17.3 to 20.3 us a round
-// instead of 18.5 to 21.3 (cost alone: 14.6 to 17.4 instead of 15.6 to 18.1).
-// From half as many tiles more the second start is hidden by the tiles still
-// running: 1,539 tiles take 22.3 us either way, 1,890 take 25.5 walked and 25.0
-// on blocks of their own.
-constexpr int64_t kResidentBlocks = 4 * 256;
-static inline unsigned linearize_grid(int64_t tiles, int32_t persist_blocks, bool four_per_cu) {
-  if (persist_blocks <= 0 && four_per_cu && tiles > kResidentBlocks &&
-      tiles <= kResidentBlocks + kResidentBlocks / 2)
-    return unsigned(kResidentBlocks);
+// k_linearize's grid when the caller has set none.  A few tiles more than the
+// device holds blocks start when the first ones end, and on blocks of their own
+// they also wait for those to start; walked by the resident blocks (four on each
+// CU to linearize), 1,053 to 1,458 tiles of 768 points take 17.0 to 20.1 us a
+// round instead of 18.3 to 21.3, and their cost alone (five on each CU) for 1,296
+// to 1,728 tiles 15.1 to 17.3 us instead of 15.7 to 18.5.  From half as many tiles
+// more the later start is hidden by the tiles still running: linearizing 1,539
+// tiles takes 21.7 us either way, 1,890 take 25.0 walked and 24.5 on blocks of
+// their own.
+constexpr int kCus = 256;
+static inline unsigned linearize_grid(int64_t tiles, int32_t persist_blocks, int blocks_per_cu) {
+  const int64_t resident = blocks_per_cu * int64_t(kCus);
+  if (persist_blocks <= 0 && blocks_per_cu > 1 && tiles > resident && tiles <= resident * 3 / 2)
+    return unsigned(resident);
   return tile_grid(tiles, persist_blocks);
 }
 
@@ -1937,7 +1945,7 @@ static hipError_t launch_lin(const vgicp_factorset_s *fs, int64_t tb, int64_t te
                              const double *poses, const FactorConsts *consts, double *partials,
                              int32_t *corr, float kappa, hipStream_t st) {
   if (te <= tb) return hipSuccess;
-  const unsigned grid = linearize_grid(te - tb, fs->persist_blocks, ACC != VGICP_ACC_F64);
+  const unsigned grid = linearize_grid(te - tb, fs->persist_blocks, kBlocksPerCu<ACC, LIN, R64, FUSE>);
   if (corr) {
     k_linearize<ACC, LIN, R64, true, FUSE><<<grid, kBlock, 0, st>>>(
         fs->d_factors, fs->d_tiles, tb, te, stride, poses, consts, partials, corr, kappa);

@@ -84,7 +84,7 @@ def test_contribution_counts(vg, ctx, n):
         assert np.all(np.abs(got[key].cpu().numpy() - r) <= (4 * n + 8) * 2.0 ** -52 * m), key
 
 
-@pytest.mark.parametrize("tiles", [1024, 1025, 1536, 1537])
+@pytest.mark.parametrize("tiles", [1024, 1025, 1280, 1281, 1536, 1537, 1920, 1921])
 def test_automatic_grid(vg, ctx, tiles):
     """The automatic grid gives the bits of one block per tile on either side
     of the counts whose tiles resident blocks walk."""

@@ -15,6 +15,8 @@
 
 #include "group.hpp"
 
+#include <cstring>
+
 #include <rocprim/device/device_radix_sort.hpp>
 
 namespace vgicp {
@@ -378,21 +380,18 @@ hipError_t sort_sources(const vgicp_cloud *sources, const std::vector<int32_t> &
   return e;
 }
 
-// Orders the clouds `which` by grouping, as many at once as kOrderWorkspace
-// holds, in ctx's scratch.  redo receives the ones that have to be sorted.
-// Enqueued on ctx's stream and synchronized.
+// Enqueues the grouping of the clouds order.grouped, as many at once as
+// kOrderWorkspace holds, in ctx's scratch on its stream; d_redo's words are set
+// for the ones that have to be sorted.
 hipError_t group_sources(vgicp_ctx ctx, const vgicp_cloud *sources,
-                         const std::vector<int32_t> &which, const std::vector<double> &cell,
-                         const std::vector<SortedSource> &out, unsigned long long *d_bad,
-                         std::vector<int32_t> &redo) {
+                         const std::vector<double> &cell, SourceOrder &order, uint32_t *d_redo) {
   const hipStream_t st = ctx->stream;
+  const std::vector<int32_t> &which = order.grouped;
   const size_t count = which.size();
-  // jobs and flags first, then the batches' workspaces over each other
+  // the jobs first, then the batches' workspaces over each other
   size_t head = 0;
   OrderJob *d_jobs = nullptr;
-  uint32_t *d_redo = nullptr;
   carve_piece<OrderJob>(nullptr, head, &d_jobs, count);
-  carve_piece<uint32_t>(nullptr, head, &d_redo, count);
   std::vector<OrderJob> jobs(count);
   std::vector<size_t> batch;  // first job of each
   size_t most = 0, at = head;
@@ -424,10 +423,9 @@ hipError_t group_sources(vgicp_ctx ctx, const vgicp_cloud *sources,
   place(base);
   head = 0;
   carve_piece(base, head, &d_jobs, count);
-  carve_piece(base, head, &d_redo, count);
   for (size_t k = 0; k < count; ++k) {
     const vgicp_cloud &c = sources[which[k]];
-    const SortedSource &o = out[size_t(which[k])];
+    const SortedSource &o = order.out[size_t(which[k])];
     jobs[k].xyz = c.xyz;
     jobs[k].cov = c.cov;
     jobs[k].xyz_out = const_cast<float *>(o.xyz);
@@ -437,8 +435,10 @@ hipError_t group_sources(vgicp_ctx ctx, const vgicp_cloud *sources,
     jobs[k].inv_cell = float(1.0 / cell[size_t(which[k])]);
     jobs[k].redo = d_redo + k;
   }
-  hipError_t e =
-      hipMemcpyAsync(d_jobs, jobs.data(), count * sizeof(OrderJob), hipMemcpyHostToDevice, st);
+  order.jobs.resize(count * sizeof(OrderJob));
+  std::memcpy(order.jobs.data(), jobs.data(), order.jobs.size());
+  hipError_t e = hipMemcpyAsync(d_jobs, order.jobs.data(), order.jobs.size(),
+                                hipMemcpyHostToDevice, st);
   for (size_t b = 0; b < batch.size() && e == hipSuccess; ++b) {
     const size_t k0 = batch[b], k1 = b + 1 < batch.size() ? batch[b + 1] : count;
     uint32_t nmax = 0, slots = 0;
@@ -452,76 +452,86 @@ hipError_t group_sources(vgicp_ctx ctx, const vgicp_cloud *sources,
     k_order_insert<<<dim3(points, nj), 256, 0, st>>>(d);
     k_order_compact<<<dim3(slots / kCompactSlots, nj), kCompactThreads, 0, st>>>(d);
     k_order_number<<<dim3(kOrderBlocks + points, nj), 256, 0, st>>>(d);
-    k_order_place<<<dim3(points, nj), 256, 0, st>>>(d, d_bad);
+    k_order_place<<<dim3(points, nj), 256, 0, st>>>(d, order.d_bad);
     e = hipGetLastError();
   }
-  std::vector<uint32_t> flags(count);
-  if (e == hipSuccess)
-    e = hipMemcpyAsync(flags.data(), d_redo, count * sizeof(uint32_t), hipMemcpyDeviceToHost, st);
-  const hipError_t se = hipStreamSynchronize(st);
-  if (e == hipSuccess) e = se;
-  if (e != hipSuccess) return e;
-  for (size_t k = 0; k < count; ++k)
-    if (flags[k]) redo.push_back(which[k]);
-  return hipSuccess;
+  return e;
+}
+
+// Gives the copies back after an error, once nothing enqueued uses them.
+hipError_t drop_copies(vgicp_ctx ctx, SourceOrder &order, hipError_t e) {
+  (void)hipStreamSynchronize(ctx->stream);
+  if (order.buffer) (void)hipFree(order.buffer);
+  order.buffer = nullptr;
+  order.out.assign(order.out.size(), SortedSource{});
+  return e;
 }
 
 }  // namespace
 
-hipError_t make_sorted_sources(vgicp_ctx ctx, const vgicp_cloud *sources, int32_t n_sources,
-                               const std::vector<double> &cell, void **buffer,
-                               std::vector<SortedSource> &out, int64_t *nonfinite) {
-  const hipStream_t st = ctx->stream;
-  *buffer = nullptr;
-  if (nonfinite) nonfinite[0] = nonfinite[1] = 0;
-  out.assign(size_t(n_sources), SortedSource{});
+hipError_t begin_sorted_sources(vgicp_ctx ctx, const vgicp_cloud *sources, int32_t n_sources,
+                                const std::vector<double> &cell, SourceOrder &order) {
+  order.out.assign(size_t(n_sources), SortedSource{});
   // layout: per used cloud, covariances [n][6], coordinates [n][3], permutation
-  // [n]; then the two counts of non-finite points
+  // [n]; then the two counts of non-finite points and the grouped clouds' words
   size_t total = 0;
   std::vector<size_t> off(size_t(n_sources), 0);
-  std::vector<int32_t> grouped, sorted;
   for (int32_t s = 0; s < n_sources; ++s) {
     const int64_t n = sources[s].n;
     if (!(cell[size_t(s)] > 0.0) || n <= 0) continue;
     off[size_t(s)] = total;
     total += align256(24 * size_t(n)) + align256(12 * size_t(n)) + align256(4 * size_t(n));
-    (n <= kGroupMaxPoints ? grouped : sorted).push_back(s);
+    (n <= kGroupMaxPoints ? order.grouped : order.sorted).push_back(s);
   }
   if (total == 0) return hipSuccess;
-  hipError_t e = hipMalloc(buffer, total + 2 * sizeof(unsigned long long));
+  const size_t words = 2 * sizeof(unsigned long long) + order.grouped.size() * sizeof(uint32_t);
+  hipError_t e = hipMalloc(&order.buffer, total + words);
   if (e != hipSuccess) {
-    *buffer = nullptr;
+    order.buffer = nullptr;
     return e;
   }
-  char *base = static_cast<char *>(*buffer);
-  for (const auto *list : {&grouped, &sorted})
+  char *base = static_cast<char *>(order.buffer);
+  for (const auto *list : {&order.grouped, &order.sorted})
     for (int32_t s : *list) {
       const size_t n = size_t(sources[s].n);
       char *p = base + off[size_t(s)];
-      out[size_t(s)] = SortedSource{
+      order.out[size_t(s)] = SortedSource{
           reinterpret_cast<float *>(p + align256(24 * n)), reinterpret_cast<float *>(p),
           reinterpret_cast<int32_t *>(p + align256(24 * n) + align256(12 * n))};
     }
-  auto *d_bad = reinterpret_cast<unsigned long long *>(base + total);
-  e = hipMemsetAsync(d_bad, 0, 2 * sizeof(unsigned long long), st);
-  if (e == hipSuccess && !grouped.empty())
-    e = group_sources(ctx, sources, grouped, cell, out, d_bad, sorted);
-  if (e == hipSuccess && !sorted.empty()) e = sort_sources(sources, sorted, cell, out, d_bad, st);
-  unsigned long long bad[2] = {0, 0};
-  if (e == hipSuccess)
-    e = hipMemcpyAsync(bad, d_bad, sizeof(bad), hipMemcpyDeviceToHost, st);
-  const hipError_t se = hipStreamSynchronize(st);
+  order.d_bad = reinterpret_cast<unsigned long long *>(base + total);
+  e = hipMemsetAsync(order.d_bad, 0, words, ctx->stream);
+  if (e == hipSuccess && !order.grouped.empty())
+    e = group_sources(ctx, sources, cell, order, reinterpret_cast<uint32_t *>(order.d_bad + 2));
+  return e == hipSuccess ? e : drop_copies(ctx, order, e);
+}
+
+hipError_t finish_sorted_sources(vgicp_ctx ctx, const vgicp_cloud *sources,
+                                 const std::vector<double> &cell, SourceOrder &order) {
+  const hipStream_t st = ctx->stream;
+  if (!order.buffer) return hipStreamSynchronize(st);
+  // the counts and the grouped clouds' words
+  std::vector<unsigned long long> words(2 + (order.grouped.size() + 1) / 2);
+  const size_t bytes = 2 * sizeof(unsigned long long) + order.grouped.size() * sizeof(uint32_t);
+  hipError_t e = hipMemcpyAsync(words.data(), order.d_bad, bytes, hipMemcpyDeviceToHost, st);
+  hipError_t se = hipStreamSynchronize(st);
   if (e == hipSuccess) e = se;
-  if (e == hipSuccess && nonfinite) {
-    nonfinite[0] = int64_t(bad[0]);
-    nonfinite[1] = int64_t(bad[1]);
+  if (e != hipSuccess) return drop_copies(ctx, order, e);
+  const uint32_t *redo = reinterpret_cast<const uint32_t *>(words.data() + 2);
+  for (size_t k = 0; k < order.grouped.size(); ++k)
+    if (redo[k]) order.sorted.push_back(order.grouped[k]);
+  if (!order.sorted.empty()) {
+    e = sort_sources(sources, order.sorted, cell, order.out, order.d_bad, st);
+    if (e == hipSuccess)
+      e = hipMemcpyAsync(words.data(), order.d_bad, 2 * sizeof(unsigned long long),
+                         hipMemcpyDeviceToHost, st);
+    se = hipStreamSynchronize(st);
+    if (e == hipSuccess) e = se;
+    if (e != hipSuccess) return drop_copies(ctx, order, e);
   }
-  if (e != hipSuccess) {
-    (void)hipFree(*buffer);
-    *buffer = nullptr;
-    out.assign(size_t(n_sources), SortedSource{});
-  }
-  return e;
+  order.nonfinite[0] = int64_t(words[0]);
+  order.nonfinite[1] = int64_t(words[1]);
+  return hipSuccess;
 }
 
 }  // namespace vgicp

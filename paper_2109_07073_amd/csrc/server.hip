@@ -613,20 +613,21 @@ int vgicp_server_add_frame(vgicp_server srv, const float *h_xyz, const float *h_
     // Requests have no per-point outputs, so the permutation is not kept.
     if (rc == VGICP_OK && n > 0) {
       const std::vector<double> cell{resolution};
-      std::vector<SortedSource> ss;
-      void *buf = nullptr;
+      SourceOrder order;
       hipStream_t st = srv->ingest.stream;
-      hipError_t se = make_sorted_sources(&srv->ingest, &c, 1, cell, &buf, ss);
-      if (se == hipSuccess && buf) {
-        se = hipMemcpyAsync(fr.cloud, ss[0].xyz, size_t(3 * n) * sizeof(float),
+      hipError_t se = begin_sorted_sources(&srv->ingest, &c, 1, cell, order);
+      if (se == hipSuccess) se = finish_sorted_sources(&srv->ingest, &c, cell, order);
+      if (se == hipSuccess && order.buffer) {
+        const SortedSource &ss = order.out[0];
+        se = hipMemcpyAsync(fr.cloud, ss.xyz, size_t(3 * n) * sizeof(float),
                             hipMemcpyDeviceToDevice, st);
         if (se == hipSuccess)
-          se = hipMemcpyAsync(fr.cloud + fr.cov_offset, ss[0].cov, size_t(6 * n) * sizeof(float),
+          se = hipMemcpyAsync(fr.cloud + fr.cov_offset, ss.cov, size_t(6 * n) * sizeof(float),
                               hipMemcpyDeviceToDevice, st);
         const hipError_t ye = hipStreamSynchronize(st);
         if (se == hipSuccess) se = ye;
       }
-      if (buf) (void)hipFree(buf);
+      if (order.buffer) (void)hipFree(order.buffer);
       if (se != hipSuccess) {
         vgicp_map_free(fr.map);
         fr.map = nullptr;

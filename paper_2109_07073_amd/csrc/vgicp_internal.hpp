@@ -237,13 +237,27 @@ struct SortedSource {
 };
 
 // Ordered copies of the clouds s with cell[s] > 0 and n > 0, in one device
-// allocation returned in *buffer (NULL when there is none); out[s] points into
-// it.  nonfinite (may be NULL) receives the number of copied points with a
-// non-finite coordinate and with a non-finite covariance entry.  Works in
-// ctx's scratch, enqueued on its stream and synchronized before returning.
-hipError_t make_sorted_sources(vgicp_ctx ctx, const vgicp_cloud *sources, int32_t n_sources,
-                               const std::vector<double> &cell, void **buffer,
-                               std::vector<SortedSource> &out, int64_t *nonfinite = nullptr);
+// allocation `buffer` (NULL when there is none); out[s] points into it.
+// begin_sorted_sources enqueues the work on ctx's stream, in its scratch, and
+// sets buffer and out; finish_sorted_sources waits for it (and whatever else was
+// enqueued), makes the copies that have to be sorted, and sets nonfinite to the
+// number of copied points with a non-finite coordinate and with a non-finite
+// covariance entry.  On an error of either, buffer is NULL again.
+struct SourceOrder {
+  void *buffer = nullptr;
+  std::vector<SortedSource> out;
+  int64_t nonfinite[2] = {0, 0};
+  // between the two
+  std::vector<int32_t> grouped, sorted;  // clouds to group, and to sort
+  std::vector<unsigned char> jobs;       // the grouped ones' table on its way to the device
+  // device, behind the copies: the two counts, then a word per grouped cloud
+  // that is set when it has to be sorted
+  unsigned long long *d_bad = nullptr;
+};
+hipError_t begin_sorted_sources(vgicp_ctx ctx, const vgicp_cloud *sources, int32_t n_sources,
+                                const std::vector<double> &cell, SourceOrder &order);
+hipError_t finish_sorted_sources(vgicp_ctx ctx, const vgicp_cloud *sources,
+                                 const std::vector<double> &cell, SourceOrder &order);
 
 // Replace the source copies of fs by per-factor copies with each factor's
 // points in the order of the target voxels they fall in at `poses` (device)
@@ -394,11 +408,15 @@ struct vgicp_factorset_s {
   int32_t tile_points = 0;
   // Blocks of a persistent grid (a multiple of 8), 0 for one block per tile.
   int32_t persist_blocks = 0;
-  vgicp::FactorDesc *d_factors = nullptr;  // device
+  // device: one allocation for the tables made at creation (descriptors, tiles
+  // and the assembly's lists)
+  void *d_tables = nullptr;
+  vgicp::FactorDesc *d_factors = nullptr;  // device, in d_tables
   // device [n_factors] relative-pose constants, rewritten by every round over
   // the whole tile table before its linearize launch (kFactorConstsBytes each)
   void *d_consts = nullptr;
-  vgicp::Tile *d_tiles = nullptr;          // device
+  vgicp::Tile *d_tiles = nullptr;          // device, in d_tables
+  bool own_tiles = false;                  // unless they have outgrown it
   double *d_partials = nullptr;            // device [n_tiles][kPartialStride]
   // Pair-form tile partials, [pair_capacity][kPairStride], allocated at the
   // first pair-form call.

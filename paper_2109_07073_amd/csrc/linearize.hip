@@ -19,6 +19,7 @@
 // which the reduce kernel applies once per factor in FP64.
 
 #include <algorithm>
+#include <type_traits>
 
 #include "vgicp_internal.hpp"
 
@@ -881,7 +882,14 @@ __device__ __forceinline__ bool add_pair_terms(SumsT &acc, const FactorConsts &k
                                                const float S[6], uint32_t &nwide) {
 #pragma clang fp contract(off)
 #define FMA __builtin_fmaf
-  const float *R = k.R;
+  // The mixed sums with FP64 covariances have the fewest registers left: rounded
+  // from R64 at each hit, and with the constants computed in every tile (see
+  // linearize_tile), R leaves 8 spills in the hit loop instead of 34.
+  constexpr bool kRound =
+      FUSE == kFuse64 && std::is_same_v<SumsT, Sums<VGICP_ACC_MIXED, kNumPairSums>>;
+  float R[9];
+#pragma unroll
+  for (int i = 0; i < 9; ++i) R[i] = kRound ? float(k.R64[i]) : k.R[i];
   // F = (R^T)^T C (R^T) + C' with the transposed rotation
   const float RT[9] = {R[0], R[3], R[6], R[1], R[4], R[7], R[2], R[5], R[8]};
   const double RT64[9] = {k.R64[0], k.R64[3], k.R64[6], k.R64[1], k.R64[4],
@@ -1253,8 +1261,9 @@ __device__ __forceinline__ void linearize_tile(
   // the relative pose (from the round's table when there is one) while the
   // loads are in flight.  The gated variant always computes it: compiled with
   // the table's branch it ran 13 % slower on the full-size precision workload.
+  // So does the pair form's mixed variant, for its spills.
   FactorConsts k;
-  if constexpr (FUSE == kFuseGate)
+  if constexpr (FUSE == kFuseGate || (PAIR && ACC == VGICP_ACC_MIXED && FUSE == kFuse64))
     k = factor_consts(fd, poses);
   else
     k = consts ? consts[td.factor] : factor_consts(fd, poses);

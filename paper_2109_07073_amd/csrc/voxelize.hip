@@ -206,10 +206,10 @@ k_build_payload(const float *__restrict__ xyz, const float *__restrict__ cov, in
 //            ordinals of its voxels; the table's empty records;
 //   records  per brick: its record.
 // A call on 20,011 returns takes 46 us (180 us by sorting), on a merged submap
-// of 320,000 points 98 us (488 us; 102 us with four other bricks in a lane's
-// flight while numbering and each brick's own loads one after the other).  Its
-// insert takes 31 us of them, bound by 142,000 atomics.  Beyond kGroupMaxPoints the counters'
-// share shrinks and the sort is bound by its passes, so it stays.
+// of 320,000 points 97 us (476 us; 102 us with four other bricks in a lane's
+// flight while numbering and each brick's own loads one after the other).  The
+// insert takes 31 us of those, bound by 142,000 atomics.  Beyond kGroupMaxPoints
+// the counters' share shrinks and the sort is bound by its passes, so it stays.
 constexpr uint32_t kNumberBlocks = 512;
 constexpr uint32_t kNumberBricks = 4;  // bricks a wave numbers at once
 constexpr uint32_t kNumberLoads = 8;   // other bricks a lane has in flight

@@ -1767,6 +1767,10 @@ k_reduce(const FactorDesc *__restrict__ factors, int64_t factor_base,
         __hip_atomic_store(&inl[f], count, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
       return;
     }
+    // In the wide variant every wave waits for its own stores of H and b: the
+    // barrier is compiled without a wait for stores (a workgroup's waves share
+    // their L1), and the release below waits for the first wave's only.
+    if constexpr (WIDE) __threadfence_system();
     __syncthreads();
     if (lane == 0)
       __hip_atomic_store(&inl[f], count, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);

@@ -175,7 +175,10 @@ const char *vgicp_last_error(vgicp_ctx ctx);
  * Errors: EINVAL (out NULL, device out of range), EHIP. */
 int vgicp_ctx_create(int device, void *hip_stream, vgicp_ctx *out);
 
-/* Change the stream later calls enqueue on.  Errors: EINVAL. */
+/* Change the stream later calls enqueue on.  The context's own workspace may
+ * still be in use on the old one: the library orders its next use after that.
+ * The caller orders what it passes itself (a map or cloud made on the old
+ * stream and used on the new one).  Errors: EINVAL. */
 int vgicp_ctx_set_stream(vgicp_ctx ctx, void *hip_stream);
 
 /* Wait for the context's stream.  Errors: EINVAL, EHIP. */

@@ -38,6 +38,7 @@ struct GroupHeader {
   uint32_t max_count;  // points of the fullest of them (0 without one),
   uint32_t heavy_at;   // and how many of them are listed
   uint32_t err;
+  uint32_t done;  // blocks of the last kernel that have read the workspace
 };
 
 struct Group {
@@ -115,7 +116,7 @@ __device__ __forceinline__ void group_clear(const Group &g, uint32_t block) {
   const uint32_t i = block * 256 + threadIdx.x, slots = 1u << g.log2slots;  // 16 bytes each
   if (i < slots * 16) reinterpret_cast<uint4 *>(g.count)[i] = make_uint4(0, 0, 0, 0);
   if (i < slots) g.keys[i] = kEmptyKey;
-  if (i == 0) *g.hdr = GroupHeader{0, 0, 0, 0, 0};
+  if (i == 0) *g.hdr = GroupHeader{0, 0, 0, 0, 0, 0};
 }
 
 // Point i of n.  key(i, brick, cell) sets the point's brick key and its cell in

@@ -416,6 +416,8 @@ hipError_t group_sources(vgicp_ctx ctx, const vgicp_cloud *sources,
     most = std::max(most, at);
   };
   place(nullptr);
+  const hipError_t claimed = claim_scratch(ctx);
+  if (claimed != hipSuccess) return claimed;
   std::string msg;
   const int rc = ensure_scratch(ctx, most, msg);
   if (rc != VGICP_OK) return rc == VGICP_ENOMEM ? hipErrorOutOfMemory : hipErrorUnknown;

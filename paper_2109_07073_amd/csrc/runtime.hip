@@ -260,6 +260,7 @@ int vgicp_ctx_create(int device, void *hip_stream, vgicp_ctx *out) {
 int vgicp_ctx_set_stream(vgicp_ctx ctx, void *hip_stream) {
   if (!ctx) return fail(nullptr, VGICP_EINVAL, "vgicp_ctx_set_stream: ctx is NULL");
   ctx->stream = static_cast<hipStream_t>(hip_stream);
+  ctx->stream_set = true;
   return VGICP_OK;
 }
 

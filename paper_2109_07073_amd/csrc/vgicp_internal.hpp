@@ -298,6 +298,10 @@ constexpr int kPairStride = 96;
 constexpr uint32_t kErrNonFinite = 1u;
 constexpr uint32_t kErrRange = 2u;
 
+// Words of a context's pinned host memory: two readbacks of the sorted
+// construction, the counts of the grouped one, and the scratch's last use.
+constexpr int kCountsWord = 4, kScratchWord = 12;
+
 // Waits until arrived() is true, which a kernel on st makes it by writing to
 // pinned memory: for a while by looking, which saves the runtime's wake-up,
 // then (a stream with much work before it) by synchronizing st.  Returns
@@ -311,6 +315,10 @@ hipError_t wait_for_host_words(hipStream_t st, Arrived arrived) {
   const hipError_t e = hipStreamSynchronize(st);
   return e != hipSuccess ? e : arrived() ? hipSuccess : hipErrorUnknown;
 }
+
+// Waits for the work in the scratch that a call on another stream has left
+// behind.  Before every use of the scratch.
+hipError_t claim_scratch(vgicp_ctx ctx);
 
 // Grows ctx's scratch to at least `bytes` (synchronizing its stream when it
 // replaces the old one).  Returns a status and sets msg on failure.
@@ -341,11 +349,21 @@ struct vgicp_context_s {
   int device = 0;
   hipStream_t stream = nullptr;
   std::string last_error;
-  // Growable scratch for voxelization.
+  // Growable scratch for voxelization and for ordering a factor set's clouds.
   void *scratch = nullptr;
   size_t scratch_bytes = 0;
+  // A voxelization returns while its last kernels still read the scratch; the
+  // last of them writes scratch_seq to the word kScratchWord of host_pinned.
+  // Whether that is pending, and whether the stream has been set since the
+  // scratch was last claimed.  (A word rather than the old stream, which the
+  // caller may have destroyed by then, or an event, whose record makes a
+  // voxelization of 20,011 points and its export take 81 us instead of 47.)
+  uint32_t scratch_seq = 0;
+  bool scratch_pending = false;
+  bool stream_set = false;
   uint32_t *err_word = nullptr;       // device
-  uint32_t *host_pinned = nullptr;    // pinned host words (64 bytes) for small readbacks
+  // pinned host words (64 bytes) for small readbacks: see kCountsWord
+  uint32_t *host_pinned = nullptr;
   uint32_t group_seq = 0;             // voxelizations whose counts the host has asked for
   int cu_count = 0;
   // Growable workspace of the keyframe calls (vgicp_connect,

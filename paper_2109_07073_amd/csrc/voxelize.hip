@@ -555,10 +555,24 @@ k_group_finish(VoxelGroup g, uint32_t n_bricks, uint32_t n_voxels, uint32_t n_he
 
 __global__ void __launch_bounds__(256)
 k_group_records(VoxelGroup g, uint32_t n_bricks, BrickRecord *__restrict__ bricks, uint32_t log2cap,
-                uint32_t *__restrict__ occ, uint32_t occ_mask) {
-  const uint32_t s = blockIdx.x * 256 + threadIdx.x;
-  if (s < n_bricks)
-    insert_record(g.skey[s], g.smask[s], g.sbase[s], bricks, log2cap, occ, occ_mask);
+                uint32_t *__restrict__ occ, uint32_t occ_mask, uint32_t *host, uint32_t seq) {
+  const uint32_t s = blockIdx.x * 256 + threadIdx.x, at = min(s, n_bricks - 1);
+  const uint64_t key = g.skey[at], mask = g.smask[at];
+  const uint32_t base = g.sbase[at];
+  // The last block to have read the workspace says so.  (Every wave has its
+  // values before the barrier; nothing written is to be seen with the word, so
+  // it needs no release.)
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  __syncthreads();
+  if (threadIdx.x == 0 && atomicAdd(&g.hdr->done, 1u) == gridDim.x - 1)
+    __hip_atomic_store(host, seq, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+  if (s < n_bricks) insert_record(key, mask, base, bricks, log2cap, occ, occ_mask);
+}
+
+// The same after a sorted construction, whose last kernel has too many blocks to
+// count (a launch is a hundredth of its time).
+__global__ void k_write_word(uint32_t *host, uint32_t seq) {
+  __hip_atomic_store(host, seq, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
 __global__ void __launch_bounds__(256)
@@ -670,6 +684,38 @@ int voxelize_impl(vgicp_ctx ctx, const vgicp_cloud *cloud, double resolution, vg
 
 namespace vgicp {
 
+hipError_t claim_scratch(vgicp_ctx ctx) {
+  if (!ctx->stream_set) return hipSuccess;
+  if (ctx->scratch_pending) {
+    const uint32_t *word = ctx->host_pinned + kScratchWord;
+    auto done = [&] { return __atomic_load_n(word, __ATOMIC_ACQUIRE) == ctx->scratch_seq; };
+    for (int spin = 0; spin < 20000 && !done(); ++spin) __builtin_ia32_pause();
+    if (!done()) {
+      const hipError_t e = hipDeviceSynchronize();
+      if (e != hipSuccess) return e;
+    }
+    ctx->scratch_pending = false;
+  }
+  ctx->stream_set = false;
+  return hipSuccess;
+}
+
+// A call's use of the scratch: it ends with the kernel that writes the word, or,
+// where the call returns before that kernel is enqueued, with the stream's work.
+struct ScratchUse {
+  vgicp_ctx ctx;
+  const bool any;  // an empty cloud uses none
+  bool word_follows = false;
+  ScratchUse(vgicp_ctx c, bool used) : ctx(c), any(used) {
+    if (any) __atomic_store_n(ctx->host_pinned + kScratchWord, ~++ctx->scratch_seq, __ATOMIC_RELAXED);
+  }
+  ~ScratchUse() {
+    if (!any) return;
+    if (!word_follows) (void)hipStreamSynchronize(ctx->stream);
+    ctx->scratch_pending = word_follows;
+  }
+};
+
 int ensure_scratch(vgicp_ctx ctx, size_t bytes, std::string &msg) {
   if (ctx->scratch_bytes >= bytes) return VGICP_OK;
   if (ctx->scratch) {
@@ -700,22 +746,18 @@ static size_t carve_voxel_group(char *base, size_t n, VoxelGroup *g) {
 }
 
 // Groups the cloud's points (the launches up to `number`) and waits for the
-// counts.  *taken is false when the cloud has to be sorted instead.
-static int group_points(vgicp_ctx ctx, const vgicp_cloud *cloud, float s, VoxelGroup *g,
-                        GroupCounts *counts, bool *taken, std::string &msg) {
+// counts.  *taken is false when the cloud has to be sorted instead.  pinned_dev
+// is the device's address of ctx's pinned words.
+static int group_points(vgicp_ctx ctx, const vgicp_cloud *cloud, float s, uint32_t *pinned_dev,
+                        VoxelGroup *g, GroupCounts *counts, bool *taken, std::string &msg) {
   const hipStream_t st = ctx->stream;
   const uint32_t n = uint32_t(cloud->n);
   const int rc = ensure_scratch(ctx, carve_voxel_group(nullptr, n, g), msg);
   if (rc != VGICP_OK) return rc;
   carve_voxel_group(static_cast<char *>(ctx->scratch), n, g);
   const uint32_t slots = 1u << g->log2slots;
-  // the counts follow the two words of the sorted construction
-  constexpr int kCountsWord = 4;
   auto *host = reinterpret_cast<GroupCounts *>(ctx->host_pinned + kCountsWord);
-  void *pinned_dev = nullptr;
-  HIP_TRY(hipHostGetDevicePointer(&pinned_dev, ctx->host_pinned, 0));
-  auto *host_dev =
-      reinterpret_cast<GroupCounts *>(static_cast<uint32_t *>(pinned_dev) + kCountsWord);
+  auto *host_dev = reinterpret_cast<GroupCounts *>(pinned_dev + kCountsWord);
   // the words may be new to this context and hold another one's counts
   const uint32_t seq = ++ctx->group_seq;
   __atomic_store_n(&host->seq, ~seq, __ATOMIC_RELAXED);
@@ -757,8 +799,13 @@ int voxelize_impl(vgicp_ctx ctx, const vgicp_cloud *cloud, double resolution, vg
   VoxelGroup group{};
   GroupCounts counts{};
   bool grouped = false;
+  void *pinned = nullptr;
+  HIP_TRY(hipHostGetDevicePointer(&pinned, ctx->host_pinned, 0));
+  uint32_t *const pinned_dev = static_cast<uint32_t *>(pinned);
+  if (n > 0) HIP_TRY(claim_scratch(ctx));
+  ScratchUse use(ctx, n > 0);
   if (n > 0 && n <= kGroupMaxPoints) {
-    int rc = group_points(ctx, cloud, s, &group, &counts, &grouped, msg);
+    int rc = group_points(ctx, cloud, s, pinned_dev, &group, &counts, &grouped, msg);
     if (rc == VGICP_OK) rc = point_error(counts.err, msg);
     if (rc != VGICP_OK) return rc;
     if (grouped) {
@@ -899,8 +946,8 @@ int voxelize_impl(vgicp_ctx ctx, const vgicp_cloud *cloud, double resolution, vg
                      finish_lds(counts.max_count), st>>>(
         group, nb, nv, counts.n_heavy, fill, cloud->xyz, cloud->cov, uint32_t(n), m->bricks, cap,
         m->occ, obits / 32, m->stats, m->info);
-    k_group_records<<<grid_for(nb), 256, 0, st>>>(group, nb, m->bricks, log2cap, m->occ,
-                                                  obits - 1);
+    k_group_records<<<grid_for(nb), 256, 0, st>>>(group, nb, m->bricks, log2cap, m->occ, obits - 1,
+                                                  pinned_dev + kScratchWord, ctx->scratch_seq);
   } else {
     k_fill_empty<<<fill, 256, 0, st>>>(m->bricks, cap, m->occ, obits / 32);
   }
@@ -912,6 +959,7 @@ int voxelize_impl(vgicp_ctx ctx, const vgicp_cloud *cloud, double resolution, vg
                                                         sc.seg, vord_out, vkey, n_voxels,
                                                         m->stats, m->info);
   }
+  if (!grouped && n > 0) k_write_word<<<1, 1, 0, st>>>(pinned_dev + kScratchWord, ctx->scratch_seq);
   e = hipGetLastError();
   if (e != hipSuccess) {
     (void)hipFree(m->buffer);
@@ -919,6 +967,7 @@ int voxelize_impl(vgicp_ctx ctx, const vgicp_cloud *cloud, double resolution, vg
     msg = std::string("vgicp_voxelize: kernel launch: ") + hipGetErrorString(e);
     return VGICP_EHIP;
   }
+  use.word_follows = true;
   *out = m;
   return VGICP_OK;
 }

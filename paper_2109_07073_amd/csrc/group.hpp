@@ -3,8 +3,9 @@
 // Points are counted into an open-addressed table of 64 counters per brick, so
 // nothing of the cloud's size is sorted; only the bricks are ordered, by
 // counting, for each, the ones before it.  Bound by the latency of dependent
-// launches, atomics and gathers (a scan moves about a megabyte), so the steps
-// are few and each keeps many loads in flight:
+// launches, atomics and gathers, not by the bytes (for a scan of 20,000 points
+// 4 MB of counters are cleared and about 2 MB moved), so the steps are few and
+// each keeps many loads in flight:
 //   clear    the counters and slots of the table;
 //   insert   per point: its brick's slot, its arrival number in its cell;
 //   compact  per 512 slots: a list of the occupied ones, and where each
@@ -18,12 +19,15 @@
 
 namespace vgicp {
 
+// The largest grouped cloud.  (Voxels of 2^20 street points: 160 us grouped and
+// 680 sorted at 0.5 m, 227 and 500 at 0.25 m; the totals below hold 2^21 - 1.)
 constexpr int64_t kGroupMaxPoints = int64_t(1) << 20;
 constexpr uint32_t kGroupMaxSlots = 1u << 15;  // 8 MB of counters
 constexpr uint32_t kGroupProbes = 64;          // slots a point tries
 constexpr uint32_t kLightMax = 64;             // points of a cell a wave orders
-constexpr uint32_t kHeavyMax = 4096;           // points of a cell at most
-constexpr uint32_t kErrFull = 4u;              // error bit: a brick found no slot
+// Error bit: a brick found no slot or a cell has too many points, so the cloud
+// has to be sorted.  Whatever follows in the chain then does nothing.
+constexpr uint32_t kErrFull = 4u;
 constexpr uint32_t kNoCell = 0xffffffffu;
 
 // Totals of the listed bricks in one word: points in the low 21 bits, cells in
@@ -120,13 +124,15 @@ __device__ __forceinline__ void group_clear(const Group &g, uint32_t block) {
 }
 
 // Point i of n.  key(i, brick, cell) sets the point's brick key and its cell in
-// the brick and returns the error bits of a point that is refused.
+// the brick and returns the error bits of a point that is refused.  A brick
+// tries `probes` slots and a cell takes `most` points.
 // Consecutive points of a scan often fall in one cell (the near rings put
 // hundreds there), so a wave's runs of equal keys look their brick up once and
 // take their arrival numbers with one atomic (320,000 points: 60 us with an
 // atomic each, 28 us by runs).
 template <typename Key>
-__device__ __forceinline__ void group_insert(const Group &g, uint32_t i, uint32_t n, Key key) {
+__device__ __forceinline__ void group_point(const Group &g, uint32_t i, uint32_t n, uint32_t probes,
+                                            uint32_t most, Key key) {
   const uint32_t lane = threadIdx.x & 63;
   uint64_t brick = 0;
   uint32_t cell = 0;
@@ -145,7 +151,7 @@ __device__ __forceinline__ void group_insert(const Group &g, uint32_t i, uint32_
     const uint32_t smask = (1u << g.log2slots) - 1u;
     uint32_t h = uint32_t((brick * 0x9E3779B97F4A7C15ull) >> (64 - g.log2slots));
     bad = kErrFull;
-    for (uint32_t p = 0; p < kGroupProbes; ++p) {
+    for (uint32_t p = 0; p < probes; ++p) {
       // a slot's key never changes once set, and a stale empty one only sends
       // the point to the exchange, so a cached one serves (2 us of 320,000
       // points' 35)
@@ -164,14 +170,60 @@ __device__ __forceinline__ void group_insert(const Group &g, uint32_t i, uint32_
     if (!bad) {
       code = (h << 6) | cell;
       arrival = atomicAdd(&g.count[code], run);
+      if (arrival + run > most) bad = kErrFull;
     }
   }
-  if (bad) atomicOr(&g.hdr->err, bad);
+  const uint64_t refused = __ballot(bad != 0);
+  if (refused) {
+    uint32_t bits = 0;
+#pragma unroll
+    for (uint32_t b = 1; b <= kErrFull; b <<= 1) bits |= __ballot((bad & b) != 0) ? b : 0u;
+    if (lane == uint32_t(__ffsll((unsigned long long)refused)) - 1u) atomicOr(&g.hdr->err, bits);
+  }
   code = __shfl(code, int(head));
   arrival = __shfl(arrival, int(head)) + (lane - head);
   if (i < n) {
     g.code[i] = code;
     g.arrival[i] = arrival;
+  }
+}
+
+// Whether a kernel of the chain goes on; the insert's waves may set it meanwhile.
+__device__ __forceinline__ bool group_full(const Group &g) {
+  const uint32_t err = __hip_atomic_load(&g.hdr->err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  return __builtin_amdgcn_readfirstlane(err) & kErrFull;
+}
+
+// The points of one wave of insert_grid's blocks of 256 threads.
+// Of a large cloud a wave takes several groups of 64 points one after the
+// other, so that the first of all waves are a sample of the cloud, and stricter
+// limits for it stop most clouds that have to be sorted before the rest of their
+// points fill the table.  (All at once, an insert ran to its end before anything
+// could be known of it: 105 us for 320,000 points in 60,600 bricks, now 71, and
+// 349 for 2^20 in 127,900, now 103.)  Fewer waves are enough to keep the atomics
+// busy: at 320,000 points a voxelization takes 83 us in 4 groups, 89 in 8 and 93
+// in one, at 2^20 160 in 8 and in 4, 180 in one.  Up to 2^17 points one group
+// each leaves no CU without waves.
+constexpr uint32_t kSampleProbes = 24;  // a third of the table
+
+__host__ __device__ inline uint32_t insert_runs(uint32_t n) {
+  return n <= (1u << 17) ? 1u : n <= (1u << 19) ? 4u : 8u;
+}
+__host__ __device__ inline uint32_t insert_grid(uint32_t n) {
+  const uint32_t points = 256 * insert_runs(n);
+  return (n + points - 1) / points;
+}
+
+template <typename Key>
+__device__ __forceinline__ void group_insert(const Group &g, uint32_t block, uint32_t n,
+                                             uint32_t most, Key key) {
+  const uint32_t runs = insert_runs(n);
+  const uint32_t first = (block * 256 + (threadIdx.x & ~63u)) * runs + (threadIdx.x & 63u);
+  if (runs == 1) return group_point(g, first, n, kGroupProbes, most, key);
+  group_point(g, first, n, kSampleProbes, 2 * most / runs, key);
+  for (uint32_t r = 1; r < runs; ++r) {
+    if (group_full(g)) return;
+    group_point(g, first + r * 64, n, kGroupProbes, most, key);
   }
 }
 
@@ -192,7 +244,9 @@ __device__ __forceinline__ void group_compact(const Group &g, uint32_t block) {
   __shared__ uint64_t at;
   const uint32_t tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const uint32_t slot = block * kCompactSlots + tid;
+  const uint32_t err = g.hdr->err;
   const bool used = tid < kCompactSlots && g.keys[slot] != kEmptyKey;
+  if (err & kErrFull) return;  // no brick is listed then
   const uint64_t m = __ballot(used);
   if (lane == 0 && wave < kSlotWaves) slot_n[wave] = uint32_t(__popcll(m));
   if (tid == 0) cell_n = heavy_n = most_n = 0;
@@ -263,8 +317,8 @@ __device__ __forceinline__ void group_compact(const Group &g, uint32_t block) {
 // Point i of n, after compact.
 __device__ __forceinline__ void group_scatter(const Group &g, uint32_t i, uint32_t n) {
   if (i >= n) return;
-  const uint32_t code = g.code[i];
-  if (code != kNoCell) g.list[g.first[code >> 6] + g.rel[code] + g.arrival[i]] = i;
+  const uint32_t err = g.hdr->err, code = g.code[i];  // the code is not set if full
+  if (!(err & kErrFull) && code != kNoCell) g.list[g.first[code >> 6] + g.rel[code] + g.arrival[i]] = i;
 }
 
 }  // namespace vgicp

@@ -105,7 +105,13 @@ k_gather_points(const float *__restrict__ xyz, const float *__restrict__ cov, ui
 // the bricks before each brick, and place puts every point behind the points
 // of earlier cells and the earlier points of its own.  Five launches order as
 // many clouds as the workspace holds; sorting them one by one took twelve
-// launches a cloud (450 us of a 10-scan submap's factor set).
+// launches a cloud (450 us of a 10-scan submap's factor set).  A wave's points
+// read the list of their cell once each, so a cell costs the square of its
+// points: beyond kOrderCellMax a cloud is sorted (a set over one cloud of
+// 320,000 points, 1,072 in its fullest cell: 350 us grouped, 350 sorted; 4,011:
+// 680 and 360; of 2^20, 1,527: 1,000 and 425).  Numbering squares the bricks, so
+// a cloud that is alone gets all of kOrderBlocks (320,000 points in 18,000
+// bricks: 270 us, 545 with 64).
 struct OrderJob {
   Group g;
   uint32_t *base;  // [slots] points in earlier bricks
@@ -119,9 +125,24 @@ struct OrderJob {
 
 constexpr size_t kOrderWorkspace = size_t(192) << 20;  // bytes of grouped clouds at once
 constexpr uint32_t kOrderJobs = 256;                   // and clouds
-constexpr uint32_t kOrderBlocks = 64;                  // blocks that number a cloud's bricks
+constexpr uint32_t kOrderBlocks = 512;                 // blocks that number bricks,
+constexpr uint32_t kOrderCloudBlocks = 64;             // of each cloud at least these
+constexpr uint32_t kOrderCellMax = 1024;               // points of a cell at most
 constexpr uint32_t kOrderBricks = 4;                   // bricks a wave numbers at once
 constexpr uint32_t kOrderLoads = 8;                    // other bricks a lane has in flight
+
+// The brick and cell of a point, as group.hpp asks for them.
+struct CellOfPoint {
+  const float *xyz;
+  uint32_t n;
+  float inv_cell;
+  __device__ uint32_t operator()(uint32_t i, uint64_t &brick, uint32_t &cell) const {
+    const uint64_t k = morton_key(xyz, n, i, inv_cell);
+    brick = k >> 6;
+    cell = uint32_t(k) & 63u;
+    return 0u;
+  }
+};
 
 __global__ void __launch_bounds__(256)
 k_order_clear(const OrderJob *__restrict__ jobs) {
@@ -131,17 +152,9 @@ k_order_clear(const OrderJob *__restrict__ jobs) {
 __global__ void __launch_bounds__(256)
 k_order_insert(const OrderJob *__restrict__ jobs) {
   const OrderJob &job = jobs[blockIdx.y];
-  const uint32_t n = job.n;
-  if (blockIdx.x * 256 >= n) return;
-  const float *xyz = job.xyz;
-  const float inv = job.inv_cell;
-  group_insert(job.g, blockIdx.x * 256 + threadIdx.x, n,
-               [&](uint32_t i, uint64_t &brick, uint32_t &cell) {
-                 const uint64_t k = morton_key(xyz, n, i, inv);
-                 brick = k >> 6;
-                 cell = uint32_t(k) & 63u;
-                 return 0u;
-               });
+  if (blockIdx.x >= insert_grid(job.n)) return;
+  group_insert(job.g, blockIdx.x, job.n, kOrderCellMax,
+               CellOfPoint{job.xyz, job.n, job.inv_cell});
 }
 
 __global__ void __launch_bounds__(kCompactThreads)
@@ -150,20 +163,19 @@ k_order_compact(const OrderJob *__restrict__ jobs) {
   if (blockIdx.x * kCompactSlots < (1u << g.log2slots)) group_compact(g, blockIdx.x);
 }
 
-// Blocks [0, kOrderBlocks): bricks; the others: points.
+// Blocks [0, number_blocks): bricks; the others: points.
 __global__ void __launch_bounds__(256)
-k_order_number(const OrderJob *__restrict__ jobs) {
+k_order_number(const OrderJob *__restrict__ jobs, uint32_t number_blocks) {
   const OrderJob &job = jobs[blockIdx.y];
   const Group &g = job.g;
-  if (blockIdx.x >= kOrderBlocks) {
-    group_scatter(g, (blockIdx.x - kOrderBlocks) * 256 + threadIdx.x, job.n);
+  if (blockIdx.x >= number_blocks) {
+    group_scatter(g, (blockIdx.x - number_blocks) * 256 + threadIdx.x, job.n);
     return;
   }
-  if (blockIdx.x == 0 && threadIdx.x == 0)
-    *job.redo = (g.hdr->err != 0 || g.hdr->max_count > kHeavyMax) ? 1u : 0u;
+  if (blockIdx.x == 0 && threadIdx.x == 0) *job.redo = g.hdr->err != 0 ? 1u : 0u;
   const uint32_t nb = uint32_t(g.hdr->totals >> kBricksShift), lane = threadIdx.x & 63;
   const uint32_t w = __builtin_amdgcn_readfirstlane(blockIdx.x * 4 + (threadIdx.x >> 6));
-  for (uint32_t i0 = w * kOrderBricks; i0 < nb; i0 += kOrderBlocks * 4 * kOrderBricks) {
+  for (uint32_t i0 = w * kOrderBricks; i0 < nb; i0 += number_blocks * 4 * kOrderBricks) {
     uint64_t key[kOrderBricks];
     uint32_t slot[kOrderBricks], base[kOrderBricks];
 #pragma unroll
@@ -328,11 +340,23 @@ hipError_t reorder_by_target(vgicp_factorset_s *fs, const double *poses, hipStre
 
 namespace {
 
-// Orders the clouds `which` one by one with a radix sort of their Morton keys,
-// into the copies out names.  Enqueued on st and synchronized.
-hipError_t sort_sources(const vgicp_cloud *sources, const std::vector<int32_t> &which,
-                        const std::vector<double> &cell, const std::vector<SortedSource> &out,
-                        unsigned long long *d_bad, hipStream_t st) {
+// ctx's scratch, at least `bytes` of it, free for this call's use.
+hipError_t reserve_scratch(vgicp_ctx ctx, size_t bytes) {
+  const hipError_t e = claim_scratch(ctx);
+  if (e != hipSuccess) return e;
+  std::string msg;
+  const int rc = ensure_scratch(ctx, bytes, msg);
+  return rc == VGICP_OK       ? hipSuccess
+         : rc == VGICP_ENOMEM ? hipErrorOutOfMemory
+                              : hipErrorUnknown;
+}
+
+// Enqueues the ordering of the clouds `which`, one by one, with a radix sort of
+// their Morton keys in ctx's scratch, into the copies out names.
+hipError_t sort_sources(vgicp_ctx ctx, const vgicp_cloud *sources,
+                        const std::vector<int32_t> &which, const std::vector<double> &cell,
+                        const std::vector<SortedSource> &out, unsigned long long *d_bad) {
+  const hipStream_t st = ctx->stream;
   size_t sort_bytes = 0;
   uint32_t nmax = 0;
   for (int32_t s : which) {
@@ -346,9 +370,9 @@ hipError_t sort_sources(const vgicp_cloud *sources, const std::vector<int32_t> &
     nmax = std::max(nmax, uint32_t(sources[s].n));
   }
   const size_t kbytes = align256(8 * size_t(nmax)), ibytes = align256(4 * size_t(nmax));
-  char *tmp = nullptr;
-  hipError_t e = hipMalloc(&tmp, 2 * kbytes + ibytes + align256(sort_bytes));
+  hipError_t e = reserve_scratch(ctx, 2 * kbytes + ibytes + align256(sort_bytes));
   if (e != hipSuccess) return e;
+  char *tmp = static_cast<char *>(ctx->scratch);
   uint64_t *keys_in = reinterpret_cast<uint64_t *>(tmp);
   uint64_t *keys_out = reinterpret_cast<uint64_t *>(tmp + kbytes);
   uint32_t *idx_in = reinterpret_cast<uint32_t *>(tmp + 2 * kbytes);
@@ -372,11 +396,6 @@ hipError_t sort_sources(const vgicp_cloud *sources, const std::vector<int32_t> &
       e = hipGetLastError();
     }
   }
-  // the temporaries are reused cloud after cloud on the stream; free them once
-  // the last gather has run
-  const hipError_t se = hipStreamSynchronize(st);
-  if (e == hipSuccess) e = se;
-  (void)hipFree(tmp);
   return e;
 }
 
@@ -416,11 +435,8 @@ hipError_t group_sources(vgicp_ctx ctx, const vgicp_cloud *sources,
     most = std::max(most, at);
   };
   place(nullptr);
-  const hipError_t claimed = claim_scratch(ctx);
-  if (claimed != hipSuccess) return claimed;
-  std::string msg;
-  const int rc = ensure_scratch(ctx, most, msg);
-  if (rc != VGICP_OK) return rc == VGICP_ENOMEM ? hipErrorOutOfMemory : hipErrorUnknown;
+  hipError_t e = reserve_scratch(ctx, most);
+  if (e != hipSuccess) return e;
   char *base = static_cast<char *>(ctx->scratch);
   place(base);
   head = 0;
@@ -439,21 +455,22 @@ hipError_t group_sources(vgicp_ctx ctx, const vgicp_cloud *sources,
   }
   order.jobs.resize(count * sizeof(OrderJob));
   std::memcpy(order.jobs.data(), jobs.data(), order.jobs.size());
-  hipError_t e = hipMemcpyAsync(d_jobs, order.jobs.data(), order.jobs.size(),
-                                hipMemcpyHostToDevice, st);
+  e = hipMemcpyAsync(d_jobs, order.jobs.data(), order.jobs.size(), hipMemcpyHostToDevice, st);
   for (size_t b = 0; b < batch.size() && e == hipSuccess; ++b) {
     const size_t k0 = batch[b], k1 = b + 1 < batch.size() ? batch[b + 1] : count;
-    uint32_t nmax = 0, slots = 0;
+    uint32_t nmax = 0, slots = 0, insert = 0;
     for (size_t k = k0; k < k1; ++k) {
       nmax = std::max(nmax, jobs[k].n);
       slots = std::max(slots, 1u << jobs[k].g.log2slots);
+      insert = std::max(insert, insert_grid(jobs[k].n));
     }
     const unsigned nj = unsigned(k1 - k0), points = (nmax + 255) / 256;
+    const unsigned number = std::max(kOrderCloudBlocks, kOrderBlocks / nj);
     const OrderJob *d = d_jobs + k0;
     k_order_clear<<<dim3(slots / 16, nj), 256, 0, st>>>(d);
-    k_order_insert<<<dim3(points, nj), 256, 0, st>>>(d);
+    k_order_insert<<<dim3(insert, nj), 256, 0, st>>>(d);
     k_order_compact<<<dim3(slots / kCompactSlots, nj), kCompactThreads, 0, st>>>(d);
-    k_order_number<<<dim3(kOrderBlocks + points, nj), 256, 0, st>>>(d);
+    k_order_number<<<dim3(number + points, nj), 256, 0, st>>>(d, number);
     k_order_place<<<dim3(points, nj), 256, 0, st>>>(d, order.d_bad);
     e = hipGetLastError();
   }
@@ -514,21 +531,23 @@ hipError_t finish_sorted_sources(vgicp_ctx ctx, const vgicp_cloud *sources,
   if (!order.buffer) return hipStreamSynchronize(st);
   // the counts and the grouped clouds' words
   std::vector<unsigned long long> words(2 + (order.grouped.size() + 1) / 2);
-  const size_t bytes = 2 * sizeof(unsigned long long) + order.grouped.size() * sizeof(uint32_t);
-  hipError_t e = hipMemcpyAsync(words.data(), order.d_bad, bytes, hipMemcpyDeviceToHost, st);
-  hipError_t se = hipStreamSynchronize(st);
-  if (e == hipSuccess) e = se;
-  if (e != hipSuccess) return drop_copies(ctx, order, e);
-  const uint32_t *redo = reinterpret_cast<const uint32_t *>(words.data() + 2);
-  for (size_t k = 0; k < order.grouped.size(); ++k)
-    if (redo[k]) order.sorted.push_back(order.grouped[k]);
+  auto fetch = [&](size_t bytes) {
+    const hipError_t e =
+        hipMemcpyAsync(words.data(), order.d_bad, bytes, hipMemcpyDeviceToHost, st);
+    const hipError_t se = hipStreamSynchronize(st);
+    return e == hipSuccess ? se : e;
+  };
+  hipError_t e = hipSuccess;
+  if (!order.grouped.empty()) {
+    e = fetch(2 * sizeof(unsigned long long) + order.grouped.size() * sizeof(uint32_t));
+    if (e != hipSuccess) return drop_copies(ctx, order, e);
+    const uint32_t *redo = reinterpret_cast<const uint32_t *>(words.data() + 2);
+    for (size_t k = 0; k < order.grouped.size(); ++k)
+      if (redo[k]) order.sorted.push_back(order.grouped[k]);
+  }
   if (!order.sorted.empty()) {
-    e = sort_sources(sources, order.sorted, cell, order.out, order.d_bad, st);
-    if (e == hipSuccess)
-      e = hipMemcpyAsync(words.data(), order.d_bad, 2 * sizeof(unsigned long long),
-                         hipMemcpyDeviceToHost, st);
-    se = hipStreamSynchronize(st);
-    if (e == hipSuccess) e = se;
+    e = sort_sources(ctx, sources, order.sorted, cell, order.out, order.d_bad);
+    if (e == hipSuccess) e = fetch(2 * sizeof(unsigned long long));
     if (e != hipSuccess) return drop_copies(ctx, order, e);
   }
   order.nonfinite[0] = int64_t(words[0]);

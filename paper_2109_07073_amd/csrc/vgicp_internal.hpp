@@ -302,6 +302,10 @@ constexpr uint32_t kErrRange = 2u;
 // construction, the counts of the grouped one, and the scratch's last use.
 constexpr int kCountsWord = 4, kScratchWord = 12;
 
+// How a call leaves a context's scratch (see vgicp_context_s): nothing enqueued
+// uses it; something does, until a word is written; something does.
+enum { kScratchFree, kScratchWordFollows, kScratchInUse };
+
 // Waits until arrived() is true, which a kernel on st makes it by writing to
 // pinned memory: for a while by looking, which saves the runtime's wake-up,
 // then (a stream with much work before it) by synchronizing st.  Returns
@@ -352,14 +356,14 @@ struct vgicp_context_s {
   // Growable scratch for voxelization and for ordering a factor set's clouds.
   void *scratch = nullptr;
   size_t scratch_bytes = 0;
-  // A voxelization returns while its last kernels still read the scratch; the
-  // last of them writes scratch_seq to the word kScratchWord of host_pinned.
-  // Whether that is pending, and whether the stream has been set since the
-  // scratch was last claimed.  (A word rather than the old stream, which the
+  // How the last call left the scratch, and whether the stream has been set since
+  // the scratch was last claimed.  A voxelization returns while its last kernels
+  // still read it; the last of a grouped one writes scratch_seq to the word
+  // kScratchWord of host_pinned.  (A word rather than the old stream, which the
   // caller may have destroyed by then, or an event, whose record makes a
   // voxelization of 20,011 points and its export take 81 us instead of 47.)
+  int scratch_left = vgicp::kScratchFree;
   uint32_t scratch_seq = 0;
-  bool scratch_pending = false;
   bool stream_set = false;
   uint32_t *err_word = nullptr;       // device
   // pinned host words (64 bytes) for small readbacks: see kCountsWord

@@ -9,7 +9,7 @@
 // Clouds of at most kGroupMaxPoints points are grouped by brick in a hash
 // table (group.hpp): six launches and one wait of the host.
 // Larger clouds, and the few whose bricks do not fit the table or that put
-// more than kHeavyMax points in one voxel, are sorted instead: keys -> radix
+// more than kVoxelMax points in one voxel, are sorted instead: keys -> radix
 // sort of (key, point index) -> segment heads -> scan -> segment starts ->
 // [host sync: voxel count] -> per voxel its brick-major sort key -> radix sort
 // of (brick key and bit, voxel ordinal) -> brick heads -> scan -> brick starts
@@ -68,14 +68,28 @@ k_segment_heads(const uint64_t *__restrict__ sorted_keys, int64_t n, uint32_t *_
   head[i] = (i == 0 || sorted_keys[i] != sorted_keys[i - 1]) ? 1u : 0u;
 }
 
-// ord1[i] is the inclusive scan of head: the 1-based ordinal of element i.
+// What the host waits for in the sorted construction (pinned): the points'
+// error bits and the number of segments; `seq` is written last.
+struct SegmentCounts {
+  uint32_t err, n, seq;
+};
+static_assert(sizeof(SegmentCounts) <= kCountsWord * sizeof(uint32_t), "words of their own");
+
+// ord1[i] is the inclusive scan of head: the 1-based ordinal of element i.  err
+// (may be NULL) holds the points' error bits.
 __global__ void __launch_bounds__(256)
 k_segment_starts(const uint32_t *__restrict__ head, const uint32_t *__restrict__ ord1, int64_t n,
-                 uint32_t *__restrict__ seg) {
+                 uint32_t *__restrict__ seg, const uint32_t *__restrict__ err, SegmentCounts *host,
+                 uint32_t seq) {
   const int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
   if (i >= n) return;
   if (head[i]) seg[ord1[i] - 1] = uint32_t(i);
-  if (i == n - 1) seg[ord1[i]] = uint32_t(n);
+  if (i == n - 1) {
+    seg[ord1[i]] = uint32_t(n);
+    host->err = err ? *err : 0u;
+    host->n = ord1[i];
+    __hip_atomic_store(&host->seq, seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+  }
 }
 
 // Record i of an empty table, and word i of its bitset.
@@ -159,9 +173,21 @@ k_build_bricks(const uint64_t *__restrict__ bsort, const uint32_t *__restrict__ 
   insert_record(brick_key_of_sort_key(bsort[d0]), mask, d0, bricks, log2cap, occ, occ_mask);
 }
 
+// Coordinates and covariance of point p.
+__device__ __forceinline__ void gather_point(const float *__restrict__ xyz,
+                                             const float *__restrict__ cov, uint32_t n, uint32_t p,
+                                             float v[9]) {
+  v[0] = xyz[p], v[1] = xyz[uint64_t(n) + p], v[2] = xyz[2ull * n + p];
+  const float2 *c = reinterpret_cast<const float2 *>(cov + 6ull * p);
+#pragma unroll
+  for (int a = 0; a < 3; ++a) v[3 + 2 * a] = c[a].x, v[4 + 2 * a] = c[a].y;
+}
+
 // One thread per voxel, by dense (brick-major) position d: sequential FP64
 // sums over the voxel's points in point order, one FP64 division, one
-// rounding to FP32.
+// rounding to FP32.  Bound by the fullest voxels, whose points are gathered one
+// dependent pair of loads after the other: kPayloadPoints are in flight at once.
+constexpr uint32_t kPayloadPoints = 8;
 __global__ void __launch_bounds__(256)
 k_build_payload(const float *__restrict__ xyz, const float *__restrict__ cov, int64_t n,
                 const uint32_t *__restrict__ sorted_idx, const uint32_t *__restrict__ seg,
@@ -174,12 +200,27 @@ k_build_payload(const float *__restrict__ xyz, const float *__restrict__ cov, in
   const uint32_t b = seg[v], e = seg[v + 1];
   double sm[3] = {0.0, 0.0, 0.0};
   double sc[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
-  for (uint32_t j = b; j < e; ++j) {
-    const uint32_t p = sorted_idx[j];
+  auto add = [&](const float *p) {
 #pragma unroll
-    for (int a = 0; a < 3; ++a) sm[a] += double(xyz[a * n + p]);
+    for (int a = 0; a < 3; ++a) sm[a] += double(p[a]);
 #pragma unroll
-    for (int a = 0; a < 6; ++a) sc[a] += double(cov[6 * int64_t(p) + a]);
+    for (int a = 0; a < 6; ++a) sc[a] += double(p[3 + a]);
+  };
+  uint32_t j = b;
+  for (; j + kPayloadPoints <= e; j += kPayloadPoints) {
+    uint32_t p[kPayloadPoints];
+    float x[kPayloadPoints][9];
+#pragma unroll
+    for (uint32_t u = 0; u < kPayloadPoints; ++u) p[u] = sorted_idx[j + u];
+#pragma unroll
+    for (uint32_t u = 0; u < kPayloadPoints; ++u) gather_point(xyz, cov, uint32_t(n), p[u], x[u]);
+#pragma unroll
+    for (uint32_t u = 0; u < kPayloadPoints; ++u) add(x[u]);
+  }
+  for (; j < e; ++j) {
+    float x[9];
+    gather_point(xyz, cov, uint32_t(n), sorted_idx[j], x);
+    add(x);
   }
   const double cnt = double(e - b);
   VoxelStats st;
@@ -205,11 +246,16 @@ k_build_payload(const float *__restrict__ xyz, const float *__restrict__ cov, in
 //            summed in that order in FP64; per brick: the lexicographic
 //            ordinals of its voxels; the table's empty records;
 //   records  per brick: its record.
-// A call on 20,011 returns takes 46 us (180 us by sorting), on a merged submap
-// of 320,000 points 97 us (476 us; 102 us with four other bricks in a lane's
-// flight while numbering and each brick's own loads one after the other).  The
-// insert takes 31 us of those, bound by 142,000 atomics.  Beyond kGroupMaxPoints
-// the counters' share shrinks and the sort is bound by its passes, so it stays.
+// A call on 20,011 returns takes 46 us (185 us by sorting), on a merged submap
+// of 320,000 points at 0.5 m 84 us (480 us; 7 us more with four other bricks in a
+// lane's flight while numbering and each brick's own loads one after the other).
+// What can tell that a cloud does not fit is the insert, so a cloud that is
+// sorted in the end pays for it, most where it has too many bricks: 320,000
+// points at 0.05 m (60,600) take 510 us, sorted at once 400, and 2^20 at 0.1 m
+// (38,400) 615 and 525.  From about 18,000 bricks at 32,768 slots on it is one or
+// the other; there grouping takes 280 us (320,000 points at 0.1 m) and sorting
+// 365.
+constexpr uint32_t kVoxelMax = 4096;  // points of a voxel at most: they are ordered in LDS
 constexpr uint32_t kNumberBlocks = 512;
 constexpr uint32_t kNumberBricks = 4;  // bricks a wave numbers at once
 constexpr uint32_t kNumberLoads = 8;   // other bricks a lane has in flight
@@ -227,21 +273,29 @@ struct VoxelGroup : Group {
   uint32_t *heavy;         // voxels of more than kLightMax points
 };
 
+// The brick and cell of a point, as group.hpp asks for them.
+struct VoxelOfPoint {
+  const float *xyz;
+  uint32_t n;
+  float s;
+  __device__ uint32_t operator()(uint32_t i, uint64_t &brick, uint32_t &cell) const {
+    int32_t k[3];
+    const uint32_t bad = point_key(xyz, n, i, s, k);
+    brick = brick_key(brick_field(k[0]), brick_field(k[1]), brick_field(k[2]));
+    cell = brick_bit(k[0], k[1], k[2]);
+    return bad;
+  }
+};
+
 __global__ void __launch_bounds__(256)
-k_group_clear(VoxelGroup g) {
+k_group_clear(VoxelGroup g, uint32_t *__restrict__ err_word) {
   group_clear(g, blockIdx.x);
+  if (blockIdx.x == 0 && threadIdx.x == 0) *err_word = 0;  // for a sorted construction
 }
 
 __global__ void __launch_bounds__(256)
-k_group_insert(VoxelGroup g, const float *__restrict__ xyz, uint32_t n, float s) {
-  group_insert(g, blockIdx.x * 256 + threadIdx.x, n,
-               [&](uint32_t i, uint64_t &brick, uint32_t &cell) {
-                 int32_t k[3];
-                 const uint32_t bad = point_key(xyz, n, i, s, k);
-                 brick = brick_key(brick_field(k[0]), brick_field(k[1]), brick_field(k[2]));
-                 cell = brick_bit(k[0], k[1], k[2]);
-                 return bad;
-               });
+k_group_insert(VoxelGroup g, VoxelOfPoint key) {
+  group_insert(g, blockIdx.x, key.n, kVoxelMax, key);
 }
 
 __global__ void __launch_bounds__(kCompactThreads)
@@ -332,16 +386,6 @@ k_group_number(VoxelGroup g, uint32_t number_blocks, uint32_t n, GroupCounts *ho
       }
     }
   }
-}
-
-// Coordinates and covariance of point p.
-__device__ __forceinline__ void gather_point(const float *__restrict__ xyz,
-                                             const float *__restrict__ cov, uint32_t n, uint32_t p,
-                                             float v[9]) {
-  v[0] = xyz[p], v[1] = xyz[uint64_t(n) + p], v[2] = xyz[2ull * n + p];
-  const float2 *c = reinterpret_cast<const float2 *>(cov + 6ull * p);
-#pragma unroll
-  for (int a = 0; a < 3; ++a) v[3 + 2 * a] = c[a].x, v[4 + 2 * a] = c[a].y;
 }
 
 // Adds m values to acc one after the other.
@@ -569,12 +613,6 @@ k_group_records(VoxelGroup g, uint32_t n_bricks, BrickRecord *__restrict__ brick
   if (s < n_bricks) insert_record(key, mask, base, bricks, log2cap, occ, occ_mask);
 }
 
-// The same after a sorted construction, whose last kernel has too many blocks to
-// count (a launch is a hundredth of its time).
-__global__ void k_write_word(uint32_t *host, uint32_t seq) {
-  __hip_atomic_store(host, seq, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-}
-
 __global__ void __launch_bounds__(256)
 k_export(const VoxelStats *__restrict__ stats, const VoxelInfo *__restrict__ info,
          int64_t n_voxels, int32_t *__restrict__ keys, float *__restrict__ mean,
@@ -686,33 +724,33 @@ namespace vgicp {
 
 hipError_t claim_scratch(vgicp_ctx ctx) {
   if (!ctx->stream_set) return hipSuccess;
-  if (ctx->scratch_pending) {
-    const uint32_t *word = ctx->host_pinned + kScratchWord;
-    auto done = [&] { return __atomic_load_n(word, __ATOMIC_ACQUIRE) == ctx->scratch_seq; };
+  const uint32_t *word = ctx->host_pinned + kScratchWord;
+  auto done = [&] { return __atomic_load_n(word, __ATOMIC_ACQUIRE) == ctx->scratch_seq; };
+  if (ctx->scratch_left == kScratchWordFollows) {
     for (int spin = 0; spin < 20000 && !done(); ++spin) __builtin_ia32_pause();
-    if (!done()) {
-      const hipError_t e = hipDeviceSynchronize();
-      if (e != hipSuccess) return e;
-    }
-    ctx->scratch_pending = false;
+    if (done()) ctx->scratch_left = kScratchFree;
+  }
+  if (ctx->scratch_left != kScratchFree) {
+    const hipError_t e = hipDeviceSynchronize();
+    if (e != hipSuccess) return e;
+    ctx->scratch_left = kScratchFree;
   }
   ctx->stream_set = false;
   return hipSuccess;
 }
 
-// A call's use of the scratch: it ends with the kernel that writes the word, or,
-// where the call returns before that kernel is enqueued, with the stream's work.
+// A call's use of the scratch, which a call that returns early ends itself.
 struct ScratchUse {
   vgicp_ctx ctx;
   const bool any;  // an empty cloud uses none
-  bool word_follows = false;
+  int left = kScratchFree;
   ScratchUse(vgicp_ctx c, bool used) : ctx(c), any(used) {
     if (any) __atomic_store_n(ctx->host_pinned + kScratchWord, ~++ctx->scratch_seq, __ATOMIC_RELAXED);
   }
   ~ScratchUse() {
     if (!any) return;
-    if (!word_follows) (void)hipStreamSynchronize(ctx->stream);
-    ctx->scratch_pending = word_follows;
+    if (left == kScratchFree) (void)hipStreamSynchronize(ctx->stream);
+    ctx->scratch_left = left;
   }
 };
 
@@ -762,8 +800,9 @@ static int group_points(vgicp_ctx ctx, const vgicp_cloud *cloud, float s, uint32
   const uint32_t seq = ++ctx->group_seq;
   __atomic_store_n(&host->seq, ~seq, __ATOMIC_RELAXED);
   const uint32_t points = grid_for(n), number = std::min(kNumberBlocks, grid_for(n, 16));
-  k_group_clear<<<slots / 16, 256, 0, st>>>(*g);
-  k_group_insert<<<points, 256, 0, st>>>(*g, cloud->xyz, n, s);
+  const VoxelOfPoint key{cloud->xyz, n, s};
+  k_group_clear<<<slots / 16, 256, 0, st>>>(*g, ctx->err_word);
+  k_group_insert<<<insert_grid(n), 256, 0, st>>>(*g, key);
   k_group_compact<<<slots / kCompactSlots, kCompactThreads, 0, st>>>(*g);
   k_group_number<<<number + points, 256, 0, st>>>(*g, number, n, host_dev, seq);
   HIP_TRY(hipGetLastError());
@@ -772,7 +811,7 @@ static int group_points(vgicp_ctx ctx, const vgicp_cloud *cloud, float s, uint32
   HIP_TRY(wait_for_host_words(
       st, [&] { return __atomic_load_n(&host->seq, __ATOMIC_ACQUIRE) == seq; }));
   *counts = *host;
-  *taken = !(counts->err & kErrFull) && counts->max_count <= kHeavyMax;
+  *taken = !(counts->err & kErrFull);
   return VGICP_OK;
 }
 
@@ -804,9 +843,22 @@ int voxelize_impl(vgicp_ctx ctx, const vgicp_cloud *cloud, double resolution, vg
   uint32_t *const pinned_dev = static_cast<uint32_t *>(pinned);
   if (n > 0) HIP_TRY(claim_scratch(ctx));
   ScratchUse use(ctx, n > 0);
+  // the sorted construction's counts
+  auto *segments = reinterpret_cast<SegmentCounts *>(ctx->host_pinned);
+  auto *segments_dev = reinterpret_cast<SegmentCounts *>(pinned_dev);
+  auto next_seq = [&] {
+    const uint32_t seq = ++ctx->group_seq;
+    __atomic_store_n(&segments->seq, ~seq, __ATOMIC_RELAXED);
+    return seq;
+  };
+  auto segments_arrive = [&](uint32_t seq) {
+    return wait_for_host_words(
+        st, [&] { return __atomic_load_n(&segments->seq, __ATOMIC_ACQUIRE) == seq; });
+  };
   if (n > 0 && n <= kGroupMaxPoints) {
     int rc = group_points(ctx, cloud, s, pinned_dev, &group, &counts, &grouped, msg);
-    if (rc == VGICP_OK) rc = point_error(counts.err, msg);
+    // (of a cloud that is sorted instead, not every point has been looked at)
+    if (rc == VGICP_OK && grouped) rc = point_error(counts.err, msg);
     if (rc != VGICP_OK) return rc;
     if (grouped) {
       n_voxels = counts.n_voxels;
@@ -820,7 +872,7 @@ int voxelize_impl(vgicp_ctx ctx, const vgicp_cloud *cloud, double resolution, vg
     if (rc != VGICP_OK) return rc;
     sc = carve(ctx->scratch, n, std::max(sort_bytes, scan_bytes));
 
-    HIP_TRY(hipMemsetAsync(ctx->err_word, 0, sizeof(uint32_t), st));
+    if (n > kGroupMaxPoints) HIP_TRY(hipMemsetAsync(ctx->err_word, 0, sizeof(uint32_t), st));
     k_voxel_keys<<<grid_for(n), 256, 0, st>>>(cloud->xyz, n, s, sc.keys_in, sc.idx_in,
                                                ctx->err_word);
     HIP_TRY(hipGetLastError());
@@ -832,16 +884,14 @@ int voxelize_impl(vgicp_ctx ctx, const vgicp_cloud *cloud, double resolution, vg
     tb = sc.temp_bytes;
     HIP_TRY(rocprim::inclusive_scan(sc.temp, tb, sc.head, sc.ord1, size_t(n),
                                     rocprim::plus<uint32_t>(), st));
-    k_segment_starts<<<grid_for(n), 256, 0, st>>>(sc.head, sc.ord1, n, sc.seg);
+    const uint32_t seq = next_seq();
+    k_segment_starts<<<grid_for(n), 256, 0, st>>>(sc.head, sc.ord1, n, sc.seg, ctx->err_word,
+                                                   segments_dev, seq);
     HIP_TRY(hipGetLastError());
-    HIP_TRY(hipMemcpyAsync(ctx->host_pinned, ctx->err_word, sizeof(uint32_t),
-                           hipMemcpyDeviceToHost, st));
-    HIP_TRY(hipMemcpyAsync(ctx->host_pinned + 1, sc.ord1 + (n - 1), sizeof(uint32_t),
-                           hipMemcpyDeviceToHost, st));
-    HIP_TRY(hipStreamSynchronize(st));
-    const int prc = point_error(ctx->host_pinned[0], msg);
+    HIP_TRY(segments_arrive(seq));
+    const int prc = point_error(segments->err, msg);
     if (prc != VGICP_OK) return prc;
-    n_voxels = int64_t(ctx->host_pinned[1]);
+    n_voxels = int64_t(segments->n);
   }
 
   // Brick order: sort the voxels by (brick key, position in the brick).
@@ -880,19 +930,18 @@ int voxelize_impl(vgicp_ctx ctx, const vgicp_cloud *cloud, double resolution, vg
       pe = rocprim::inclusive_scan(temp, tb, bhead, bord1, size_t(V), rocprim::plus<uint32_t>(),
                                    st);
     if (pe == hipSuccess) {
-      k_segment_starts<<<grid_for(V), 256, 0, st>>>(bhead, bord1, V, sc.bstart);
+      const uint32_t seq = next_seq();
+      k_segment_starts<<<grid_for(V), 256, 0, st>>>(bhead, bord1, V, sc.bstart, nullptr,
+                                                     segments_dev, seq);
       pe = hipGetLastError();
+      if (pe == hipSuccess) pe = segments_arrive(seq);
     }
-    if (pe == hipSuccess)
-      pe = hipMemcpyAsync(ctx->host_pinned + 1, bord1 + (V - 1), sizeof(uint32_t),
-                          hipMemcpyDeviceToHost, st);
-    if (pe == hipSuccess) pe = hipStreamSynchronize(st);
     if (own_temp) {
       (void)hipStreamSynchronize(st);
       (void)hipFree(own_temp);
     }
     HIP_TRY(pe);
-    n_bricks = int64_t(ctx->host_pinned[1]);
+    n_bricks = int64_t(segments->n);
   }
 
   // Load factor at most 1/8: a lookup in an empty brick (most misses of a
@@ -959,7 +1008,6 @@ int voxelize_impl(vgicp_ctx ctx, const vgicp_cloud *cloud, double resolution, vg
                                                         sc.seg, vord_out, vkey, n_voxels,
                                                         m->stats, m->info);
   }
-  if (!grouped && n > 0) k_write_word<<<1, 1, 0, st>>>(pinned_dev + kScratchWord, ctx->scratch_seq);
   e = hipGetLastError();
   if (e != hipSuccess) {
     (void)hipFree(m->buffer);
@@ -967,7 +1015,7 @@ int voxelize_impl(vgicp_ctx ctx, const vgicp_cloud *cloud, double resolution, vg
     msg = std::string("vgicp_voxelize: kernel launch: ") + hipGetErrorString(e);
     return VGICP_EHIP;
   }
-  use.word_follows = true;
+  use.left = grouped ? kScratchWordFollows : kScratchInUse;
   *out = m;
   return VGICP_OK;
 }

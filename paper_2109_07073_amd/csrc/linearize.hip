@@ -1221,6 +1221,14 @@ constexpr int tile_sums() {
   return PAIR ? kNumPairSums : LIN ? kNumSums : 1;
 }
 
+// Whether a variant computes its factors' constants in every tile also where a
+// round could read them from the table.  The gated one: compiled with the table's
+// branch it ran 13 % slower on the full-size precision workload.  The pair form's
+// mixed one, for its spills (see add_pair_terms).
+constexpr bool tiles_compute_consts(int accum, bool pair, int fuse) {
+  return fuse == kFuseGate || (pair && accum == VGICP_ACC_MIXED && fuse == kFuse64);
+}
+
 // PAIR: the pair form's 91 sums of the tile go to partials_pair (stride
 // kPairStride), its counters to partials as in the source-frame form.
 template <int ACC, bool LIN, bool R64, bool CORR, int FUSE, bool PAIR = false>
@@ -1259,11 +1267,9 @@ __device__ __forceinline__ void linearize_tile(
   uint32_t ow[kOccWordsPerThread];
   tile_loads<kChunk>(fd, ow, cur, [&](uint32_t r, float v[3]) { load_row(cx, first, r, v); });
   // the relative pose (from the round's table when there is one) while the
-  // loads are in flight.  The gated variant always computes it: compiled with
-  // the table's branch it ran 13 % slower on the full-size precision workload.
-  // So does the pair form's mixed variant, for its spills.
+  // loads are in flight
   FactorConsts k;
-  if constexpr (FUSE == kFuseGate || (PAIR && ACC == VGICP_ACC_MIXED && FUSE == kFuse64))
+  if constexpr (tiles_compute_consts(ACC, PAIR, FUSE))
     k = factor_consts(fd, poses);
   else
     k = consts ? consts[td.factor] : factor_consts(fd, poses);
@@ -2060,8 +2066,25 @@ k_factor_consts(const FactorDesc *__restrict__ factors, int64_t n, const double 
   out[f] = factor_consts_lane(factors[f], poses);
 }
 
-hipError_t launch_factor_consts(const vgicp_factorset_s *fs, const double *poses, hipStream_t st) {
-  if (!fs->d_consts || fs->n_factors <= 0) return hipSuccess;
+// Rounds of more tiles than this read their factors' constants from a table
+// that one launch writes first; smaller rounds compute them in every tile,
+// while its first loads are in flight.  The launch takes 2.5 us and a gap, the
+// constants about 190 VALU instructions per wave and tile: without the table a
+// round of 500 factors in 3,500 tiles takes 84.6 us instead of 86.3 and a
+// submap's iteration (two rounds of 1,216 tiles) 43.0 us instead of 45.7,
+// while 4,500 factors in 12,144 tiles take 0.2 to 1.1 % longer.
+constexpr int64_t kConstsTableTiles = 4096;
+
+// Writes the table of a round over the whole tile table where its kernel reads
+// one; *consts is the table, or NULL.
+hipError_t launch_round_consts(const vgicp_factorset_s *fs, int accum, int fused, float kappa,
+                               bool pair, const double *poses, hipStream_t st,
+                               const void **consts) {
+  *consts = nullptr;
+  const int fuse = fused == VGICP_FUSED_F64 ? kFuse64 : kappa > 0.f ? kFuseGate : kFuse32;
+  if (!fs->d_consts || fs->n_tiles <= kConstsTableTiles || tiles_compute_consts(accum, pair, fuse))
+    return hipSuccess;
+  *consts = fs->d_consts;
   k_factor_consts<<<unsigned((fs->n_factors + 63) / 64), 64, 0, st>>>(
       fs->d_factors, fs->n_factors, poses, static_cast<FactorConsts *>(fs->d_consts));
   return hipGetLastError();
@@ -2070,7 +2093,7 @@ hipError_t launch_factor_consts(const vgicp_factorset_s *fs, const double *poses
 // Launches over the tiles tb + k * stride, k < te - tb (stride 1: the range
 // [tb, te) of the tile table; a factor's own tiles: its tile_begin, n_tiles
 // and tile_stride).  `consts` (may be NULL: every tile computes its factor's
-// constants) is the table launch_factor_consts wrote for these poses.
+// constants) is the table launch_round_consts wrote for these poses.
 hipError_t launch_linearize_into(const vgicp_factorset_s *fs, int accum, int resid, int fused,
                                  float kappa, bool lin, int64_t tb, int64_t te,
                                  const double *poses, double *partials, int32_t *corr,

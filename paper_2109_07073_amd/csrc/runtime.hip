@@ -17,7 +17,9 @@ int map_export_impl(vgicp_ctx ctx, vgicp_map m, int32_t *keys, float *mean, floa
 hipError_t launch_linearize(const vgicp_factorset_s *fs, int accum, int resid, int fused,
                             float kappa, bool lin, int64_t tb, int64_t te, const double *poses, int32_t *corr,
                             hipStream_t st, int32_t stride = 1, const void *consts = nullptr);
-hipError_t launch_factor_consts(const vgicp_factorset_s *fs, const double *poses, hipStream_t st);
+hipError_t launch_round_consts(const vgicp_factorset_s *fs, int accum, int fused, float kappa,
+                               bool pair, const double *poses, hipStream_t st,
+                               const void **consts);
 hipError_t launch_overlap(const vgicp_factorset_s *fs, int64_t tb, int64_t te,
                           const double *poses, hipStream_t st, int32_t stride = 1);
 hipError_t launch_reduce(const vgicp_factorset_s *fs, int64_t f0, int64_t nf, const double *poses,
@@ -681,15 +683,6 @@ namespace {
 constexpr int kKindLinearize = 0;
 constexpr int kKindEvaluate = 1;
 
-// Rounds of more tiles than this read their factors' constants from a table
-// that one launch writes first; smaller rounds compute them in every tile,
-// while its first loads are in flight.  The launch takes 2.5 us and a gap, the
-// constants about 190 VALU instructions per wave and tile: without the table a
-// round of 500 factors in 3,500 tiles takes 84.6 us instead of 86.3 and a
-// submap's iteration (two rounds of 1,216 tiles) 43.0 us instead of 45.7,
-// while 4,500 factors in 12,144 tiles take 0.2 to 1.1 % longer.
-constexpr int64_t kConstsTableTiles = 4096;
-
 }  // namespace
 
 int vgicp::check_common(vgicp_ctx ctx, vgicp_factorset fs, const double *poses, const char *who) {
@@ -762,15 +755,14 @@ hipError_t enqueue_range(vgicp_ctx ctx, vgicp_factorset fs, int kind, int accum,
                          hipStream_t st, int form = VGICP_FORM_SOURCE, int32_t stride = 1) {
   const int tk = kind == kKindLinearize ? VGICP_KERNEL_LINEARIZE : VGICP_KERNEL_EVALUATE;
   hipError_t err = hipSuccess;
-  // a launch over the whole of a large tile table reads the factors' constants
-  // from a table written once for the round; the others compute them in every
-  // tile
+  // a launch over a part of the tile table computes the factors' constants in
+  // every tile
   const void *consts = nullptr;
-  if (tb == 0 && te == fs->n_tiles && f0 == 0 && nf == fs->n_factors && fs->d_consts &&
-      fs->n_tiles > kConstsTableTiles) {
-    err = launch_factor_consts(fs, poses, st);
+  if (tb == 0 && te == fs->n_tiles && f0 == 0 && nf == fs->n_factors) {
+    err = launch_round_consts(fs, accum, fused, kappa,
+                              form == VGICP_FORM_PAIR && kind == kKindLinearize, poses, st,
+                              &consts);
     if (err != hipSuccess) return err;
-    consts = fs->d_consts;
   }
   if (form == VGICP_FORM_PAIR && kind == kKindLinearize) {
     if (ctx) {
@@ -1119,11 +1111,12 @@ int vgicp_factorset_time_kernel(vgicp_ctx ctx, vgicp_factorset fs, const double 
     if (rc) return rc;
   }
   hipEvent_t t0 = nullptr, t1 = nullptr;
-  // the round's constants table, written before the timed launches (a round
-  // writes it once before its linearize launch)
-  hipError_t e = kernel == VGICP_KERNEL_OVERLAP ? hipSuccess
-                                                : launch_factor_consts(fs, poses, ctx->stream);
-  const void *consts = kernel == VGICP_KERNEL_OVERLAP ? nullptr : fs->d_consts;
+  // the constants table of a round that reads one, written before the timed
+  // launches as it is before the round's
+  const void *consts = nullptr;
+  hipError_t e = hipSuccess;
+  if (kernel != VGICP_KERNEL_OVERLAP)
+    e = launch_round_consts(fs, o.accum, o.fused, o.fp64_kappa, pair, poses, ctx->stream, &consts);
   if (e == hipSuccess) e = hipEventCreate(&t0);
   if (e == hipSuccess) e = hipEventCreate(&t1);
   if (e == hipSuccess) e = hipEventRecord(t0, ctx->stream);

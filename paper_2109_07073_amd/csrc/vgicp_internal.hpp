@@ -434,8 +434,8 @@ struct vgicp_factorset_s {
   // and the assembly's lists)
   void *d_tables = nullptr;
   vgicp::FactorDesc *d_factors = nullptr;  // device, in d_tables
-  // device [n_factors] relative-pose constants, rewritten by every round over
-  // the whole tile table before its linearize launch (kFactorConstsBytes each)
+  // device [n_factors] relative-pose constants (kFactorConstsBytes each),
+  // rewritten before its linearize launch by every round that reads them
   void *d_consts = nullptr;
   vgicp::Tile *d_tiles = nullptr;          // device, in d_tables
   bool own_tiles = false;                  // unless they have outgrown it

@@ -172,6 +172,10 @@ const char *vgicp_last_error(vgicp_ctx ctx);
 
 /* Create a context on HIP device `device` that enqueues on `hip_stream` (a
  * hipStream_t; NULL means the default stream).  The stream is borrowed.
+ * A context keeps device workspace from one call to the next, until it is
+ * destroyed: that of its largest voxelization (20,000 points 10 MB, 2^20 points
+ * 40 MB, more points about 72 bytes each), and at most 256 MB for the factor
+ * sets it has created.
  * Errors: EINVAL (out NULL, device out of range), EHIP. */
 int vgicp_ctx_create(int device, void *hip_stream, vgicp_ctx *out);
 
@@ -572,7 +576,9 @@ typedef struct vgicp_server_s *vgicp_server;
 #define VGICP_REQ_OVERLAP 2   /* outputs inliers (= hits), overlap         */
 
 typedef struct {
-  int64_t memory_budget_bytes; /* device bytes for resident frames; 0 = no limit     */
+  int64_t memory_budget_bytes; /* device bytes for resident frames; 0 = no limit
+                                  (the workspace that adding them needs is kept on
+                                  top, as a context's, see vgicp_ctx_create)         */
   int32_t max_batch_factors;   /* factors per batch (slot size), >= 1               */
   int32_t max_batch_points;    /* source points per batch, >= 1                     */
   int32_t max_batch_poses;     /* poses per batch, >= 1                             */

@@ -477,9 +477,19 @@ hipError_t group_sources(vgicp_ctx ctx, const vgicp_cloud *sources,
   return e;
 }
 
+// Gives scratch back that the ordering has grown beyond kScratchKeep, once
+// nothing enqueued uses it.
+void trim_scratch(vgicp_ctx ctx, const SourceOrder &order) {
+  if (ctx->scratch_bytes <= std::max(kScratchKeep, order.scratch_before)) return;
+  (void)hipFree(ctx->scratch);
+  ctx->scratch = nullptr;
+  ctx->scratch_bytes = 0;
+}
+
 // Gives the copies back after an error, once nothing enqueued uses them.
 hipError_t drop_copies(vgicp_ctx ctx, SourceOrder &order, hipError_t e) {
   (void)hipStreamSynchronize(ctx->stream);
+  trim_scratch(ctx, order);
   if (order.buffer) (void)hipFree(order.buffer);
   order.buffer = nullptr;
   order.out.assign(order.out.size(), SortedSource{});
@@ -491,6 +501,7 @@ hipError_t drop_copies(vgicp_ctx ctx, SourceOrder &order, hipError_t e) {
 hipError_t begin_sorted_sources(vgicp_ctx ctx, const vgicp_cloud *sources, int32_t n_sources,
                                 const std::vector<double> &cell, SourceOrder &order) {
   order.out.assign(size_t(n_sources), SortedSource{});
+  order.scratch_before = ctx->scratch_bytes;
   // layout: per used cloud, covariances [n][6], coordinates [n][3], permutation
   // [n]; then the two counts of non-finite points and the grouped clouds' words
   size_t total = 0;
@@ -550,6 +561,7 @@ hipError_t finish_sorted_sources(vgicp_ctx ctx, const vgicp_cloud *sources,
     if (e == hipSuccess) e = fetch(2 * sizeof(unsigned long long));
     if (e != hipSuccess) return drop_copies(ctx, order, e);
   }
+  trim_scratch(ctx, order);
   order.nonfinite[0] = int64_t(words[0]);
   order.nonfinite[1] = int64_t(words[1]);
   return hipSuccess;

@@ -242,7 +242,8 @@ struct SortedSource {
 // sets buffer and out; finish_sorted_sources waits for it (and whatever else was
 // enqueued), makes the copies that have to be sorted, and sets nonfinite to the
 // number of copied points with a non-finite coordinate and with a non-finite
-// covariance entry.  On an error of either, buffer is NULL again.
+// covariance entry.  On an error of either, buffer is NULL again.  Of a scratch
+// that they had to grow the context keeps kScratchKeep bytes at most.
 struct SourceOrder {
   void *buffer = nullptr;
   std::vector<SortedSource> out;
@@ -250,6 +251,7 @@ struct SourceOrder {
   // between the two
   std::vector<int32_t> grouped, sorted;  // clouds to group, and to sort
   std::vector<unsigned char> jobs;       // the grouped ones' table on its way to the device
+  size_t scratch_before = 0;             // bytes of the scratch
   // device, behind the copies: the two counts, then a word per grouped cloud
   // that is set when it has to be sorted
   unsigned long long *d_bad = nullptr;
@@ -327,6 +329,11 @@ hipError_t claim_scratch(vgicp_ctx ctx);
 // Grows ctx's scratch to at least `bytes` (synchronizing its stream when it
 // replaces the old one).  Returns a status and sets msg on failure.
 int ensure_scratch(vgicp_ctx ctx, size_t bytes, std::string &msg);
+
+// Scratch that ordering clouds may leave a context with: that of kOrderWorkspace
+// and some, so that a program's next set finds it, but not the temporaries of
+// clouds that are sorted (some 25 bytes a point).
+constexpr size_t kScratchKeep = size_t(256) << 20;
 
 // Records `msg` as the last error of ctx (or of the calling thread when ctx
 // is NULL) and returns `code`.

@@ -1,0 +1,34 @@
+"""Device memory that a context keeps after a factor set over a large cloud has
+been created and destroyed: 256 MB at most (and the caller's own)."""
+
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("n", [1 << 20, 20_000_000])
+def test_memory_kept_after_a_factor_set(n):
+    import torch
+    from paper_2109_07073_amd import vgicp as vg
+    ctx = vg.Context(0)
+    g = torch.Generator(device="cuda").manual_seed(n)
+    xyz = torch.rand((3, n), generator=g, device="cuda") * 100.0
+    cov = torch.tensor([1.0, 0, 0, 1.0, 0, 1e-3], device="cuda").repeat(n, 1)
+    m = vg.voxelize(ctx, xyz[:, :2000].contiguous(), cov[:2000].contiguous(), 0.5)
+    rows = np.array([(0, 0, 0, 1)], np.int32)
+    torch.cuda.synchronize()
+    before = torch.cuda.mem_get_info()[0]
+    fs = vg.FactorSet(ctx, [(xyz, cov)], [m], rows, 2)
+    assert before - torch.cuda.mem_get_info()[0] >= 40 * n  # its copy
+    fs.destroy()
+    torch.cuda.synchronize()
+    assert before - torch.cuda.mem_get_info()[0] <= (256 + 16) << 20
+    # the next creation finds its workspace again
+    fs = vg.FactorSet(ctx, [(xyz, cov)], [m], rows, 2)
+    poses = torch.eye(3, 4, dtype=torch.float64, device="cuda")[:, :3].reshape(-1)
+    poses = torch.cat([poses, torch.zeros(3, dtype=torch.float64, device="cuda")]).repeat(2, 1)
+    out = vg.evaluate_errors(ctx, fs, poses)
+    ctx.synchronize()
+    assert int(out["inliers"][0]) >= 2000
+    ctx.close()

@@ -370,6 +370,9 @@ void launch_batch(vgicp_server srv, size_t si) {
                         st, true);
   }
   if (e != hipSuccess) {
+    // the launches before the failed one read the slot's staging, which the next
+    // batch writes, and frames, which may be freed
+    (void)hipStreamSynchronize(st);
     s.err = e;
     s.finished = true;  // retired as failed by the worker
   }

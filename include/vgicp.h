@@ -15,8 +15,8 @@
  *     the data_ptr() of a torch tensor on the GPU); "host" pointers are read
  *     before the call returns.
  *   - Work is enqueued on the context's HIP stream.  Device outputs are valid
- *     once that stream has been synchronized.  vgicp_voxelize is the one call
- *     that synchronizes itself (it sizes the map).
+ *     once that stream has been synchronized.  Calls that wait for the device
+ *     themselves say so (vgicp_voxelize does, to size the map).
  *   - Every function returns VGICP_OK (0) or a negative status.  The message of
  *     the last failure is available from vgicp_last_error(ctx) (or with a NULL
  *     ctx for failures that had no valid context).  On failure no output is
@@ -216,9 +216,11 @@ int vgicp_ctx_destroy(vgicp_ctx ctx);
  * ------------------------------------------------------------------------ */
 
 /* Build the voxel map of `cloud` (host struct, device arrays) at `resolution`
- * metres.  Synchronizes the stream once.  The map is library-owned device
- * memory; free it with vgicp_map_free.  The cloud is not referenced after the
- * call returns.
+ * metres.  Waits for the counts of the voxels, not for the map itself: the last
+ * kernels, which read the cloud, may still be enqueued on the stream when the
+ * call returns, so the cloud's memory may be reused by later work on the stream,
+ * or freed or written elsewhere once the stream has got there.  The map is
+ * library-owned device memory; free it with vgicp_map_free.
  * Errors: EINVAL (NULL pointers with n > 0, n outside [0, 2^26], resolution
  * not finite or <= 0, more than 2^24 occupied 4 x 4 x 4 bricks), ENONFINITE,
  * ERANGE, ENOMEM, EHIP. */
@@ -517,7 +519,8 @@ int vgicp_overlap(vgicp_ctx ctx, vgicp_factorset fs, const double *poses, int64_
  * and h_overlap [n_maps] (host float64, may be NULL) receive the counts and
  * rates, h_admitted [n_maps] (host int32) 1 for every map admitted by
  * `threshold` under `rule` (VGICP_GATE_*), *n_admitted (may be NULL) their
- * number.  Synchronizes ctx's stream (the outputs are on the host).
+ * number.  Returns when they are on the host: everything enqueued on ctx's
+ * stream before has run.
  * Errors: EINVAL (NULL or foreign arguments, a non-finite pose or threshold,
  * an unknown rule), ENOMEM, EHIP. */
 int vgicp_connect(vgicp_ctx ctx, const vgicp_cloud *cloud, const double *h_pose,
@@ -548,8 +551,8 @@ typedef struct {
  * h_last_pose (equal when n_submap is 1; all ignored when n_submap is 0).
  * *overlap_last and *overlap_first (may be NULL) receive the overlaps of the
  * frame against the last and first maps (0 when n_submap is 0).  The
- * decision is made in that order: START, SKIP, CLOSE, INSERT.  Synchronizes
- * ctx's stream.  Errors: EINVAL, ENOMEM, EHIP. */
+ * decision is made in that order: START, SKIP, CLOSE, INSERT.  Waits as
+ * vgicp_connect does.  Errors: EINVAL, ENOMEM, EHIP. */
 int vgicp_submap_step(vgicp_ctx ctx, const vgicp_submap_rules *rules, const vgicp_cloud *frame,
                       const double *h_pose, vgicp_map first, const double *h_first_pose,
                       vgicp_map last, const double *h_last_pose, int32_t n_submap,
@@ -592,7 +595,10 @@ typedef struct {
 } vgicp_server_config;
 
 /* Create a server on HIP device `device` with its own streams and worker
- * thread.  Errors: EINVAL, ENOMEM, EHIP. */
+ * thread.  While batches are on the device the worker looks for their outputs
+ * without a pause until 2 ms after the last one ended, on a core of its own, and
+ * then every 50 us, when it also notices a batch that failed; without any it
+ * sleeps.  Errors: EINVAL, ENOMEM, EHIP. */
 int vgicp_server_create(int device, const vgicp_server_config *cfg, vgicp_server *out);
 
 /* Stop the worker after the submitted requests complete and free everything

@@ -83,8 +83,9 @@ int grow(vgicp_ctx ctx, size_t dev_bytes, size_t host_bytes, const char *who) {
 
 // Copies `words` 16-byte words of pinned host memory to the device.  For the
 // tens of kilobytes of a call's tables a launch is cheaper than the copy engine
-// and the hand-over between the two (a call against 199 maps: 30 us, 42 us with
-// hipMemcpyAsync, 48 us with the counts copied back as well).
+// and the hand-over between the two (the C call for 20,000 points against 199
+// maps, by itself: 30 us, 42 us with hipMemcpyAsync, 48 us with the counts copied
+// back as well; the Python binding's argument lists take some 25 us more).
 __global__ void __launch_bounds__(256)
 k_upload(const uint4 *__restrict__ host, uint4 *__restrict__ dev, uint32_t words) {
   const uint32_t i = blockIdx.x * 256 + threadIdx.x;

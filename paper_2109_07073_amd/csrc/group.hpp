@@ -124,15 +124,15 @@ __device__ __forceinline__ void group_clear(const Group &g, uint32_t block) {
 }
 
 // Point i of n.  key(i, brick, cell) sets the point's brick key and its cell in
-// the brick and returns the error bits of a point that is refused.  A brick
-// tries `probes` slots and a cell takes `most` points.
+// the brick and returns the error bits of a point that is refused; a cell takes
+// `most` points.
 // Consecutive points of a scan often fall in one cell (the near rings put
 // hundreds there), so a wave's runs of equal keys look their brick up once and
 // take their arrival numbers with one atomic (320,000 points: 60 us with an
 // atomic each, 28 us by runs).
 template <typename Key>
-__device__ __forceinline__ void group_point(const Group &g, uint32_t i, uint32_t n, uint32_t probes,
-                                            uint32_t most, Key key) {
+__device__ __forceinline__ void group_point(const Group &g, uint32_t i, uint32_t n, uint32_t most,
+                                            Key key) {
   const uint32_t lane = threadIdx.x & 63;
   uint64_t brick = 0;
   uint32_t cell = 0;
@@ -151,7 +151,7 @@ __device__ __forceinline__ void group_point(const Group &g, uint32_t i, uint32_t
     const uint32_t smask = (1u << g.log2slots) - 1u;
     uint32_t h = uint32_t((brick * 0x9E3779B97F4A7C15ull) >> (64 - g.log2slots));
     bad = kErrFull;
-    for (uint32_t p = 0; p < probes; ++p) {
+    for (uint32_t p = 0; p < kGroupProbes; ++p) {
       // a slot's key never changes once set, and a stale empty one only sends
       // the point to the exchange, so a cached one serves (2 us of 320,000
       // points' 35)
@@ -196,16 +196,13 @@ __device__ __forceinline__ bool group_full(const Group &g) {
 
 // The points of one wave of insert_grid's blocks of 256 threads.
 // Of a large cloud a wave takes several groups of 64 points one after the
-// other, so that the first of all waves are a sample of the cloud, and stricter
-// limits for it stop most clouds that have to be sorted before the rest of their
-// points fill the table.  (All at once, an insert ran to its end before anything
-// could be known of it: 105 us for 320,000 points in 60,600 bricks, now 71, and
-// 349 for 2^20 in 127,900, now 103.)  Fewer waves are enough to keep the atomics
-// busy: at 320,000 points a voxelization takes 83 us in 4 groups, 89 in 8 and 93
-// in one, at 2^20 160 in 8 and in 4, 180 in one.  Up to 2^17 points one group
-// each leaves no CU without waves.
-constexpr uint32_t kSampleProbes = 24;  // a third of the table
-
+// other, so that those of a cloud that has to be sorted stop once one has found
+// out.  (All at once, an insert ran to its end before anything could be known of
+// it: 105 us for 320,000 points in 60,600 bricks, now 86, and 349 for 2^20 in
+// 127,900, now 112.)  Fewer waves are enough to keep the atomics busy: at 320,000
+// points a voxelization takes 83 us in 4 groups, 89 in 8 and 93 in one, at 2^20
+// 161 in 8 and in 4, 178 in one.  Up to 2^17 points one group each leaves no CU
+// without waves.
 __host__ __device__ inline uint32_t insert_runs(uint32_t n) {
   return n <= (1u << 17) ? 1u : n <= (1u << 19) ? 4u : 8u;
 }
@@ -219,11 +216,9 @@ __device__ __forceinline__ void group_insert(const Group &g, uint32_t block, uin
                                              uint32_t most, Key key) {
   const uint32_t runs = insert_runs(n);
   const uint32_t first = (block * 256 + (threadIdx.x & ~63u)) * runs + (threadIdx.x & 63u);
-  if (runs == 1) return group_point(g, first, n, kGroupProbes, most, key);
-  group_point(g, first, n, kSampleProbes, 2 * most / runs, key);
-  for (uint32_t r = 1; r < runs; ++r) {
-    if (group_full(g)) return;
-    group_point(g, first + r * 64, n, kGroupProbes, most, key);
+  for (uint32_t r = 0; r < runs; ++r) {
+    if (r > 0 && group_full(g)) return;
+    group_point(g, first + r * 64, n, most, key);
   }
 }
 

@@ -251,8 +251,8 @@ k_build_payload(const float *__restrict__ xyz, const float *__restrict__ cov, in
 // lane's flight while numbering and each brick's own loads one after the other).
 // What can tell that a cloud does not fit is the insert, so a cloud that is
 // sorted in the end pays for it, most where it has too many bricks: 320,000
-// points at 0.05 m (60,600) take 510 us, sorted at once 400, and 2^20 at 0.1 m
-// (38,400) 615 and 525.  From about 18,000 bricks at 32,768 slots on it is one or
+// points at 0.05 m (60,600) take 505 us, sorted at once 400, and 2^20 at 0.1 m
+// (38,400) 620 and 530.  From about 18,000 bricks at 32,768 slots on it is one or
 // the other; there grouping takes 280 us (320,000 points at 0.1 m) and sorting
 // 365.
 constexpr uint32_t kVoxelMax = 4096;  // points of a voxel at most: they are ordered in LDS

@@ -60,6 +60,12 @@ def test_sorted_voxels(vg, ctx, counts):
     check(vg, ctx, *cloud(np.random.default_rng(sum(counts)), counts))
 
 
+@pytest.mark.parametrize("counts", [[4096] + [30] * 5000, [4097] + [30] * 5000, [64] * 2048,
+                                    [64] * 2048 + [1], [64] * 8192 + [1]])
+def test_points_of_several_groups_a_wave(vg, ctx, counts):
+    check(vg, ctx, *cloud(np.random.default_rng(len(counts)), counts))
+
+
 @pytest.mark.parametrize("n", [24000, 32768, 40000, 200000])
 def test_bricks_about_the_table(vg, ctx, n):
     check(vg, ctx, *bricks(np.random.default_rng(n), n))

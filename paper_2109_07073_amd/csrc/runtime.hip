@@ -261,8 +261,9 @@ int vgicp_ctx_create(int device, void *hip_stream, vgicp_ctx *out) {
 
 int vgicp_ctx_set_stream(vgicp_ctx ctx, void *hip_stream) {
   if (!ctx) return fail(nullptr, VGICP_EINVAL, "vgicp_ctx_set_stream: ctx is NULL");
+  // (a program that sets its one stream before every call has nothing to wait for)
+  if (static_cast<hipStream_t>(hip_stream) != ctx->stream) ctx->stream_set = true;
   ctx->stream = static_cast<hipStream_t>(hip_stream);
-  ctx->stream_set = true;
   return VGICP_OK;
 }
 
